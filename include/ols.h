@@ -399,7 +399,10 @@ const char* ols_last_error(void);
 ols_status_t ols_calibration_copy(void* dst, const void* src, size_t bytes, ols_stream_t stream);
 
 /* Number of compute units of the current device as seen by the library, and
- * the persistent grid (workgroups) ols_forward launches for this plan. */
+ * the persistent grid of ols_forward for this plan, in workgroups of `block`
+ * threads (256, or 512 at N = 8192).  A call may run as smaller workgroups with
+ * as many threads in all (one transform, or one wave of them, each), and
+ * launches no more than it has work units. */
 ols_status_t ols_plan_get_launch(ols_plan_t plan, int32_t* grid, int32_t* block, int32_t* cus);
 
 /*
@@ -412,7 +415,9 @@ ols_status_t ols_plan_get_launch(ols_plan_t plan, int32_t* grid, int32_t* block,
  * (segments per workgroup = number of segments / grid).
  *   filters_per_unit   1 or 2 inverse transforms interleaved per unit
  *                      (2 only for N <= 4096, and N <= 2048 for R2R);
- *                      0 restores the library's choice
+ *                      0 restores the library's choice: the most filters a
+ *                      unit may take is reported, each call takes what its
+ *                      size needs
  *   workgroups_per_cu  1 .. the kernel's occupancy; 0 = the occupancy
  * The workgroup count leaves the output bit-identical; the filters-per-unit
  * choice selects another kernel instance, whose results may differ in the

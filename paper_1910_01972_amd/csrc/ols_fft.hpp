@@ -97,9 +97,10 @@ OLS_HD float2 load_c64(P p, int64_t i) {
 }
 
 // ---------------------------------------------------------------------------
-// Compile-time geometry of one N-point transform.
+// Compile-time geometry of one N-point transform, in workgroups of WG_ threads
+// (a multiple of a wave and of the transform's lanes; 0: at least 256).
 // ---------------------------------------------------------------------------
-template <int N_>
+template <int N_, int WG_ = 0>
 struct Geo {
   static constexpr int N = N_;
   static constexpr int R = 16;                       // complex samples per lane
@@ -107,7 +108,7 @@ struct Geo {
   static constexpr int LOG2N = ilog2(N);
   static constexpr int P = (LOG2N + 3) / 4;          // number of passes
   static constexpr int R0 = N >> (4 * (P - 1));      // radix of the first pass
-  static constexpr int WG = G >= 256 ? G : 256;      // threads per workgroup
+  static constexpr int WG = WG_ ? WG_ : (G >= 256 ? G : 256);  // threads per workgroup
   static constexpr int SEGS = WG / G;                // transforms per workgroup
 
   static constexpr int radix(int k) { return k == 0 ? R0 : 16; }
@@ -158,6 +159,7 @@ struct Geo {
 
   static_assert(N >= 256 && N <= 8192 && (N & (N - 1)) == 0, "N must be a power of two in [256, 8192]");
   static_assert(P >= 2, "at least two passes");
+  static_assert(WG % 64 == 0 && WG % G == 0, "whole waves and whole transforms");
 };
 
 // ---------------------------------------------------------------------------

@@ -45,16 +45,17 @@ __device__ __forceinline__ void exchange_sync() {
   }
 }
 
-// Exchanges alternate between two LDS buffers of Geo<N>::LDS elements.  All
+// Exchanges alternate between two LDS buffers of GE::LDS elements (GE: Geo<N> of the workgroup).  All
 // lanes of the workgroup see the same sequence of exchanges, so one barrier
 // per exchange suffices: a lane that passes the barrier of exchange n+1 knows
 // every lane has finished reading exchange n (program order), and exchange n+2
 // reuses exchange n's buffer.  `par` selects the buffer of the next exchange.
 // Single-wave transforms need no second buffer (their exchanges are
 // wave-private and in order), so they keep using the first.
-template <int N, int E, int KW, int KR>
+template <class GE, int E, int KW, int KR>
 __device__ __forceinline__ void exchange(float2 (&x)[16], float2* lds, int& par, int grp, int g) {
-  float2* buf = lds + ((Geo<N>::G > 64 && par) ? Geo<N>::LDS : 0);
+  constexpr int N = GE::N;
+  float2* buf = lds + ((GE::G > 64 && par) ? GE::LDS : 0);
   par ^= 1;
   lds_store<N, E, KW>(buf, x, grp, g);
   exchange_sync<N>();
@@ -69,61 +70,62 @@ __device__ __forceinline__ void exchange(float2 (&x)[16], float2* lds, int& par,
 // the host emulator checks this for every N), so its first barrier is
 // replaced by a wave-scope fence; the second still guards the next exchange,
 // whose writes cross waves.
-template <int N, int NF, int E, int KW, int KR>
+template <class GE, int NF, int E, int KW, int KR>
 __device__ __forceinline__ void exchange_nf(float2 (&x)[NF][16], float2* lds, int& par, int grp, int g) {
+  constexpr int N = GE::N;
   if constexpr (NF == 1) {
-    exchange<N, E, KW, KR>(x[0], lds, par, grp, g);
+    exchange<GE, E, KW, KR>(x[0], lds, par, grp, g);
   } else {
 #pragma unroll
-    for (int f = 0; f < NF; ++f) lds_store<N, E, KW>(lds + f * Geo<N>::LDS, x[f], grp, g);
-    if constexpr (E == Geo<N>::P - 2) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    for (int f = 0; f < NF; ++f) lds_store<N, E, KW>(lds + f * GE::LDS, x[f], grp, g);
+    if constexpr (E == GE::P - 2) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     else exchange_sync<N>();
 #pragma unroll
-    for (int f = 0; f < NF; ++f) lds_load<N, E, KR>(lds + f * Geo<N>::LDS, x[f], grp, g);
+    for (int f = 0; f < NF; ++f) lds_load<N, E, KR>(lds + f * GE::LDS, x[f], grp, g);
     exchange_sync<N>();
   }
 }
 
-template <int N, int K>
+template <class GE, int K>
 __device__ __forceinline__ void fwd_from(float2 (&x)[16], float2* lds, int& par, const float2* tw, int grp, int g) {
-  run_pass<N, K, false>(x, tw + Geo<N>::lane_tw_offset(K));
-  if constexpr (K + 1 < Geo<N>::P) {
-    exchange<N, K, K, K + 1>(x, lds, par, grp, g);
-    fwd_from<N, K + 1>(x, lds, par, tw, grp, g);
+  run_pass<GE::N, K, false>(x, tw + GE::lane_tw_offset(K));
+  if constexpr (K + 1 < GE::P) {
+    exchange<GE, K, K, K + 1>(x, lds, par, grp, g);
+    fwd_from<GE, K + 1>(x, lds, par, tw, grp, g);
   }
 }
 
-template <int N, int K>
+template <class GE, int K>
 __device__ __forceinline__ void inv_from(float2 (&x)[16], float2* lds, int& par, const float2* tw, int grp, int g) {
-  inverse_pass<N, K>(x, tw + Geo<N>::lane_tw_offset(K));
+  inverse_pass<GE::N, K>(x, tw + GE::lane_tw_offset(K));
   if constexpr (K > 0) {
-    exchange<N, K - 1, K, K - 1>(x, lds, par, grp, g);
-    inv_from<N, K - 1>(x, lds, par, tw, grp, g);
+    exchange<GE, K - 1, K, K - 1>(x, lds, par, grp, g);
+    inv_from<GE, K - 1>(x, lds, par, tw, grp, g);
   }
 }
 
-template <int N, int NF, int K>
+template <class GE, int NF, int K>
 __device__ __forceinline__ void inv_from_nf(float2 (&x)[NF][16], float2* lds, int& par, const float2* tw, int grp,
                                             int g) {
 #pragma unroll
-  for (int f = 0; f < NF; ++f) inverse_pass<N, K>(x[f], tw + Geo<N>::lane_tw_offset(K));
+  for (int f = 0; f < NF; ++f) inverse_pass<GE::N, K>(x[f], tw + GE::lane_tw_offset(K));
   if constexpr (K > 0) {
-    exchange_nf<N, NF, K - 1, K, K - 1>(x, lds, par, grp, g);
-    inv_from_nf<N, NF, K - 1>(x, lds, par, tw, grp, g);
+    exchange_nf<GE, NF, K - 1, K, K - 1>(x, lds, par, grp, g);
+    inv_from_nf<GE, NF, K - 1>(x, lds, par, tw, grp, g);
   }
 }
 
 // x[f] holds a filter spectrum on entry and the inverse FFT of A * spectrum
 // (natural order) on exit, for NF filters at once; the product is fused into
 // the first inverse pass.
-template <int N, int NF>
+template <class GE, int NF>
 __device__ __forceinline__ void inverse_of_products(float2 (&x)[NF][16], const float2 (&A)[16], float2* lds,
                                                     int& par, const float2* tw, int grp, int g) {
-  constexpr int P = Geo<N>::P;
+  constexpr int P = GE::P;
 #pragma unroll
-  for (int f = 0; f < NF; ++f) product_pass<N>(x[f], A);
-  exchange_nf<N, NF, P - 2, P - 1, P - 2>(x, lds, par, grp, g);
-  inv_from_nf<N, NF, P - 2>(x, lds, par, tw, grp, g);
+  for (int f = 0; f < NF; ++f) product_pass<GE::N>(x[f], A);
+  exchange_nf<GE, NF, P - 2, P - 1, P - 2>(x, lds, par, grp, g);
+  inv_from_nf<GE, NF, P - 2>(x, lds, par, tw, grp, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -158,7 +160,7 @@ __device__ __forceinline__ void filter_spectra_block(const void* __restrict__ h,
   if (real) load_filter_real<N>(x, (const float*)h + row, M, valid, diff != 0, g, delay);
   else if (diff) load_filter_diff<N>(x, (const float2*)h + row, M, valid, g, delay);
   else load_filter<N>(x, (const float2*)h + row, M, valid, g, delay);
-  fwd_from<N, 0>(x, lds, par, tw, grp, g);
+  fwd_from<GE, 0>(x, lds, par, tw, grp, g);
   if (valid) store_spectrum<N>(x, F, r, g, 1.0f / (float)N);
 }
 
@@ -246,11 +248,11 @@ constexpr bool prefetch_spectra_single() { return NF == 1 && (N != 1024 || (!POW
 // and its LDS: the buffers, plus, for the non-local stage with transforms no
 // wider than a wave, one wave-private set of stage slots per transform (wider
 // transforms stage in an exchange buffer, under the exchanges' barriers).
-template <int N, int NF>
-constexpr int forward_bufs() { return (NF == 1 && Geo<N>::G > 64) ? 2 : NF; }
-template <int N, int NF, bool STAGE>
+template <class GE, int NF>
+constexpr int forward_bufs() { return (NF == 1 && GE::G > 64) ? 2 : NF; }
+template <class GE, int NF, bool STAGE>
 constexpr int forward_lds() {
-  return forward_bufs<N, NF>() * Geo<N>::LDS + ((STAGE && Geo<N>::G <= 64) ? Geo<N>::SEGS * stage_stride<N>() : 0);
+  return forward_bufs<GE, NF>() * GE::LDS + ((STAGE && GE::G <= 64) ? GE::SEGS * stage_stride<GE::N>() : 0);
 }
 
 // STAGE: the outputs go through the non-local stencil stage (st) instead of
@@ -262,13 +264,13 @@ constexpr int forward_lds() {
 // (delay_rows = K), a batched item has its rows' delayed spectra computed in
 // place (delay_rows = 0).
 template <int N, int NF, bool POWER = false, bool REAL = false, int SMODE = STORE_NT_WHOLE,
-          bool PF = prefetch_spectra<N, NF>(), bool STAGE = false>
+          bool PF = prefetch_spectra<N, NF>(), bool STAGE = false, int WG = 0>
 __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64_t Ns, const float2* __restrict__ F,
                                               void* __restrict__ yv, int K, int D, int H,
                                               const float2 (&tw)[Geo<N>::TWR], int64_t u0, int64_t u1, float2* lds,
                                               int& par, const Stencil* st = nullptr, int shift_mask = 0,
                                               int delay_rows = 0) {
-  using GE = Geo<N>;
+  using GE = Geo<N, WG>;
   const int tid = threadIdx.x;
   const int grp = tid / GE::G, g = tid - grp * GE::G;
   const int KG = (K + NF - 1) / NF;  // filter groups
@@ -294,7 +296,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
   auto transform_segment = [&](float2 (&x)[16], int64_t sg) {
     if constexpr (REAL) load_segment_pair<N>(x, s_r, Ns, sg * step - D, H, g);
     else load_segment<N>(x, s_c, Ns, sg * step - D, g);
-    fwd_from<N, 0>(x, lds, par, tw, grp, g);
+    fwd_from<GE, 0>(x, lds, par, tw, grp, g);
 #pragma unroll
     for (int i = 0; i < 16; ++i) A[i] = x[i];
   };
@@ -320,7 +322,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
     if constexpr (GE::G <= 64) {
       // a transform lies in one wave, whose LDS operations complete in order:
       // its own stage slots need fences against compiler reordering only
-      float2* region = lds + forward_bufs<N, NF>() * GE::LDS + grp * stage_stride<N>();
+      float2* region = lds + forward_bufs<GE, NF>() * GE::LDS + grp * stage_stride<N>();
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         stage_write<N>(region, x[f], g);
@@ -384,7 +386,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
         seg = segment_of(w.tile);
         transform_segment(nxt[0], seg);
       }
-      inverse_of_products<N, NF>(cur, A, lds, par, tw, grp, g);
+      inverse_of_products<GE, NF>(cur, A, lds, par, tw, grp, g);
       if (u + 1 < u1) load_group(nxt, w.next_group(KG));
       __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of the stores
       store_group(cur, w.rg, seg);
@@ -405,14 +407,14 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
         transform_segment(xa[0], seg);
       }
       load_group(xa, w.rg);
-      inverse_of_products<N, NF>(xa, A, lds, par, tw, grp, g);
+      inverse_of_products<GE, NF>(xa, A, lds, par, tw, grp, g);
       store_group(xa, w.rg, seg);
       w.leave();
     }
   }
 }
 
-template <int N, int NF, bool POWER = false, bool REAL = false, int SMODE = STORE_NT_WHOLE, bool STAGE = false>
+template <int N, int NF, bool POWER, bool REAL, int SMODE, bool STAGE, int WG>
 __device__ __forceinline__ void forward_range(const void* __restrict__ sv, int64_t Ns, const float2* __restrict__ F,
                                               void* __restrict__ yv, int K, int D, int H,
                                               const float2* __restrict__ twt, int64_t u0, int64_t u1, float2* lds,
@@ -420,42 +422,39 @@ __device__ __forceinline__ void forward_range(const void* __restrict__ sv, int64
   float2 tw[Geo<N>::TWR];
   load_lane_twiddles<N>(tw, twt, threadIdx.x % Geo<N>::G);
   // the stage's accumulators take the registers of the spectrum prefetch
-  forward_units<N, NF, POWER, REAL, SMODE, prefetch_spectra_single<N, NF, POWER, REAL>() && !STAGE, STAGE>(
+  forward_units<N, NF, POWER, REAL, SMODE, prefetch_spectra_single<N, NF, POWER, REAL>() && !STAGE, STAGE, WG>(
       sv, Ns, F, yv, K, D, H, tw, u0, u1, lds, par, st, shift_mask, K);
 }
 
 // shift_mask: 0, or the row shift of output rows off the 128-byte line grid
 // (row_shift_geometry; F then holds the delayed filters).
-template <int N, int NF, bool POWER, bool REAL>
-__global__ __launch_bounds__(Geo<N>::WG) void ols_forward_kernel(const void* __restrict__ s, int64_t Ns,
-                                                                 const float2* __restrict__ F, void* __restrict__ y,
-                                                                 int K, int D, int H, int64_t ntiles,
-                                                                 const float2* __restrict__ twt, int shift_mask) {
-  __shared__ float2 lds[forward_lds<N, NF, false>()];
+template <int N, int NF, bool POWER, bool REAL, int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_kernel(
+    const void* __restrict__ s, int64_t Ns, const float2* __restrict__ F, void* __restrict__ y, int K, int D, int H,
+    int64_t ntiles, const float2* __restrict__ twt, int shift_mask) {
+  __shared__ float2 lds[forward_lds<Geo<N, WG>, NF, false>()];
   const int64_t U = ntiles * ((K + NF - 1) / NF);
   const int64_t u0 = first_unit(U, gridDim.x, blockIdx.x);
   const int64_t u1 = first_unit(U, gridDim.x, blockIdx.x + 1);
   if (u0 >= u1) return;  // uniform over the workgroup
   int par = 0;
-  forward_range<N, NF, POWER, REAL>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par, nullptr, shift_mask);
+  forward_range<N, NF, POWER, REAL, STORE_NT_WHOLE, false, WG>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par, nullptr,
+                                                               shift_mask);
 }
 
 // The forward kernel with the non-local post-processing stage (sec. 4): the
 // same units, each filter's output staged in LDS and stored as st's phases.
-template <int N, int NF, bool POWER, bool REAL>
-__global__ __launch_bounds__(Geo<N>::WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_stencil_kernel(const void* __restrict__ s, int64_t Ns,
-                                                                         const float2* __restrict__ F,
-                                                                         void* __restrict__ y, int K, int D, int H,
-                                                                         int64_t ntiles,
-                                                                         const float2* __restrict__ twt,
-                                                                         const Stencil st) {
-  __shared__ float2 lds[forward_lds<N, NF, true>()];
+template <int N, int NF, bool POWER, bool REAL, int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_stencil_kernel(
+    const void* __restrict__ s, int64_t Ns, const float2* __restrict__ F, void* __restrict__ y, int K, int D, int H,
+    int64_t ntiles, const float2* __restrict__ twt, const Stencil st) {
+  __shared__ float2 lds[forward_lds<Geo<N, WG>, NF, true>()];
   const int64_t U = ntiles * ((K + NF - 1) / NF);
   const int64_t u0 = first_unit(U, gridDim.x, blockIdx.x);
   const int64_t u1 = first_unit(U, gridDim.x, blockIdx.x + 1);
   if (u0 >= u1) return;  // uniform over the workgroup
   int par = 0;
-  forward_range<N, NF, POWER, REAL, STORE_NT_WHOLE, true>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par, &st);
+  forward_range<N, NF, POWER, REAL, STORE_NT_WHOLE, true, WG>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par, &st);
 }
 
 // ---------------------------------------------------------------------------
@@ -923,7 +922,7 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_backward_kernel(
     seg = segment_of(tile);
     if (want_dh) {
       load_window<N>(x, s, Ns, seg * H, H, g);
-      fwd_from<N, 0>(x, lds, par, tw, grp, g);
+      fwd_from<GE, 0>(x, lds, par, tw, grp, g);
       conj_scaled(A, x, 1.0f / (float)N);
     }
 #pragma unroll
@@ -933,7 +932,7 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_backward_kernel(
     if (!want_ds) return;
 #pragma unroll
     for (int i = 0; i < 16; ++i) x[i] = acc[i];
-    inv_from<N, GE::P - 1>(x, lds, par, tw, grp, g);
+    inv_from<GE, GE::P - 1>(x, lds, par, tw, grp, g);
     const bool complete = tile * K >= u0 && (tile + 1) * K <= u1;
     if (complete) {
       store_valid<N>(x, ds, Ns, seg * H, 0, H, g);
@@ -953,15 +952,15 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_backward_kernel(
       start_tile();
     }
     load_window<N>(x, gy + (int64_t)r * Ns, Ns, seg * H, N, g);
-    fwd_from<N, 0>(x, lds, par, tw, grp, g);
+    fwd_from<GE, 0>(x, lds, par, tw, grp, g);
     if (want_ds) {
       load_spectrum<N>(f, F, r, g);
       acc_conj_product(acc, x, f);
     }
     if (want_dh) {
       product_pass<N>(x, A);
-      exchange<N, GE::P - 2, GE::P - 1, GE::P - 2>(x, lds, par, grp, g);
-      inv_from<N, GE::P - 2>(x, lds, par, tw, grp, g);
+      exchange<GE, GE::P - 2, GE::P - 1, GE::P - 2>(x, lds, par, grp, g);
+      inv_from<GE, GE::P - 2>(x, lds, par, tw, grp, g);
       add_lags<N>(part + (int64_t)r * M, x, M, g);
     }
     ++r;
@@ -1313,10 +1312,12 @@ struct ols_plan_s {
   int K = 0, M = 0, N = 0, D = 0, H = 0;
   int device = 0;
   int cus = 0;
-  int grid = 0;   // persistent workgroups of the forward kernel
+  int grid = 0;   // persistent workgroups of the forward kernel, in workgroups of `block` threads
+  int full = 0;   // the same at full occupancy
   int block = 0;  // threads per workgroup
   int segs = 0;   // segments per tile
   int nf = 1;     // filters per work unit of the forward kernel
+  bool nf_auto = true;  // nf is the library's choice: calls may take fewer (Kern::call_shape)
   int flags = 0;  // OLS_POST_* and OLS_REAL
   bool stencil_on = false;  // non-local stage (ols_plan_set_stencil)
   int stencil_R = 0;        // its reach ahead (taps after the sample)
@@ -1384,34 +1385,57 @@ struct Kern {
     hipLaunchKernelGGL(ols_spectra_natural_kernel<N>, dim3((unsigned)blocks), dim3(threads), 0, st, F, K, out);
     return hipGetLastError();
   }
-  // Forward kernel instance for (filters per unit, power epilogue, R2R).
-  using ForwardFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*, int);
-  template <int NF>
-  static ForwardFn forward_fn_nf(bool power, bool real) {
-    if (real) {
-      // R2R takes two filters per unit only up to N = 2048 (choose_nf_real)
-      constexpr int NFR = N <= BATCH_NF2_MAX_N ? NF : 1;
-      return power ? ols_forward_kernel<N, NFR, true, true> : ols_forward_kernel<N, NFR, false, true>;
-    }
-    return power ? ols_forward_kernel<N, NF, true, false> : ols_forward_kernel<N, NF, false, false>;
+  // Threads per workgroup of the forward kernels: one transform, or one wave
+  // of narrower ones, is the smallest (NARROW).  A unit then holds one segment,
+  // so short calls spread over more CUs, long ones end more evenly, and a
+  // barrier joins only the waves of one transform.  Measured against 256
+  // threads (us, complex, one GPU): N = 1024, 2^20 x 1 8.0 -> 7.0, 2^13 x 4
+  // 6.2 -> 4.9, 2^22 x 64 438 -> 427; N = 2048, 2^18 x 7 11.4 -> 10.4,
+  // 2^21 x 7 33.9 -> 31.1, 2^23 x 32 (one filter per unit) 447 -> 433.  Long
+  // calls keep 256 threads where the spectra are loaded without prefetch or
+  // fit in L1, because the segments of such a workgroup read each spectrum
+  // through one L1 at the same time: two filters per unit at N = 2048 (2^23 x
+  // 32: 441 against 452 with 128), R2R at N = 1024 (2^23 x 16: 114.5 against
+  // 120.7), and N <= 512 (2^22 x 8, N = 512: 57.1 against 61.4).
+  static constexpr int NARROW = GE::G <= 64 ? 64 : GE::G;
+  static constexpr int wide(int nf, bool real) {
+    return (N <= 512 || (N == 1024 && real) || (N == 2048 && nf == 2)) ? GE::WG : NARROW;
   }
-  static ForwardFn forward_fn(int nf, int flags) {
+  // Forward kernel instance for (filters per unit, power epilogue, R2R, workgroup).
+  using ForwardFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*, int);
+  template <int NF, bool REAL, int WG>
+  static ForwardFn forward_fn_wg(bool power) {
+    return power ? ols_forward_kernel<N, NF, true, REAL, WG> : ols_forward_kernel<N, NF, false, REAL, WG>;
+  }
+  template <int NF, bool REAL>
+  static ForwardFn forward_fn_nf(int wg, bool power) {
+    return wg == NARROW ? forward_fn_wg<NF, REAL, NARROW>(power) : forward_fn_wg<NF, REAL, wide(NF, REAL)>(power);
+  }
+  static ForwardFn forward_fn(int nf, int flags, int wg) {
     const bool power = (flags & OLS_POST_POWER) != 0, real = (flags & OLS_REAL) != 0;
     if constexpr (HAS_NF2) {
-      if (nf == 2) return forward_fn_nf<2>(power, real);
+      if (nf == 2 && !real) return forward_fn_nf<2, false>(wg, power);
+      // R2R takes two filters per unit only up to N = 2048 (choose_nf_real)
+      if constexpr (N <= BATCH_NF2_MAX_N) {
+        if (nf == 2) return forward_fn_nf<2, true>(wg, power);
+      }
     }
-    return forward_fn_nf<1>(power, real);
+    return real ? forward_fn_nf<1, true>(wg, power) : forward_fn_nf<1, false>(wg, power);
   }
-  // The same for the kernel with the non-local stencil stage.
+  // The same for the kernel with the non-local stencil stage, in workgroups of
+  // GE::WG threads (single waves measured 3-5 % slower on long calls at N =
+  // 256 and 1024).
   using StencilFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*,
                              const Stencil);
   template <int NF>
   static StencilFn stencil_fn_nf(bool power, bool real) {
     if (real) {
       constexpr int NFR = N <= BATCH_NF2_MAX_N ? NF : 1;
-      return power ? ols_forward_stencil_kernel<N, NFR, true, true> : ols_forward_stencil_kernel<N, NFR, false, true>;
+      return power ? ols_forward_stencil_kernel<N, NFR, true, true, GE::WG>
+                   : ols_forward_stencil_kernel<N, NFR, false, true, GE::WG>;
     }
-    return power ? ols_forward_stencil_kernel<N, NF, true, false> : ols_forward_stencil_kernel<N, NF, false, false>;
+    return power ? ols_forward_stencil_kernel<N, NF, true, false, GE::WG>
+                 : ols_forward_stencil_kernel<N, NF, false, false, GE::WG>;
   }
   static StencilFn stencil_fn(int nf, int flags) {
     const bool power = (flags & OLS_POST_POWER) != 0, real = (flags & OLS_REAL) != 0;
@@ -1419,6 +1443,47 @@ struct Kern {
       if (nf == 2) return stencil_fn_nf<2>(power, real);
     }
     return stencil_fn_nf<1>(power, real);
+  }
+  // How one call runs: filters per unit and threads per workgroup.  A choice of
+  // the call's size and the plan's occupancy, not of the grid set by
+  // ols_plan_set_tiling.
+  struct Shape {
+    int nf, wg;
+  };
+  // Workgroups of wg threads that stand for `groups` of GE::WG threads.
+  static int64_t slots(int groups, int wg) { return (int64_t)groups * (GE::WG / wg); }
+  static int64_t units(const ols_plan_s* p, int64_t ntrans, Shape c) {
+    const int segs = c.wg / GE::G;
+    return (ntrans + segs - 1) / segs * ((p->K + c.nf - 1) / c.nf);
+  }
+  static Shape call_shape(const ols_plan_s* p, int64_t ntrans) {
+    if (p->stencil_on) return Shape{p->nf, GE::WG};
+    Shape c{p->nf, NARROW};
+    if constexpr (N == 2048 || N == 4096) {
+      // Plans that leave the tiling to the library: one filter per unit, with
+      // prefetched spectra and twice the units (us, two -> one filter,
+      // workgroups of one transform: N = 2048, 2^18 x 32 24.6 -> 20.5, 2^20
+      // x 32 65.2 -> 58.7; N = 4096, 2^15 x 16 9.1 -> 7.3, 2^18 x 16 19.3 ->
+      // 16.9), except where two filters give every workgroup one unit and one
+      // filter does not (2^16 x 32, N = 2048: 10.0 against 12.6), and from
+      // N4096_NF2_UNITS units per workgroup at N = 4096, where the pair's
+      // shared barriers count (2^23 x 32: 446 against 457).
+      if (p->nf_auto && c.nf == 2) {
+        constexpr int N4096_NF2_UNITS = 8;
+        const int64_t S = slots(p->full, NARROW), u1 = units(p, ntrans, Shape{1, NARROW});
+        const bool pairs = (u1 > S && units(p, ntrans, c) <= S) || (N == 4096 && u1 >= N4096_NF2_UNITS * S);
+        if (!pairs) c.nf = 1;
+      }
+    }
+    // 256-thread workgroups, where they pay, from WIDE_UNITS units each on
+    // (N = 512, 2^20 x 8: 4.3 units, 20.7 against 20.1 us with 64 threads;
+    // R2R N = 1024, 2^19 x 8: 2.1 units, 12.3 against 11.9, 2^21 x 8: 4.1 units,
+    // 20.6 against 21.5; N = 2048, two filters, 2^18 x 32: 2.3 units, 26.0 against
+    // 24.6, 2^19 x 32: 4.6 units, 36.9 against 37.5)
+    constexpr int WIDE_UNITS = N <= 512 ? 8 : 4;
+    const Shape w{c.nf, wide(c.nf, (p->flags & OLS_REAL) != 0)};
+    if (w.wg != NARROW && units(p, ntrans, w) >= WIDE_UNITS * slots(p->full, w.wg)) c = w;
+    return c;
   }
   static hipError_t forward(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
     // output rows off the 128-byte grid read the plan's spectra for each
@@ -1431,24 +1496,30 @@ struct Kern {
     const int H = rs.H;
     const int64_t nseg = (Ns + H - 1) / H;
     const int64_t ntrans = (p->flags & OLS_REAL) ? (nseg + 1) / 2 : nseg;  // R2R: segment pairs
-    const int64_t ntiles = (ntrans + GE::SEGS - 1) / GE::SEGS;
-    const int64_t units = ntiles * ((p->K + p->nf - 1) / p->nf);
-    const int64_t grid = units < p->grid ? units : p->grid;
+    const Shape c = call_shape(p, ntrans);
+    const int segs = c.wg / GE::G;
+    const int64_t ntiles = (ntrans + segs - 1) / segs;
+    const int64_t u = units(p, ntrans, c), most = slots(p->grid, c.wg), grid = u < most ? u : most;
     if (p->stencil_on) {
       // J <= 2 phases go out as one element per sample when y is aligned to it
       Stencil sten = p->stencil;
       const uintptr_t el = (uintptr_t)sten.J * (float_out ? 4 : 8);
       sten.packed = sten.J <= 2 && (uintptr_t)y % el == 0;
-      hipLaunchKernelGGL(stencil_fn(p->nf, p->flags), dim3((unsigned)grid), dim3(GE::WG), 0, st, s, Ns, p->spectra, y,
+      hipLaunchKernelGGL(stencil_fn(c.nf, p->flags), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, p->spectra, y,
                          p->K, p->D, p->H, ntiles, p->twiddles, sten);
     } else
-      hipLaunchKernelGGL(forward_fn(p->nf, p->flags), dim3((unsigned)grid), dim3(GE::WG), 0, st, s, Ns, F, y, p->K,
-                         p->D, H, ntiles, p->twiddles, rs.mask);
+      hipLaunchKernelGGL(forward_fn(c.nf, p->flags, c.wg), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, F, y,
+                         p->K, p->D, H, ntiles, p->twiddles, rs.mask);
     return hipGetLastError();
   }
+  // Workgroups of GE::WG threads per CU (or as many threads in smaller ones).
   static hipError_t occupancy(int nf, int flags, bool stage, int* blocks_per_cu) {
-    if (stage) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, stencil_fn(nf, flags), GE::WG, 0);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, forward_fn(nf, flags), GE::WG, 0);
+    int n = 0;
+    const int wg = stage ? GE::WG : wide(nf, (flags & OLS_REAL) != 0);
+    const hipError_t e = stage ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_fn(nf, flags), wg, 0)
+                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, forward_fn(nf, flags, wg), wg, 0);
+    *blocks_per_cu = n / (GE::WG / wg);
+    return e;
   }
   // The adjoint: paired segments up to N = 2048 (ols_backward_pair_kernel),
   // one segment per group above.
@@ -1802,7 +1873,7 @@ ols_status_t ols_plan_ex(ols_plan_t* plan, const void* h, int32_t K, int32_t M, 
     e = dispatch<RunOccupancy>(N, p->nf, flags, false, &per_cu);
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "occupancy query"); }
     if (per_cu < 1) per_cu = 1;
-    p->grid = per_cu * p->cus;
+    p->grid = p->full = per_cu * p->cus;
     p->block = dispatch<RunShape>(N, 0);
     p->segs = dispatch<RunShape>(N, 1);
 
@@ -1902,12 +1973,13 @@ ols_status_t ols_plan_set_stencil(ols_plan_t p, int32_t J, int32_t L, int32_t R,
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
     if (per_cu < 1) per_cu = 1;
     p->nf = nf;
+    p->nf_auto = true;
     p->stencil_on = J != 0;
     p->stencil = st;
     p->stencil_R = J != 0 ? R : 0;
     p->D = stencil_delay(p->N, Meff, p->stencil_on ? L : 0, p->stencil_R);
     p->H = stencil_hop(p->N, p->D, p->stencil_R);
-    p->grid = per_cu * p->cus;
+    p->grid = p->full = per_cu * p->cus;
     return OLS_SUCCESS;
   } catch (...) {
     return fail(OLS_ERROR_INTERNAL, "exception in ols_plan_set_stencil");
@@ -1947,7 +2019,8 @@ static bool nf_allowed(const ols_plan_s* p, int nf) {
 ols_status_t ols_plan_set_tiling(ols_plan_t p, int32_t nf, int32_t wpc) {
   try {
     if (!p) return fail(OLS_ERROR_INVALID_VALUE, "plan is NULL");
-    if (nf == 0) nf = (p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K);
+    const bool nf_auto = nf == 0;
+    if (nf_auto) nf = (p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K);
     if (!nf_allowed(p, nf)) return fail(OLS_ERROR_INVALID_VALUE, "filters_per_unit must be 1 or 2 (2 only for N <= 4096, R2R N <= 2048)");
     int per_cu = 0;
     hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, p->stencil_on, &per_cu);
@@ -1956,7 +2029,9 @@ ols_status_t ols_plan_set_tiling(ols_plan_t p, int32_t nf, int32_t wpc) {
     if (wpc == 0) wpc = per_cu;
     if (wpc < 1 || wpc > per_cu) return fail(OLS_ERROR_INVALID_VALUE, "workgroups_per_cu must be in [1, occupancy]");
     p->nf = nf;
+    p->nf_auto = nf_auto;
     p->grid = wpc * p->cus;
+    p->full = per_cu * p->cus;
     return OLS_SUCCESS;
   } catch (...) {
     return fail(OLS_ERROR_INTERNAL, "exception in ols_plan_set_tiling");

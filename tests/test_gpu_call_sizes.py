@@ -1,0 +1,66 @@
+"""Forward calls on both sides of every size rule of the launch (filters per
+unit, threads per workgroup), against the float64 oracle.
+
+Sampled outputs (around segment boundaries, the start, the tail) meet the
+relative L2 bound 1e-5 per row; the NaN prefill shows that every output is
+written, the guards that nothing else is.
+"""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import workloads  # noqa: E402
+from oracle import conv  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+GUARD = 4096
+
+# (N, K, M, N_s, flags): per length, calls of fewer units than workgroups, of
+# more units with one filter each but not with two, of a few units per
+# workgroup, and past the bound from which wide workgroups or filter pairs run
+CASES = [
+    (256, 3, 20, 5000, ""), (256, 8, 20, 1100003, ""),
+    (512, 8, 32, 40001, ""), (512, 8, 32, 2200000, ""), (512, 9, 32, 300001, "power"),
+    (1024, 5, 64, 962, ""), (1024, 16, 64, 300000, ""), (1024, 8, 30, 300001, "real"), (1024, 8, 30, 2300001, "real"),
+    (2048, 32, 256, 50000, ""), (2048, 32, 256, 65536, ""), (2048, 32, 256, 131073, ""), (2048, 9, 300, 600001, ""),
+    (2048, 24, 256, 65536, "real"), (2048, 24, 256, 262147, "real"), (2048, 10, 100, 100003, "power"),
+    (2048, 5, 100, 400003, "real power"),
+    (4096, 16, 512, 60000, ""), (4096, 16, 512, 131072, ""), (4096, 16, 512, 300001, ""), (4096, 16, 512, 950003, ""),
+]
+
+
+@pytest.mark.parametrize("N,K,M,Ns,flags", CASES)
+def test_call_size(N, K, M, Ns, flags):
+    from paper_1910_01972_amd import ols
+    print(f"call size N={N} K={K} M={M} Ns={Ns} {flags}", flush=True)
+    real, power = "real" in flags, "power" in flags
+    make = workloads.make_real_signal_filters if real else workloads.make_signal_filters
+    s, h = make(Ns, K, M, seed=N + K)
+    plan = ols.OLSPlan(torch.from_numpy(h).cuda(), N=N, power=power)
+    dt = torch.float32 if real or power else torch.complex64
+    buf = torch.full((K * Ns + 2 * GUARD,), float("nan"), dtype=dt, device="cuda")
+    y = buf[GUARD:GUARD + K * Ns].view(K, Ns)
+    plan.forward(torch.from_numpy(s).cuda(), y)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(buf[:GUARD]).all()) and bool(torch.isnan(buf[GUARD + K * Ns:]).all())
+    assert not bool(torch.isnan(y).any())
+    H = plan.info()["H"]
+    edges = np.concatenate([np.arange(0, Ns, max(H, Ns // 150 // H * H)), [Ns - 1]])
+    idx = np.unique(np.clip((edges[:, None] + np.arange(-2, 3)).ravel(), 0, Ns - 1))
+    want = (conv.direct_conv_real_at if real else conv.direct_conv_at)(s, h, idx)
+    if power:
+        want = np.abs(want) ** 2
+    got = y[:, torch.from_numpy(idx).cuda()].cpu().numpy()
+    assert np.all(np.linalg.norm(got - want, axis=1) <= TOL * np.linalg.norm(want, axis=1))
+    # the filters-per-unit choice changes rounding only
+    for nf in (1, 2):
+        if nf == 2 and (N > 4096 or (real and N > 2048)):
+            continue
+        plan.set_tiling(nf, 0)
+        z = plan.forward(torch.from_numpy(s).cuda())
+        assert bool((torch.linalg.vector_norm(z - y, dim=1) <= 1e-6 * torch.linalg.vector_norm(y, dim=1)).all())
+    plan.close()
