@@ -389,6 +389,7 @@ struct EmuItem {
   int64_t Ns, unit_begin, units, tile_begin = 0, ntiles = 0;
   int K, M, N, D, H, nf;
   int shift_mask = 0;
+  int parts = 1;
 };
 
 template <int N>
@@ -673,11 +674,14 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
   std::stable_sort(items.begin(), items.end(), [](const EmuItem& u, const EmuItem& v) {
     return u.N != v.N ? u.N < v.N : u.nf < v.nf;
   });
+  int64_t all_tiles = 0;
+  for (const EmuItem& it : items) all_tiles += it.ntiles;
   for (EmuItem& it : items) {
     it.unit_begin = units;
     units += it.units;
+    it.parts = ols::batch_tile_parts(all_tiles, grid, (it.K + it.nf - 1) / it.nf);
     it.tile_begin = tiles;
-    tiles += it.ntiles;
+    tiles += it.ntiles * it.parts;
   }
   // the device schedule (first_batch_tile, next_batch_tile,
   // batch_workgroup_order): chunks of tiles dealt round-robin to the grid,
@@ -693,10 +697,9 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
       ++runs;
       for (;;) {
         EmuItem& it = items[i];
-        if (t < it.tile_begin || t >= it.tile_begin + it.ntiles) return 4;  // walk invariant
-        const int64_t per_tile = it.units / it.ntiles;
-        const int64_t a = (t - it.tile_begin) * per_tile;
-        if (dispatch<RangeN>(it.N, &it, a, a + per_tile) != 0) return 3;
+        if (t < it.tile_begin || t >= it.tile_begin + it.ntiles * it.parts) return 4;  // walk invariant
+        const ols::BatchEntry e = ols::batch_entry(t - it.tile_begin, (it.K + it.nf - 1) / it.nf, it.parts);
+        if (dispatch<RangeN>(it.N, &it, e.u0, e.u1) != 0) return 3;
         t = ols::next_batch_tile(t, P);
         if (t >= tiles) break;
         while (i + 1 < n && items[i + 1].tile_begin <= t) ++i;

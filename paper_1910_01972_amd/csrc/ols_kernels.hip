@@ -476,10 +476,10 @@ struct BatchItem {
   int64_t unit_begin;
   int64_t units;
   int32_t K, M, N, D, H, nf;
-  int64_t tile_begin;  // first tile of this item in the batch's tile list
+  int64_t tile_begin;  // first entry of this item in the batch's tile list
   int64_t ntiles;      // tiles of this item (units = ntiles * units per tile)
   int32_t shift_mask;  // rows off the 128-byte grid: filters delayed by row_delay with this mask
-  int32_t pad;
+  int32_t parts;       // entries of the tile list each tile is split into (batch_tile_parts)
 };
 
 // Values the batch setup computes on the device: totals over all items and
@@ -490,7 +490,7 @@ struct BatchHeader {
   int32_t bad_item;     // first failing item (caller's numbering), -1 if none
   int32_t n;
   int32_t pad;
-  int64_t total_tiles;  // segment tiles of all items
+  int64_t total_tiles;  // entries of the tile list: the tiles of all items, times each item's parts
   int64_t total_tasks;  // spectrum tasks (one workgroup's filters of one item)
   int64_t spec_elems;   // complex64 elements of filter spectra the items need
 };
@@ -518,33 +518,56 @@ struct BatchLayout {
 // the twiddle tables of the five batched lengths, evaluated in float64 from
 // the exact reduced angle and rounded once to float32.
 // ---------------------------------------------------------------------------
-constexpr int SETUP_THREADS = 1024;
+constexpr int SETUP_THREADS = 256;
+constexpr int SETUP_WAVES = SETUP_THREADS / 64;
 
-// Exclusive prefix sum over the workgroup of one value per thread; *total
-// receives the sum over all threads.  sh holds SETUP_THREADS values.
-__device__ int64_t block_exclusive_scan(int64_t v, int64_t* sh, int64_t* total) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int off = 1; off < SETUP_THREADS; off <<= 1) {
-    const int64_t a = t >= off ? sh[t - off] : 0;
-    __syncthreads();
-    sh[t] += a;
-    __syncthreads();
+// Exclusive prefix sums over the workgroup of NV values per thread, in place;
+// total receives the sums over all threads, sh holds NV * SETUP_WAVES values.
+// Within a wave by lane shuffles, across waves by one pass over their sums:
+// two barriers for all NV values (a shared-memory scan of one value takes 20,
+// and fourteen of those were half of the setup's time).
+template <int NV, typename T>
+__device__ __forceinline__ void block_exclusive_scan(T (&v)[NV], T* sh, T (&total)[NV]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  T incl[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) incl[k] = v[k];
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const T a = __shfl_up(incl[k], off, 64);
+      if (lane >= off) incl[k] += a;
+    }
   }
-  const int64_t incl = sh[t];
-  *total = sh[SETUP_THREADS - 1];
+  if (lane == 63) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) sh[k * SETUP_WAVES + wave] = incl[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < SETUP_WAVES; ++w) {
+      const T s = sh[k * SETUP_WAVES + w];
+      if (w < wave) before += s;
+      all += s;
+    }
+    v[k] = before + incl[k] - v[k];
+    total[k] = all;
+  }
   __syncthreads();  // sh is reused by the next scan
-  return incl - v;
 }
 
+// Twiddle table of length N, entries first, first + step, ...
 template <int N>
-__device__ void device_twiddles(float2* __restrict__ out) {
+__device__ void device_twiddles(float2* __restrict__ out, int first, int step) {
   using GE = Geo<N>;
 #pragma unroll
   for (int k = 0; k < GE::P - 1; ++k) {
     const int L = GE::len(k), S = GE::strd(k), cnt = GE::tw_count(k);
-    for (int idx = threadIdx.x; idx < cnt; idx += SETUP_THREADS) {
+    for (int idx = first; idx < cnt; idx += step) {
       const int b = idx / S + 1, l = idx - (b - 1) * S;
       const int m = (int)(((int64_t)l * b) % L);
       double sn, cs;
@@ -578,13 +601,26 @@ __device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int 
   return r;
 }
 
+// Workgroup 0 lays out the batch; the others write the twiddle tables at the
+// same time.  A call of few items is bound by this kernel's serial chain: the
+// item loads, three scans and the stores.  grid: workgroups of the forward
+// launch (batch_tile_parts).
+constexpr int SETUP_TWIDDLE_BLOCKS = 32;
 __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ols_batch_item_t* __restrict__ in,
-                                                                         BatchLayout L) {
-  __shared__ int cnt[BATCH_CLASSES][SETUP_THREADS];
-  __shared__ int64_t sh[SETUP_THREADS];
-  __shared__ int64_t cls_total[BATCH_CLASSES];
+                                                                         BatchLayout L, int grid) {
+  __shared__ int sh_cnt[BATCH_CLASSES * SETUP_WAVES];
+  __shared__ int64_t sh[4 * SETUP_WAVES];
   __shared__ unsigned long long s_fail;
   const int t = threadIdx.x, n = L.n;
+  if (blockIdx.x > 0) {
+    const int first = (blockIdx.x - 1) * SETUP_THREADS + t, step = SETUP_TWIDDLE_BLOCKS * SETUP_THREADS;
+    device_twiddles<256>(L.tw[0], first, step);
+    device_twiddles<512>(L.tw[1], first, step);
+    device_twiddles<1024>(L.tw[2], first, step);
+    device_twiddles<2048>(L.tw[3], first, step);
+    device_twiddles<4096>(L.tw[4], first, step);
+    return;
+  }
   const int chunk = (n + SETUP_THREADS - 1) / SETUP_THREADS;
   const int i0 = t * chunk < n ? t * chunk : n;
   const int i1 = i0 + chunk < n ? i0 + chunk : n;
@@ -592,9 +628,10 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
   __syncthreads();
 
   // 1. check every item, count the items of each class in this thread's chunk
-  int local[BATCH_CLASSES];
+  int base[BATCH_CLASSES];
 #pragma unroll
-  for (int c = 0; c < BATCH_CLASSES; ++c) local[c] = 0;
+  for (int c = 0; c < BATCH_CLASSES; ++c) base[c] = 0;
+  int64_t tiles[1] = {0};
   for (int i = i0; i < i1; ++i) {
     const ols_batch_item_t it = in[i];
     int N = 0;
@@ -603,7 +640,10 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
       atomicMin(&s_fail, ((unsigned long long)i << 8) | (unsigned)st);
       continue;
     }
-    ++local[batch_class(N, choose_nf_batched(N, it.K))];
+    const ItemShape s = item_shape(it, N);
+#pragma unroll
+    for (int c = 0; c < BATCH_CLASSES; ++c) base[c] += c == s.cls;
+    tiles[0] += s.ntiles;
   }
   __syncthreads();
   if (s_fail != ~0ull) {  // uniform: no item is processed
@@ -620,19 +660,15 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
 
   // 2. stable counting sort by class: exclusive prefix of every class's
   // counts over the threads, then class bases
-#pragma unroll
-  for (int c = 0; c < BATCH_CLASSES; ++c) {
-    int64_t tot;
-    cnt[c][t] = (int)block_exclusive_scan(local[c], sh, &tot);
-    if (t == 0) cls_total[c] = tot;
-  }
-  __syncthreads();
-  int64_t base[BATCH_CLASSES];
+  int64_t all_tiles[1];
+  block_exclusive_scan(tiles, sh, all_tiles);
   {
-    int64_t acc = 0;
+    int cls_total[BATCH_CLASSES];
+    block_exclusive_scan(base, sh_cnt, cls_total);
+    int acc = 0;
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c) {
-      base[c] = acc + cnt[c][t];
+      base[c] += acc;
       acc += cls_total[c];
     }
   }
@@ -641,7 +677,10 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     int N = 0;
     (void)batch_item_check(it.s, it.N_s, it.h, it.K, it.M, it.N, it.y, &N);
     const ItemShape sh_ = item_shape(it, N);
-    const int64_t pos = base[sh_.cls]++;
+    int pos = 0;
+#pragma unroll
+    for (int c = 0; c < BATCH_CLASSES; ++c)
+      if (c == sh_.cls) pos = base[c]++;
     BatchItem b;
     b.s = (const float2*)it.s;
     b.y = (float2*)it.y;
@@ -656,7 +695,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     b.D = sh_.D;
     b.H = sh_.H;
     b.shift_mask = sh_.shift_mask;
-    b.pad = 0;
+    b.parts = batch_tile_parts(all_tiles[0], grid, (it.K + sh_.nf - 1) / sh_.nf);
     b.nf = sh_.nf;
     b.tile_begin = 0;
     b.ntiles = sh_.ntiles;
@@ -665,48 +704,54 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
   }
   __syncthreads();  // the sorted table is complete (workgroup-scope visibility of global writes)
 
-  // 3. prefix sums in kernel order: tiles, units, spectra, spectrum tasks
-  int64_t my_tiles = 0, my_units = 0, my_spec = 0, my_tasks = 0;
+  // 3. prefix sums in kernel order: tile list, units, spectra, spectrum tasks
+  int64_t o[4] = {0, 0, 0, 0}, tot[4];
   for (int p = i0; p < i1; ++p) {
     const BatchItem& b = L.items[p];
-    my_tiles += b.ntiles;
-    my_units += b.units;
-    my_spec += (int64_t)b.K * b.N;
-    my_tasks += (b.K + 4096 / b.N - 1) / (4096 / b.N);
+    o[0] += b.ntiles * b.parts;
+    o[1] += b.units;
+    o[2] += (int64_t)b.K * b.N;
+    o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
   }
-  int64_t tot_tiles, tot_units, tot_spec, tot_tasks;
-  int64_t o_tiles = block_exclusive_scan(my_tiles, sh, &tot_tiles);
-  int64_t o_units = block_exclusive_scan(my_units, sh, &tot_units);
-  int64_t o_spec = block_exclusive_scan(my_spec, sh, &tot_spec);
-  int64_t o_tasks = block_exclusive_scan(my_tasks, sh, &tot_tasks);
-  const bool fits = tot_spec <= L.spec_capacity;
+  block_exclusive_scan(o, sh, tot);
+  const bool fits = tot[2] <= L.spec_capacity;
   for (int p = i0; p < i1; ++p) {
     BatchItem& b = L.items[p];
-    b.tile_begin = o_tiles;
-    b.unit_begin = o_units;
-    b.spectra = fits ? L.spectra + o_spec : nullptr;
-    L.task_begin[p] = o_tasks;
-    o_tiles += b.ntiles;
-    o_units += b.units;
-    o_spec += (int64_t)b.K * b.N;
-    o_tasks += (b.K + 4096 / b.N - 1) / (4096 / b.N);
+    b.tile_begin = o[0];
+    b.unit_begin = o[1];
+    b.spectra = fits ? L.spectra + o[2] : nullptr;
+    L.task_begin[p] = o[3];
+    o[0] += b.ntiles * b.parts;
+    o[1] += b.units;
+    o[2] += (int64_t)b.K * b.N;
+    o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
   }
   if (t == 0) {
-    L.task_begin[n] = tot_tasks;
+    L.task_begin[n] = tot[3];
     L.hdr->status = fits ? 0 : (int32_t)OLS_ERROR_INVALID_VALUE;
     L.hdr->bad_item = -1;
     L.hdr->n = n;
-    L.hdr->total_tiles = tot_tiles;
-    L.hdr->total_tasks = tot_tasks;
-    L.hdr->spec_elems = tot_spec;
+    L.hdr->total_tiles = tot[0];
+    L.hdr->total_tasks = tot[3];
+    L.hdr->spec_elems = tot[2];
   }
+}
 
-  // 4. twiddle tables
-  device_twiddles<256>(L.tw[0]);
-  device_twiddles<512>(L.tw[1]);
-  device_twiddles<1024>(L.tw[2]);
-  device_twiddles<2048>(L.tw[3]);
-  device_twiddles<4096>(L.tw[4]);
+// The item whose range holds entry v of a list: the largest i >= first with
+// begin(i) <= v, begin non-decreasing and begin(first) <= v (so items with
+// empty ranges are passed).  W lanes of a wave take one item each, W items per
+// load: a walk or bisection from one load to the next costs a memory latency
+// per step (24 items: 5 for a bisection, up to 23 for a walk).  Wave-uniform.
+template <int W, class Begin>
+__device__ __forceinline__ int find_item(int first, int n, int64_t v, Begin begin) {
+  const int lane = threadIdx.x & 63;
+  for (int i = first;;) {
+    const int c = i + 1 + (lane < W ? lane : W - 1);
+    const int64_t b = begin(c < n ? c : n - 1);
+    const int k = __popcll(__ballot(lane < W && c < n && b <= v));
+    i += k;
+    if (k < W) return i;
+  }
 }
 
 // One length's spectrum body as its own function, so the kernel's register
@@ -725,13 +770,7 @@ __global__ __launch_bounds__(256) void ols_batch_spectra_kernel(BatchLayout L) {
   if (L.hdr->status != 0) return;
   const int64_t tasks = L.hdr->total_tasks;
   for (int64_t tau = blockIdx.x; tau < tasks; tau += gridDim.x) {
-    // the item whose task range holds tau: task_begin[i] <= tau < task_begin[i + 1]
-    int lo = 0, hi = L.n;  // invariant: task_begin[lo] <= tau < task_begin[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (L.task_begin[mid] <= tau) lo = mid;
-      else hi = mid;
-    }
+    const int lo = find_item<64>(0, L.n, tau, [&](int i) { return L.task_begin[i]; });
     const BatchItem& it = L.items[lo];
     const int r0 = (int)(tau - L.task_begin[lo]) * (4096 / it.N);
     __syncthreads();  // the previous task's transform may still read LDS
@@ -787,6 +826,7 @@ __device__ __forceinline__ BatchItem read_item(gptr<const BatchItem> items, int 
   r.nf = __builtin_amdgcn_readfirstlane(items[i].nf);
   r.tile_begin = wave_uniform64(items[i].tile_begin);
   r.ntiles = wave_uniform64(items[i].ntiles);
+  r.parts = __builtin_amdgcn_readfirstlane(items[i].parts);
   r.shift_mask = __builtin_amdgcn_readfirstlane(items[i].shift_mask);
   return r;
 }
@@ -812,14 +852,14 @@ __device__ __attribute__((noinline)) BatchWalk batched_run(const BatchItem* __re
   load_lane_twiddles<N>(tw, to_global(twt), threadIdx.x % Geo<N>::G);
   for (;;) {
     const BatchItem it = read_item(items, i);
-    const int64_t per_tile = it.units / it.ntiles;
-    const int64_t a = (t - it.tile_begin) * per_tile;
-    forward_units<N, NF, false, false, STORE_NT_WHOLE>(it.s, it.Ns, it.spectra, it.y, it.K, it.D, it.H, tw, a,
-                                                       a + per_tile, lds, par, nullptr, it.shift_mask);
+    const int KG = (it.K + NF - 1) / NF;
+    const BatchEntry e = batch_entry(t - it.tile_begin, KG, it.parts);
+    forward_units<N, NF, false, false, STORE_NT_WHOLE>(it.s, it.Ns, it.spectra, it.y, it.K, it.D, it.H, tw, e.u0,
+                                                       e.u1, lds, par, nullptr, it.shift_mask);
     t = next_batch_tile(t, P);
     if (t >= total_tiles) return BatchWalk{t, i, par};
     // t grows, so the item walk only moves forward (items without tiles are skipped)
-    while (i + 1 < nitems && items[i + 1].tile_begin <= t) ++i;
+    i = find_item<4>(i, nitems, t, [&](int k) { return items[k].tile_begin; });
     if (items[i].N != N || items[i].nf != NF) return BatchWalk{t, i, par};
   }
 }
@@ -856,7 +896,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void o
   BatchWalk w{first_batch_tile(batch_workgroup_order(blockIdx.x, P)), 0, 0};
   const gptr<const BatchItem> gitems = to_global(items);
   while (w.t < total_tiles) {
-    while (w.i + 1 < nitems && gitems[w.i + 1].tile_begin <= w.t) ++w.i;
+    w.i = find_item<64>(w.i, nitems, w.t, [&](int k) { return gitems[k].tile_begin; });
     // items of another class lay out the LDS buffers differently, and
     // single-wave transforms exchange without barriers: every wave must have
     // finished with the previous run's buffers
@@ -1705,7 +1745,8 @@ hipError_t launch_batch(const ols_batch_item_t* dev_items, const BatchLayout& L,
   hipError_t e = batch_grids(&grid, &sgrid);
   if (e != hipSuccess) return e;
   if (dev_items) {
-    hipLaunchKernelGGL(ols_batch_setup_kernel, dim3(1), dim3(SETUP_THREADS), 0, st, dev_items, L);
+    hipLaunchKernelGGL(ols_batch_setup_kernel, dim3(1 + SETUP_TWIDDLE_BLOCKS), dim3(SETUP_THREADS), 0, st, dev_items,
+                       L, grid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(ols_batch_spectra_kernel, dim3(sgrid), dim3(256), 0, st, L);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -754,6 +754,24 @@ OLS_HD int batch_class(int N, int nf) { return 2 * (ilog2(N) - 8) + (nf - 1); }
 // 4-18 % slower on the uneven batch.
 OLS_HD int64_t first_batch_tile(int64_t b) { return b; }
 OLS_HD int64_t next_batch_tile(int64_t t, int64_t P) { return t + P; }
+// A batch with fewer tiles than the grid has workgroups splits the filter
+// groups of each tile over several entries of the tile list (every entry
+// transforms its segments again): as many as fill the grid, at most one per
+// group.  Larger batches keep one entry per tile.
+OLS_HD int batch_tile_parts(int64_t tiles, int64_t grid, int groups) {
+  const int64_t p = tiles > 0 ? grid / tiles : 1;
+  return p < 1 ? 1 : (p > groups ? groups : (int)p);
+}
+// Units [u0, u1) of entry e (within its item): part e mod parts of tile e /
+// parts, whose `groups` units are split evenly.
+struct BatchEntry {
+  int64_t u0, u1;
+};
+OLS_HD BatchEntry batch_entry(int64_t e, int groups, int parts) {
+  const int64_t tile = e / parts;
+  const int q = (int)(e - tile * parts);
+  return BatchEntry{tile * groups + (int64_t)groups * q / parts, tile * groups + (int64_t)groups * (q + 1) / parts};
+}
 // Workgroup index b of launch index blk: the hardware deals workgroups to the
 // 8 XCDs round-robin by launch index, so consecutive b (consecutive chunks of
 // a round, which share overlap samples and spectra) are put on one XCD and
