@@ -548,6 +548,38 @@ struct RunWaveLocal {
   }
 };
 
+// Whether every wave keeps to its own block of cells (1024 positions, padded)
+// in the accesses that the device's exchanges leave without a barrier: both
+// sides of the exchange between passes P-2 and P-1, and the pass P-2 side of
+// the one before it.  Returns the block size in cells, 0 if a wave leaves its
+// block or the two layouts disagree on it.
+template <int N, int E, int K>
+bool in_own_block(int block) {
+  using GE = Geo<N>;
+  for (int t = 0; t < GE::WG; ++t)
+    for (int j = 0; j < GE::slots(K); ++j)
+      for (int a = 0; a < GE::radix(K); ++a) {
+        const int cell = lds_base<N, E, K>(t / GE::G, t % GE::G) + lds_off<N, E, K>(j, a);
+        if (cell < block * (t / 64) || cell >= block * (t / 64 + 1)) return false;
+      }
+  return true;
+}
+template <int N>
+struct RunWaveBlock {
+  static int run(int32_t* out) {
+    using GE = Geo<N>;
+    out[0] = 0;
+    if constexpr (GE::P >= 3) {
+      constexpr int P = GE::P;
+      const int block = GE::pad(P - 2, 1024);
+      if (GE::pad(P - 3, 1024) == block && in_own_block<N, P - 2, P - 2>(block) &&
+          in_own_block<N, P - 2, P - 1>(block) && in_own_block<N, P - 3, P - 2>(block))
+        out[0] = block;
+    }
+    return 0;
+  }
+};
+
 template <int N>
 struct RunGeo {
   static int run(int32_t* out) {
@@ -711,6 +743,10 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
   (void)units;
   return 0;
 }
+
+// Cells of the LDS block that a wave keeps to in the exchanges without a
+// barrier, or 0 (see RunWaveBlock).
+int ols_emu_wave_block(int N, int32_t* out) { return ols::emu::dispatch<ols::emu::RunWaveBlock>(N, out); }
 
 // Natural-order filter spectra out[K][N] = FFT_N(pad h_r) / N through the kernel dataflow.
 int ols_emu_spectra(int N, const float* h, int K, int M, float* out) {

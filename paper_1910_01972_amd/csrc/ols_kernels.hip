@@ -29,60 +29,69 @@ namespace ols {
 // ---------------------------------------------------------------------------
 // Transform drivers (device): passes in registers, exchanges through LDS.
 // ---------------------------------------------------------------------------
-// Synchronisation of an exchange.  When a transform spans several waves
-// (G > 64) the exchange crosses waves and needs a workgroup barrier.  When
-// every transform lives inside one wave (G <= 64), a wave only ever touches
-// the LDS interval of its own transforms, in every exchange and every buffer,
-// and the LDS completes a wave's operations in program order: no barrier is
-// needed, only a fence that keeps the compiler from reordering the reads of
-// other lanes' data before the writes.
-template <int N>
-__device__ __forceinline__ void exchange_sync() {
-  if constexpr (Geo<N>::G <= 64) {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
+// When every transform lives inside one wave (G <= 64), a wave only ever
+// touches the LDS interval of its own transforms, in every exchange and every
+// buffer, and the LDS completes a wave's operations in program order: no
+// barrier is needed, only a fence that keeps the compiler from reordering the
+// reads of other lanes' data before the writes.
+//
+// Where the exchanges of a transform that spans several waves need barriers.
+// The exchange between passes P-2 and P-1 is local: it keeps every value in
+// the wave that wrote it, and wave w touches only its own block of LDS cells
+// (positions 1024 w .. 1024 w + 1023).  So does the read of a forward
+// transform's exchange before it, and the write of an inverse's exchange after
+// it, and the two layouts pad a block to the same cells (the host emulator
+// checks this for every N).  The other exchanges are crossing: one side of
+// them meets every block, and takes a workgroup barrier.
+//
+// Crossing exchanges alternate between two LDS buffers of GE::LDS elements
+// (`par` selects the next one's), and a local exchange uses the buffer of the
+// crossing exchange it adjoins: the one before it (forward) or after it
+// (inverse).  One barrier per crossing exchange then suffices: between the
+// barriers n-1 and n, buffer n mod 2 sees the writes of crossing exchange n
+// and the local exchange before it, whose wave has passed barrier n-1, so
+// every wave has arrived there and finished everything it does in that buffer
+// after barrier n-2; after barrier n it sees the reads, and the local exchange
+// of a forward transform, in the wave's own block, which other waves write
+// only after barrier n+1.  A transform of three passes thus has one barrier,
+// one of four passes two.  Transforms inside one wave need neither barriers
+// nor a second buffer: they keep using the first.
+template <class GE, int E>
+constexpr bool exchange_local() { return GE::G <= 64 || E == GE::P - 2; }
 
-// Exchanges alternate between two LDS buffers of GE::LDS elements (GE: Geo<N> of the workgroup).  All
-// lanes of the workgroup see the same sequence of exchanges, so one barrier
-// per exchange suffices: a lane that passes the barrier of exchange n+1 knows
-// every lane has finished reading exchange n (program order), and exchange n+2
-// reuses exchange n's buffer.  `par` selects the buffer of the next exchange.
-// Single-wave transforms need no second buffer (their exchanges are
-// wave-private and in order), so they keep using the first.
 template <class GE, int E, int KW, int KR>
 __device__ __forceinline__ void exchange(float2 (&x)[16], float2* lds, int& par, int grp, int g) {
   constexpr int N = GE::N;
-  float2* buf = lds + ((GE::G > 64 && par) ? GE::LDS : 0);
-  par ^= 1;
+  constexpr bool LOCAL = exchange_local<GE, E>();
+  constexpr bool FWD = KR > KW;
+  const int which = GE::G <= 64 ? 0 : (LOCAL && FWD) ? par ^ 1 : par;
+  float2* buf = lds + (which ? GE::LDS : 0);
+  if constexpr (!LOCAL) par ^= 1;
   lds_store<N, E, KW>(buf, x, grp, g);
-  exchange_sync<N>();
+  if constexpr (LOCAL) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  else __syncthreads();
   lds_load<N, E, KR>(buf, x, grp, g);
 }
 
-// NF independent transforms exchanged together: one buffer each, written
-// before one barrier and read after it; the second barrier protects the
-// buffers from the next exchange's writes.  The last exchange of the
-// transform (between passes P-2 and P-1) keeps every value inside the wave
-// that wrote it (both layouts put position bits 10 and up in the wave index;
-// the host emulator checks this for every N), so its first barrier is
-// replaced by a wave-scope fence; the second still guards the next exchange,
-// whose writes cross waves.
+// The exchanges of NF inverse transforms together: one buffer each.  A
+// crossing exchange is written before one barrier and read after it, and the
+// second barrier protects the buffers from the next unit's writes; the local
+// exchange before it needs neither.
 template <class GE, int NF, int E, int KW, int KR>
 __device__ __forceinline__ void exchange_nf(float2 (&x)[NF][16], float2* lds, int& par, int grp, int g) {
   constexpr int N = GE::N;
   if constexpr (NF == 1) {
     exchange<GE, E, KW, KR>(x[0], lds, par, grp, g);
   } else {
+    static_assert(GE::P <= 3 && KR < KW, "one crossing exchange of an inverse transform");
 #pragma unroll
     for (int f = 0; f < NF; ++f) lds_store<N, E, KW>(lds + f * GE::LDS, x[f], grp, g);
-    if constexpr (E == GE::P - 2) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    else exchange_sync<N>();
+    if constexpr (exchange_local<GE, E>()) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    else __syncthreads();
 #pragma unroll
     for (int f = 0; f < NF; ++f) lds_load<N, E, KR>(lds + f * GE::LDS, x[f], grp, g);
-    exchange_sync<N>();
+    if constexpr (exchange_local<GE, E>()) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    else __syncthreads();
   }
 }
 
@@ -334,7 +343,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
     } else {
       static_assert(GE::SEGS * stage_stride<N>() <= GE::LDS, "stage slots fit in an exchange buffer");
       if constexpr (NF == 1) {
-        // one more exchange of the two-buffer sequence (see exchange)
+        // one more crossing exchange of the two-buffer sequence (see exchange)
         float2* region = lds + (par ? GE::LDS : 0) + grp * stage_stride<N>();
         par ^= 1;
         stage_write<N>(region, x[0], g);
@@ -1037,15 +1046,20 @@ struct BwdGeo {
   static_assert(SEGS % 2 == 0, "groups come in pairs");
 };
 
-// One exchange through a single LDS buffer: the buffer is reused by the next
-// exchange, so transforms that span several waves also need the trailing
-// barrier (single-wave transforms exchange in program order).
+// One exchange through a single LDS buffer (see exchange).  A forward
+// transform's crossing write meets every block, so it waits for all waves to
+// have left theirs; an inverse's crossing read does, so it is followed by a
+// barrier.
 template <int N, int E, int KW, int KR>
 __device__ __forceinline__ void exchange_single(float2 (&x)[16], float2* buf, int grp, int g) {
+  constexpr bool LOCAL = exchange_local<Geo<N>, E>();
+  constexpr bool FWD = KR > KW;
+  if constexpr (!LOCAL && FWD) __syncthreads();
   lds_store<N, E, KW>(buf, x, grp, g);
-  exchange_sync<N>();
+  if constexpr (LOCAL) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  else __syncthreads();
   lds_load<N, E, KR>(buf, x, grp, g);
-  if constexpr (Geo<N>::G > 64) __syncthreads();
+  if constexpr (!LOCAL && !FWD) __syncthreads();
 }
 
 template <int N, int K>

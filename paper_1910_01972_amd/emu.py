@@ -214,6 +214,15 @@ def row_shift(y_addr: int, Ns: int, D: int, r: int, mask: int) -> int:
     return int(emu().ols_emu_row_shift(ctypes.c_void_p(y_addr), Ns, D, r, mask))
 
 
+def wave_block(N: int) -> int:
+    """LDS cells of the block a wave keeps to in every exchange access that the
+    device leaves without a barrier; 0 if some wave leaves its block."""
+    out = (ctypes.c_int32 * 1)()
+    if emu().ols_emu_wave_block(N, out) != 0:
+        raise ValueError(N)
+    return int(out[0])
+
+
 def batched(items, grid: int):
     """items: list of dicts with s (complex64 [N_s]), h (complex64 [K][M]), N,
     D, H (H = 0: the library's geometry, including the row shift of outputs
