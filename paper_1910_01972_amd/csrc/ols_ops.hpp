@@ -9,12 +9,64 @@
 
 namespace ols {
 
+// Raw buffers of the device code.  Loads and stores of a wave that holds one
+// segment (G >= 64) go through a buffer resource over exactly the elements
+// that exist: the hardware range check returns zero for the loads outside it
+// and drops the stores (a negative offset wraps to a huge unsigned one), with
+// no per-lane compare, branch or zero fill and 32-bit offsets.
+#if defined(__HIP_DEVICE_COMPILE__)
+constexpr int CPOL_NT = 2;  // cache-policy operand of the buffer builtins: nt
+
+// Raw buffer over [base, base + bytes).
+template <class P>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(P base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, bytes, 0x00020000);
+}
+
+// Element at byte offset off (zero outside the buffer).
+__device__ __forceinline__ float2 buffer_load_c64(__amdgpu_buffer_rsrc_t rs, int off) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+  return make_float2(__uint_as_float(d.x), __uint_as_float(d.y));
+}
+__device__ __forceinline__ float buffer_load_f32(__amdgpu_buffer_rsrc_t rs, int off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+}
+
+// Buffer over the elements of window [start, start + len) of an array of n that
+// exist, and the number of the window's elements before the first of them.
+// start is the same in every lane.
+struct WindowBuffer {
+  __amdgpu_buffer_rsrc_t rs;
+  int skip;
+};
+template <class P>
+__device__ __forceinline__ WindowBuffer window_buffer(P src, int64_t start, int len, int64_t n, int el) {
+  const int64_t before = start < 0 ? -start : 0;
+  const int skip = before < len ? (int)before : len;
+  const int64_t first = start + skip, rem = n - first;  // first >= 0, or the window is empty
+  const int count = rem <= 0 ? 0 : (rem < len - skip ? (int)rem : len - skip);
+  return WindowBuffer{make_rsrc(wave_uniform_ptr(src + (count > 0 ? first : 0)),
+                                __builtin_amdgcn_readfirstlane(count * el)),
+                      __builtin_amdgcn_readfirstlane(skip)};
+}
+#endif
+
 // Segment j covers signal samples start .. start + N - 1 with
 // start = j*H - D (D >= M-1 samples of history, sec. 3.2); samples outside
 // [0, N_s) read as zero.  Register reg of lane g receives the sample at
 // position g + time_pos_const(reg) of the segment.
 template <int N, class P>
 OLS_HD void load_segment(float2 (&x)[16], P __restrict__ s, int64_t Ns, int64_t start, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (Geo<N>::G >= 64) {
+    const WindowBuffer w = window_buffer(s, start, N, Ns, 8);
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg)
+      x[reg] = buffer_load_c64(w.rs, (g + time_pos_const<N>(reg) - w.skip) * 8);
+    return;
+  }
+#endif
   // valid positions p satisfy lo <= p < hi (clamped into [0, N])
   const int64_t lo64 = -start, hi64 = Ns - start;
   const int lo = lo64 <= 0 ? 0 : (lo64 >= N ? N : (int)lo64);
@@ -75,6 +127,17 @@ OLS_HD void load_filter_real(float2 (&x)[16], const float* __restrict__ h, int M
 // window start of segment 2q; segment 2q+1 starts H samples later.
 template <int N, class P>
 OLS_HD void load_segment_pair(float2 (&x)[16], P __restrict__ s, int64_t Ns, int64_t start, int H, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (Geo<N>::G >= 64) {
+    const WindowBuffer a = window_buffer(s, start, N, Ns, 4), b = window_buffer(s, start + H, N, Ns, 4);
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) {
+      const int p = g + time_pos_const<N>(reg);
+      x[reg] = make_float2(buffer_load_f32(a.rs, (p - a.skip) * 4), buffer_load_f32(b.rs, (p - b.skip) * 4));
+    }
+    return;
+  }
+#endif
   const int64_t lo0 = -start, hi0 = Ns - start;
   const int lo_a = lo0 <= 0 ? 0 : (lo0 >= N ? N : (int)lo0);
   const int hi_a = hi0 <= 0 ? 0 : (hi0 >= N ? N : (int)hi0);
@@ -189,15 +252,6 @@ OLS_HD void out_store(P p, f32x4 v) {
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-constexpr int CPOL_NT = 2;  // cache-policy operand of the buffer builtins: nt
-
-// Raw buffer over [base, base + bytes): accesses at offsets >= bytes are
-// dropped by the range check.
-template <class P>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t out_rsrc(P base, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, bytes, 0x00020000);
-}
-
 template <int CPOL>
 __device__ __forceinline__ void buffer_store(float2 v, __amdgpu_buffer_rsrc_t rs, int off) {
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -278,7 +332,7 @@ OLS_HD void store_segment(T* __restrict__ yrow, int64_t Ns, int64_t out0, int D,
     // wave-uniform; saying so keeps the descriptor in scalar registers (the
     // compiler cannot always prove it, and would loop over the lanes)
     const __amdgpu_buffer_rsrc_t rs =
-        out_rsrc(wave_uniform_ptr(yrow + out0), __builtin_amdgcn_readfirstlane(cnt * (int)sizeof(T)));
+        make_rsrc(wave_uniform_ptr(yrow + out0), __builtin_amdgcn_readfirstlane(cnt * (int)sizeof(T)));
     if (whole) {
 #pragma unroll
       for (int reg = R0; reg < R0 + NR; ++reg)
@@ -420,7 +474,7 @@ OLS_HD void store_phase(T* __restrict__ yrow, int64_t Ns, int64_t out0, int D, i
   const int cnt = kept_count(Ns, out0, H);
 #if defined(__HIP_DEVICE_COMPILE__)
   if constexpr (Geo<N>::G >= 64) {
-    const __amdgpu_buffer_rsrc_t rs = out_rsrc(wave_uniform_ptr(yrow + (int64_t)J * out0),
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(wave_uniform_ptr(yrow + (int64_t)J * out0),
                                                __builtin_amdgcn_readfirstlane(J * cnt * (int)sizeof(T)));
 #pragma unroll
     for (int reg = 0; reg < 16; ++reg)
@@ -559,6 +613,14 @@ OLS_HD void stage_store(const float2* __restrict__ region, const S& st, P yrow, 
 // start + p < N_s (start >= 0); zero elsewhere.
 template <int N>
 OLS_HD void load_window(float2 (&x)[16], const float2* __restrict__ src, int64_t Ns, int64_t start, int lim, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (Geo<N>::G >= 64) {
+    const WindowBuffer w = window_buffer(src, start, lim, Ns, 8);
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) x[reg] = buffer_load_c64(w.rs, (g + time_pos_const<N>(reg)) * 8);
+    return;
+  }
+#endif
   const int64_t rem = Ns - start;
   const int hi = rem <= 0 ? 0 : (rem >= lim ? lim : (int)rem);
 #pragma unroll
