@@ -1142,13 +1142,10 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
     for (int i = 0; i < 16; ++i) x[i] = E[i];
     inv_single<N, GE::P - 1>(x, xbuf, tw, grp, g);
     const bool complete = tile * KP >= u0 && (tile + 1) * KP <= u1;
-    if (complete) {
-      store_valid<N>(x, ds, Ns, seg * H, 0, H, g);
-    } else {
-      const int slot = tile == t_first ? 0 : 1;
-      float2* w = ws_ds + ((b * 2 + slot) * BG::SEGS + grp) * (int64_t)N;
-      store_valid<N>(x, w, (int64_t)H, 0, 0, H, g);
-    }
+    // the outputs, or this workgroup's part of them in its slot
+    const int slot = tile == t_first ? 0 : 1;
+    float2* const w = ws_ds + ((b * 2 + slot) * BG::SEGS + grp) * (int64_t)N;
+    store_valid<N>(x, complete ? ds : w, complete ? Ns : (int64_t)H, complete ? seg * H : 0, 0, H, g);
   };
   // gradient window of filter r (r < K) of this group's segment, forward
   // transformed into x and accumulated into E when it is a real filter

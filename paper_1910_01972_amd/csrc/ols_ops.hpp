@@ -163,6 +163,22 @@ OLS_HD int spectrum_offset(int reg, int g) { return (((reg >> 1) * Geo<N>::G + g
 
 template <int N, class P>
 OLS_HD void load_spectrum(float2 (&f)[16], P __restrict__ F, int r, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (N == 2048) {
+    // One lane offset and scalar strides instead of eight 64-bit lane
+    // addresses: 2^23 x 32 431.5 -> 428.9 us, its power 377 -> 370.5.  At N =
+    // 1024 and 4096 level or slower (2^18 x 16, N = 4096: 16.1 -> 17.4).
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(wave_uniform_ptr(F + (int64_t)r * N), N * 8);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, g * 16, j * Geo<N>::G * 16, 0);
+      f[2 * j] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+      f[2 * j + 1] = make_float2(__uint_as_float(v.z), __uint_as_float(v.w));
+    }
+    return;
+  }
+#endif
   const auto Fr = rebind_ptr<const f32x4>(F + (int64_t)r * N);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -342,6 +358,18 @@ OLS_HD void store_segment(T* __restrict__ yrow, int64_t Ns, int64_t out0, int D,
       for (int reg = R0; reg < R0 + NR; ++reg)
         buffer_store<0>(val(reg), rs, (g + time_pos_const<N>(reg) - D) * (int)sizeof(T));
     }
+    return;
+  }
+#endif
+#if defined(__HIP_DEVICE_COMPILE__)
+  // the paired adjoint's windows (2^22 x 16: N = 1024 222.5 -> 220, N = 2048 264 ->
+  // 261.5 us; at N = 4096 level, at N = 8192 more spills, 212 -> 217)
+  if constexpr (MODE == STORE_PLAIN && Geo<N>::G >= 64 && N <= 2048) {
+    const __amdgpu_buffer_rsrc_t rs =
+        make_rsrc(wave_uniform_ptr(yrow + out0), __builtin_amdgcn_readfirstlane(cnt * (int)sizeof(T)));
+#pragma unroll
+    for (int reg = R0; reg < R0 + NR; ++reg)
+      buffer_store<0>(val(reg), rs, (g + time_pos_const<N>(reg) - D) * (int)sizeof(T));
     return;
   }
 #endif
