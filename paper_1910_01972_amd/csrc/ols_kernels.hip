@@ -152,9 +152,9 @@ struct SpectraShift {
 };
 
 template <int N>
-__device__ __forceinline__ void filter_spectra_block(const void* __restrict__ h, int K, int M, float2* __restrict__ F,
-                                                     const float2* __restrict__ twt, int diff, int real, int r0,
-                                                     float2* lds, const SpectraShift sh = SpectraShift{}) {
+__device__ __forceinline__ void filter_transform(float2 (&x)[16], const void* __restrict__ h, int K, int M,
+                                                 const float2* __restrict__ twt, int diff, int real, int r0,
+                                                 float2* lds, const SpectraShift sh = SpectraShift{}) {
   using GE = Geo<N>;
   const int tid = threadIdx.x;
   const int grp = tid / GE::G, g = tid - grp * GE::G;
@@ -162,7 +162,6 @@ __device__ __forceinline__ void filter_spectra_block(const void* __restrict__ h,
   int par = 0;
   float2 tw[GE::TWR];
   load_lane_twiddles<N>(tw, twt, g);
-  float2 x[16];
   const bool valid = r < K;
   const int64_t row = (int64_t)(valid ? r : 0) * M;
   const int delay = sh.mask ? row_delay(sh.y, sh.el, sh.Ns, sh.D, r, sh.mask) : 0;
@@ -170,16 +169,50 @@ __device__ __forceinline__ void filter_spectra_block(const void* __restrict__ h,
   else if (diff) load_filter_diff<N>(x, (const float2*)h + row, M, valid, g, delay);
   else load_filter<N>(x, (const float2*)h + row, M, valid, g, delay);
   fwd_from<GE, 0>(x, lds, par, tw, grp, g);
-  if (valid) store_spectrum<N>(x, F, r, g, 1.0f / (float)N);
 }
 
+// root[m] = exp(-2 pi i m / N), m < N, evaluated in float64 and rounded once
+// (plan creation).
+__global__ void ols_roots_kernel(float2* __restrict__ root, int N) {
+  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= N) return;
+  double sn, cs;
+  sincospi(2.0 * (double)m / (double)N, &sn, &cs);
+  root[m] = make_float2((float)cs, (float)(-sn));
+}
+
+// The spectra of the plan's filters, and (Fd != nullptr, gridDim.y delays) the
+// same spectra delayed by d = blockIdx.y samples for output rows off the
+// 128-byte grid: Fd[d][r] = F[r] * exp(-2 pi i k d / N), in the same storage
+// order (the phase from the exact integer k * d mod N).  Computed with the
+// spectra, so that a forward call only reads the plan.  Every delay transforms
+// the filters again: K / SEGS workgroups leave most CUs idle, and one launch
+// with the phases read from the table replaces two, the second of which
+// evaluated a float64 sine and cosine per value (16 filters, N = 4096, per
+// filter update: 5.7 + 6.4 us and a launch gap -> 6.4 us).
 template <int N>
 __global__ __launch_bounds__(Geo<N>::WG) void ols_filter_spectra_kernel(const void* __restrict__ h, int K, int M,
                                                                         float2* __restrict__ F,
-                                                                        const float2* __restrict__ twt, int diff,
-                                                                        int real, const SpectraShift sh) {
-  __shared__ float2 lds[2 * Geo<N>::LDS];
-  filter_spectra_block<N>(h, K, M, F, twt, diff, real, blockIdx.x * Geo<N>::SEGS, lds, sh);
+                                                                        float2* __restrict__ Fd,
+                                                                        const float2* __restrict__ twt,
+                                                                        const float2* __restrict__ root, int diff,
+                                                                        int real) {
+  using GE = Geo<N>;
+  __shared__ float2 lds[2 * GE::LDS];
+  const int grp = threadIdx.x / GE::G, g = threadIdx.x - grp * GE::G;
+  const int r0 = blockIdx.x * GE::SEGS, r = r0 + grp, d = blockIdx.y;
+  float2 x[16];
+  filter_transform<N>(x, h, K, M, twt, diff, real, r0, lds);
+  if (r >= K) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = cscale(x[i], 1.0f / (float)N);
+  if (d == 0) store_spectrum<N>(x, F, r, g);
+  if (!Fd) return;
+  if (d > 0) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = cmul(x[i], root[(spectrum_index<N>(g, i) * d) & (N - 1)]);
+  }
+  store_spectrum<N>(x, Fd + (int64_t)d * K * N, r, g);
 }
 
 // Natural-order copy of the spectra: out[r][k] = F[r][spectrum_offset(reg, g)]
@@ -193,28 +226,6 @@ __global__ void ols_spectra_natural_kernel(const float2* __restrict__ F, int K, 
   const int pair = rem >> 1, j = pair / Geo<N>::G, g = pair - j * Geo<N>::G;
   const int reg = 2 * j + (rem & 1);
   out[(int64_t)r * N + spectrum_index<N>(g, reg)] = F[i];
-}
-
-// The filter spectra delayed by every d = 0 .. LS-1 samples, for output rows
-// off the 128-byte grid: out[d][r] = F[r] * exp(-2 pi i k d / N), in the same
-// storage order (the phase from the exact integer k * d mod N, in float64).
-// Computed with the spectra, so that a forward call only reads the plan.
-template <int N>
-__global__ void ols_spectra_delays_kernel(const float2* __restrict__ F, int K, int LS, float2* __restrict__ out) {
-  const int64_t KN = (int64_t)K * N;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // over LS * K * N
-  if (i >= KN * LS) return;
-  const int d = (int)(i / KN);
-  const int64_t ir = i - d * KN;  // element of F
-  const int r = (int)(ir / N);
-  const int rem = (int)(ir - (int64_t)r * N);  // = spectrum_offset(reg, g)
-  const int pair = rem >> 1, j = pair / Geo<N>::G, g = pair - j * Geo<N>::G;
-  const int reg = 2 * j + (rem & 1);
-  const int k = spectrum_index<N>(g, reg);
-  const int m = (int)(((int64_t)k * d) % N);
-  double sn, cs;
-  sincospi(2.0 * (double)m / (double)N, &sn, &cs);
-  out[i] = cmul(F[ir], make_float2((float)cs, (float)(-sn)));
 }
 
 // ---------------------------------------------------------------------------
@@ -768,8 +779,13 @@ __device__ __forceinline__ int find_item(int first, int n, int64_t v, Begin begi
 template <int N>
 __device__ __attribute__((noinline)) void batch_spectra_task(const BatchItem& it, const float2* __restrict__ twt,
                                                               int r0, float2* lds) {
-  filter_spectra_block<N>(it.h, it.K, it.M, (float2*)it.spectra, twt, 0, 0, r0, lds,
-                          SpectraShift{it.y, it.Ns, 8, it.D, it.shift_mask});
+  float2 x[16];
+  filter_transform<N>(x, it.h, it.K, it.M, twt, 0, 0, r0, lds, SpectraShift{it.y, it.Ns, 8, it.D, it.shift_mask});
+  const int r = r0 + threadIdx.x / Geo<N>::G;
+  if (r >= it.K) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = cscale(x[i], 1.0f / (float)N);
+  store_spectrum<N>(x, (float2*)it.spectra, r, threadIdx.x % Geo<N>::G);
 }
 
 // Filter spectra of every item: task tau is one workgroup's filters of one
@@ -1379,6 +1395,7 @@ struct ols_plan_s {
   float2* spectra_delays = nullptr;  // [delay_ls][K][N]: the spectra delayed by 0 .. delay_ls-1 samples
   int delay_ls = 0;                   // outputs per 128-byte line (0: no delayed spectra, rows not re-aligned)
   float2* twiddles = nullptr;
+  float2* roots = nullptr;  // exp(-2 pi i m / N), m < N; part of the twiddles' allocation
 };
 
 struct ols_batch_s {
@@ -1415,18 +1432,12 @@ struct Kern {
   using GE = Geo<N>;
   static constexpr bool HAS_NF2 = N <= 4096;
 
-  static hipError_t spectra(const void* h, int K, int M, float2* F, const float2* tw, hipStream_t st, int diff,
-                            int real) {
-    const int blocks = (K + GE::SEGS - 1) / GE::SEGS;
-    hipLaunchKernelGGL(ols_filter_spectra_kernel<N>, dim3(blocks), dim3(GE::WG), 0, st, h, K, M, F, tw, diff, real,
-                       SpectraShift{});
-    return hipGetLastError();
-  }
-  static hipError_t delays(const float2* F, int K, int LS, float2* out, hipStream_t st) {
-    const int64_t total = (int64_t)K * N * LS;
-    const int threads = 256;
-    const int64_t blocks = (total + threads - 1) / threads;
-    hipLaunchKernelGGL(ols_spectra_delays_kernel<N>, dim3((unsigned)blocks), dim3(threads), 0, st, F, K, LS, out);
+  // the plan's spectra, and its spectra for every row delay if it holds them
+  static hipError_t spectra(const ols_plan_s* p, const void* h, hipStream_t st) {
+    const int blocks = (p->K + GE::SEGS - 1) / GE::SEGS;
+    hipLaunchKernelGGL(ols_filter_spectra_kernel<N>, dim3(blocks, p->spectra_delays ? p->delay_ls : 1), dim3(GE::WG), 0,
+                       st, h, p->K, p->M, p->spectra, p->spectra_delays, p->twiddles, p->roots,
+                       (p->flags & OLS_POST_DERIVATIVE) ? 1 : 0, (p->flags & OLS_REAL) ? 1 : 0);
     return hipGetLastError();
   }
   static hipError_t natural(const float2* F, int K, float2* out, hipStream_t st) {
@@ -1640,15 +1651,7 @@ auto dispatch(int N, Args&&... args) -> decltype(F<256>::run(args...)) {
 
 template <int N>
 struct RunSpectra {
-  static hipError_t run(const void* h, int K, int M, float2* F, const float2* tw, hipStream_t st, int diff, int real) {
-    return Kern<N>::spectra(h, K, M, F, tw, st, diff, real);
-  }
-};
-template <int N>
-struct RunDelays {
-  static hipError_t run(const float2* F, int K, int LS, float2* out, hipStream_t st) {
-    return Kern<N>::delays(F, K, LS, out, st);
-  }
+  static hipError_t run(const ols_plan_s* p, const void* h, hipStream_t st) { return Kern<N>::spectra(p, h, st); }
 };
 template <int N>
 struct RunNatural {
@@ -1930,8 +1933,10 @@ ols_status_t ols_plan_ex(ols_plan_t* plan, const void* h, int32_t K, int32_t M, 
     p->segs = dispatch<RunShape>(N, 1);
 
     std::vector<float2> tw = dispatch<RunTwiddles>(N);
-    e = hipMalloc(&p->twiddles, tw.size() * sizeof(float2));
+    // the twiddle tables and, behind them, the N-th roots of unity
+    e = hipMalloc(&p->twiddles, (tw.size() + N) * sizeof(float2));
     if (e != hipSuccess) { destroy_plan(p); (void)hipGetLastError(); return fail(OLS_ERROR_OUT_OF_MEMORY, "twiddle allocation"); }
+    p->roots = p->twiddles + tw.size();
     e = hipMalloc(&p->spectra, (size_t)K * N * sizeof(float2));
     if (e != hipSuccess) { destroy_plan(p); (void)hipGetLastError(); return fail(OLS_ERROR_OUT_OF_MEMORY, "spectra allocation"); }
     // the spectra for every row delay, when they fit the budget
@@ -1944,13 +1949,10 @@ ols_status_t ols_plan_ex(ols_plan_t* plan, const void* h, int32_t K, int32_t M, 
     hipStream_t st = (hipStream_t)stream;
     e = hipMemcpyAsync(p->twiddles, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "twiddle upload"); }
-    e = dispatch<RunSpectra>(N, h, K, M, p->spectra, (const float2*)p->twiddles, st,
-                             (flags & OLS_POST_DERIVATIVE) ? 1 : 0, (flags & OLS_REAL) ? 1 : 0);
+    hipLaunchKernelGGL(ols_roots_kernel, dim3((unsigned)(N / 256)), dim3(256), 0, st, p->roots, N);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = dispatch<RunSpectra>(N, (const ols_plan_s*)p, h, st);
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "filter spectra launch"); }
-    if (p->spectra_delays) {
-      e = dispatch<RunDelays>(N, (const float2*)p->spectra, K, p->delay_ls, p->spectra_delays, st);
-      if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "delayed spectra launch"); }
-    }
     e = hipStreamSynchronize(st);  // the host twiddle buffer and h are released after this
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "plan synchronisation"); }
     *plan = p;
@@ -1965,15 +1967,8 @@ ols_status_t ols_plan_update_filters(ols_plan_t p, const void* h, ols_stream_t s
     if (!p || !h) return fail(OLS_ERROR_INVALID_VALUE, "NULL argument");
     if (((uintptr_t)h) % ((p->flags & OLS_REAL) ? 4 : 8))
       return fail(OLS_ERROR_INVALID_VALUE, "h is not aligned to its element type");
-    hipError_t e = dispatch<RunSpectra>(p->N, h, p->K, p->M, p->spectra, (const float2*)p->twiddles,
-                                        (hipStream_t)stream, (p->flags & OLS_POST_DERIVATIVE) ? 1 : 0,
-                                        (p->flags & OLS_REAL) ? 1 : 0);
+    const hipError_t e = dispatch<RunSpectra>(p->N, (const ols_plan_s*)p, h, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "filter spectra launch");
-    if (p->spectra_delays) {
-      e = dispatch<RunDelays>(p->N, (const float2*)p->spectra, p->K, p->delay_ls, p->spectra_delays,
-                              (hipStream_t)stream);
-      if (e != hipSuccess) return hip_fail(e, "delayed spectra launch");
-    }
     return OLS_SUCCESS;
   } catch (...) {
     return fail(OLS_ERROR_INTERNAL, "exception in ols_plan_update_filters");

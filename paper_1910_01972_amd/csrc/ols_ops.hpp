@@ -189,7 +189,7 @@ OLS_HD void load_spectrum(float2 (&f)[16], P __restrict__ F, int r, int g) {
 }
 
 template <int N>
-OLS_HD void store_spectrum(const float2 (&x)[16], float2* __restrict__ F, int r, int g, float scale) {
+OLS_HD void store_spectrum(const float2 (&x)[16], float2* __restrict__ F, int r, int g, float scale = 1.0f) {
   float2* Fr = F + (int64_t)r * N;
 #pragma unroll
   for (int reg = 0; reg < 16; ++reg) Fr[spectrum_offset<N>(reg, g)] = cscale(x[reg], scale);
