@@ -77,7 +77,7 @@ typedef enum {
  * The plan owns device memory for the K filter spectra (8*K*N bytes), the
  * same spectra delayed by 0 .. LS-1 samples (LS = 16, or 32 for float32
  * outputs: 8*K*N*LS bytes, allocated only when that is at most 256 MiB; see
- * ols_forward) and the twiddle tables, all allocated here; forward calls
+ * ols_forward), the twiddle tables and the N-th roots of unity, all allocated here; forward calls
  * allocate nothing.  `h` may be freed as soon as the call returns.
  * Errors: INVALID_VALUE (null plan/h, K < 1, M < 1, M > N), UNSUPPORTED (N),
  * OUT_OF_MEMORY, HIP.
@@ -247,7 +247,7 @@ ols_status_t ols_backward(ols_plan_t plan, const void* s, int64_t N_s, const voi
  * ols_backward_static -- ols_backward for callers that cannot allocate device
  * memory (code under hipGraph capture, serving loops, harnesses that forbid
  * hipMalloc): the adjoint's scratch (partial ds windows of tiles shared by
- * workgroups, per-workgroup dh lag partials and their chunk sums) lives in a
+ * workgroups, per-workgroup dh lag partials) lives in a
  * library-owned static device array of OLS_STATIC_SCRATCH_BYTES per device,
  * held until the process ends, instead of plan memory.  Same arguments,
  * outputs and kernels as ols_backward; the call allocates nothing.
@@ -261,7 +261,7 @@ ols_status_t ols_backward(ols_plan_t plan, const void* s, int64_t N_s, const voi
  *     that may overlap in time on one device (different streams, or host
  *     threads without stream ordering) race and give wrong results.
  * Errors: as ols_backward, plus INVALID_VALUE when a single workgroup's scratch
- * (2*SEGS*N + SEGS*K*M complex64 plus chunk sums) exceeds
+ * (2*SEGS*N + SEGS*K*M complex64, and K*M more per 16 slots counted) exceeds
  * OLS_STATIC_SCRATCH_BYTES (the message gives both sizes), or when the plan
  * was made on another device.
  */
@@ -269,9 +269,8 @@ ols_status_t ols_backward(ols_plan_t plan, const void* s, int64_t N_s, const voi
 ols_status_t ols_backward_static(ols_plan_t plan, const void* s, int64_t N_s, const void* gy, void* ds, void* dh,
                                  ols_stream_t stream);
 
-/* Allocate the plan's backward workspace now (grid x 2 x SEGS x N,
- * grid x SEGS x K x M and ceil(grid x SEGS / 16) x K x M complex64,
- * grid = persistent workgroups), so that
+/* Allocate the plan's backward workspace now (grid x 2 x SEGS x N and
+ * grid x SEGS x K x M complex64, grid = persistent workgroups), so that
  * ols_backward never allocates.  Idempotent.  Errors: INVALID_VALUE,
  * OUT_OF_MEMORY, HIP. */
 ols_status_t ols_plan_reserve_backward(ols_plan_t plan);

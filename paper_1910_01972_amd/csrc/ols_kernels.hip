@@ -1209,14 +1209,27 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
   finish_tile();
 }
 
-// Sums the partial ds windows of tiles split between workgroups; block b-1
-// handles the boundary between workgroups b-1 and b (the first boundary
-// inside a tile does the whole tile).  SEGS transforms per tile, K units per
-// tile (the filters, or the filter pairs of the paired adjoint).
+// What is left after the adjoint kernel, in one launch: the partial ds windows
+// of tiles split between workgroups, and the dh slots.  Both are bound by
+// memory latency (few loads per lane, all in flight at once), and they are
+// independent; as a launch of their own for the windows and two for the slots
+// they took 12.7 + 6.9 + 5.0 us on the 2^22 x 16 x 512 adjoint and 4.2 + 3.0 +
+// 2.6 us on a 50000 x 4 x 64 one (whole adjoint, graph replays, us: 285.9 -> 282.0
+// and 21.6 -> 16.7; 512 threads 285.0 and 17.5, 1024 289.4 and 19.1; 32 lags per
+// workgroup leave it too few workgroups where K M is small, 2^22 x 16 x 64:
+// 226.9 against 221.3).
+constexpr int TAIL_THREADS = 256;
+constexpr int TAIL_SPLIT = 8;    // workgroups per tile boundary: at most 4 outputs per lane (H <= 8192)
+constexpr int TAIL_LAGS = 8;    // lags per workgroup of the dh part
+constexpr int TAIL_CHUNKS = TAIL_THREADS / TAIL_LAGS;  // chunks of slots summed at a time
+
+// The boundary between workgroups b-1 and b of the adjoint kernel (the first
+// boundary inside a tile does the whole tile): sums the windows of the sharing
+// workgroups in workgroup order.  SEGS transforms per tile, K units per tile
+// (the filters, or the filter pairs of the paired adjoint).
 template <int N, int SEGS>
-__global__ void ols_ds_fixup_kernel(const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K,
-                                    int H, int64_t ntiles, int64_t P) {
-  const int64_t b = (int64_t)blockIdx.x + 1;
+__device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K,
+                                         int H, int64_t ntiles, int64_t P, int64_t b, int split) {
   const int64_t U = ntiles * K;
   const int64_t ub = first_unit(U, P, b);
   if (ub % K == 0) return;
@@ -1228,12 +1241,9 @@ __global__ void ols_ds_fixup_kernel(const float2* __restrict__ ws_ds, float2* __
   // started in an earlier tile.  Hoisted out of the element loop (64-bit
   // divisions).
   const int64_t slot_lo = first_unit(U, P, blo) / K == t ? 0 : 1;
-  // blockIdx.y splits the window between workgroups: few outputs per lane,
-  // so the lanes' loads are all in flight at once
-  const int stride = blockDim.x * gridDim.y;
   for (int sg = 0; sg < SEGS; ++sg) {
     const int64_t o0 = (t * SEGS + sg) * H;
-    for (int p = threadIdx.x + blockIdx.y * blockDim.x; p < H; p += stride) {
+    for (int p = threadIdx.x + split * TAIL_THREADS; p < H; p += TAIL_SPLIT * TAIL_THREADS) {
       if (o0 + p >= Ns) break;
       // the sharing workgroups' windows in workgroup order, loaded four at a
       // time so that the loads overlap
@@ -1267,42 +1277,46 @@ __global__ void ols_ds_fixup_kernel(const float2* __restrict__ ws_ds, float2* __
   }
 }
 
-// a + part[s0][i] + part[s0 + 1][i] + ... + part[s1 - 1][i], added in that
-// order; the loads go out eight at a time so that their latencies overlap
-// (one at a time, the sum took ~9 us for 16 or 32 slots).
-__device__ __forceinline__ float2 sum_slots(const float2* __restrict__ part, int64_t s0, int64_t s1, int64_t KM,
-                                            int64_t i) {
-  float2 a = make_float2(0.f, 0.f);
-  int64_t sl = s0;
-  for (; sl + 8 <= s1; sl += 8) {
-    float2 v[8];
+// dh[i] for TAIL_LAGS values of i: the slots in chunks of DH_CHUNK, each chunk
+// in slot order by one thread per lag, then the chunk sums in chunk order
+// (TAIL_CHUNKS chunks at a time, handed over through LDS).
+__device__ __forceinline__ void dh_sums(const float2* __restrict__ part, int64_t nslots, int64_t KM,
+                                        float2* __restrict__ dh, int64_t block) {
+  __shared__ float2 sums[TAIL_CHUNKS][TAIL_LAGS];
+  const int lag = threadIdx.x % TAIL_LAGS, row = threadIdx.x / TAIL_LAGS;
+  const int64_t i = block * TAIL_LAGS + lag;
+  float2 total = make_float2(0.f, 0.f);
+  for (int64_t c0 = 0; c0 * DH_CHUNK < nslots; c0 += TAIL_CHUNKS) {
+    const int64_t s0 = (c0 + row) * DH_CHUNK;
+    float2 v[DH_CHUNK];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = part[(sl + k) * KM + i];
+    for (int k = 0; k < DH_CHUNK; ++k)
+      v[k] = (i < KM && s0 + k < nslots) ? part[(s0 + k) * KM + i] : make_float2(0.f, 0.f);
+    float2 a = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a = cadd(a, v[k]);
+    for (int k = 0; k < DH_CHUNK; ++k)
+      if (s0 + k < nslots) a = cadd(a, v[k]);
+    sums[row][lag] = a;
+    __syncthreads();
+    if (row == 0) {
+      const int64_t left = dh_chunks(nslots) - c0;
+      const int n = left < TAIL_CHUNKS ? (int)left : TAIL_CHUNKS;
+      for (int c = 0; c < n; ++c) total = cadd(total, sums[c][lag]);
+    }
+    __syncthreads();
   }
-  for (; sl < s1; ++sl) a = cadd(a, part[sl * KM + i]);
-  return a;
+  if (row == 0 && i < KM) dh[i] = total;
 }
 
-// First level of the dh reduction: sums[c][i] = sum of part[slot][i] over
-// the slots of chunk c = blockIdx.y, in slot order.
-__global__ void ols_dh_chunk_kernel(const float2* __restrict__ part, int64_t nslots, int64_t KM,
-                                    float2* __restrict__ sums) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= KM) return;
-  const int64_t c = blockIdx.y;
-  const int64_t s0 = c * DH_CHUNK, s1 = s0 + DH_CHUNK < nslots ? s0 + DH_CHUNK : nslots;
-  sums[c * KM + i] = sum_slots(part, s0, s1, KM, i);
-}
-
-// dh[i] = sum over slots of part[slot][i], in slot order (second level: the
-// chunk sums in chunk order).
-__global__ void ols_dh_reduce_kernel(const float2* __restrict__ part, int64_t nslots, int64_t KM,
-                                     float2* __restrict__ dh) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= KM) return;
-  dh[i] = sum_slots(part, 0, nslots, KM, i);
+// Workgroups [0, ndh) sum dh, which takes longer where there are many slots, the
+// others fix ds (either may be absent).
+template <int N, int SEGS>
+__global__ __launch_bounds__(TAIL_THREADS) void ols_backward_tail_kernel(
+    const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K, int H, int64_t ntiles, int64_t P,
+    int64_t ndh, const float2* __restrict__ part, int64_t nslots, int64_t KM, float2* __restrict__ dh) {
+  const int64_t blk = blockIdx.x;
+  if (blk < ndh) dh_sums(part, nslots, KM, dh, blk);
+  else ds_fixup<N, SEGS>(ws_ds, ds, Ns, K, H, ntiles, P, (blk - ndh) / TAIL_SPLIT + 1, (int)((blk - ndh) % TAIL_SPLIT));
 }
 
 // Plain fill with zero (used instead of a memset so callers may capture it).
@@ -1336,20 +1350,19 @@ constexpr int64_t SHIFT_MIN_OUTPUTS = (int64_t)1 << 22;
 constexpr int64_t SHIFT_SPECTRA_MAX_BYTES = (int64_t)256 << 20;
 
 // Scratch of the adjoint: partial ds windows of tiles split between
-// workgroups, per-workgroup dh lag partials and their chunk sums.  Sized for a
+// workgroups and per-workgroup dh lag partials.  Sized for a
 // grid of persistent workgroups (bwd_ws_bytes); every part is written before
 // it is read within one call, so nothing needs clearing beforehand.
 struct BwdWorkspace {
   int grid = 0;
   float2* ws_ds = nullptr;    // [grid][2][SEGS][N]
   float2* part_dh = nullptr;  // [grid][SEGS][K][M]
-  float2* sum_dh = nullptr;   // [dh_chunks(grid * SEGS)][K][M]
 };
 
 // Bytes of each part of a BwdWorkspace, each rounded up to 256 bytes.
 struct BwdWorkspaceSizes {
-  size_t ds = 0, part = 0, sums = 0;
-  size_t total() const { return ds + part + sums; }
+  size_t ds = 0, part = 0;
+  size_t total() const { return ds + part; }
 };
 
 inline size_t round256(size_t v) { return (v + 255) / 256 * 256; }
@@ -1358,8 +1371,15 @@ inline BwdWorkspaceSizes bwd_ws_bytes(int grid, int segs, int N, int K, int M) {
   BwdWorkspaceSizes z;
   z.ds = round256((size_t)grid * 2 * segs * N * sizeof(float2));
   z.part = round256((size_t)grid * segs * K * M * sizeof(float2));
-  z.sums = round256((size_t)dh_chunks((int64_t)grid * segs) * K * M * sizeof(float2));
   return z;
+}
+
+// What ols_backward_static counts against its scratch for a grid: the parts
+// above and a sum per DH_CHUNK slots, which an earlier two-launch reduction
+// stored; kept in the count so that the same plans and grids fit as before.
+inline size_t bwd_static_bytes(int grid, int segs, int N, int K, int M) {
+  return bwd_ws_bytes(grid, segs, N, K, M).total() +
+         round256((size_t)dh_chunks((int64_t)grid * segs) * K * M * sizeof(float2));
 }
 
 // Carves a workspace for `grid` workgroups out of one buffer of at least
@@ -1371,7 +1391,6 @@ inline BwdWorkspace bwd_ws_carve(void* base, int grid, int segs, int N, int K, i
   w.grid = grid;
   w.ws_ds = (float2*)b;
   w.part_dh = (float2*)(b + z.ds);
-  w.sum_dh = (float2*)(b + z.ds + z.part);
   return w;
 }
 
@@ -1611,22 +1630,12 @@ struct Kern {
                        ntiles, p->twiddles, ds, w.ws_ds, w.part_dh, ds ? 1 : 0, dh ? 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (ds && grid > 1) {
-      // one workgroup per (tile boundary, eighth of the window): H <= 8192 outputs, at most 4 per lane
-      hipLaunchKernelGGL((ols_ds_fixup_kernel<N, BWD_SEGS>), dim3((unsigned)(grid - 1), 8), dim3(256), 0, st, w.ws_ds,
-                         ds, Ns, upt, p->H, ntiles, grid);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    if (dh) {
-      const int64_t KM = (int64_t)p->K * p->M;
-      const int64_t nslots = grid * BWD_SEGS, nch = dh_chunks(nslots);
-      const unsigned bx = (unsigned)((KM + 255) / 256);
-      hipLaunchKernelGGL(ols_dh_chunk_kernel, dim3(bx, (unsigned)nch), dim3(256), 0, st, w.part_dh, nslots, KM,
-                         w.sum_dh);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(ols_dh_reduce_kernel, dim3(bx), dim3(256), 0, st, w.sum_dh, nch, KM, dh);
+    // split tiles' windows and the dh slots
+    const int64_t KM = (int64_t)p->K * p->M;
+    const int64_t nfix = ds ? (grid - 1) * TAIL_SPLIT : 0, ndh = dh ? (KM + TAIL_LAGS - 1) / TAIL_LAGS : 0;
+    if (nfix + ndh > 0) {
+      hipLaunchKernelGGL((ols_backward_tail_kernel<N, BWD_SEGS>), dim3((unsigned)(nfix + ndh)), dim3(TAIL_THREADS), 0,
+                         st, w.ws_ds, ds, Ns, upt, p->H, ntiles, grid, ndh, w.part_dh, grid * BWD_SEGS, KM, dh);
       e = hipGetLastError();
     }
     return e;
@@ -2193,12 +2202,12 @@ ols_status_t ols_backward_static(ols_plan_t p, const void* s, int64_t Ns, const 
     r = bwd_full_grid(p, &grid);
     if (r != OLS_SUCCESS) return r;
     // as many workgroups as the scratch holds, at most the full grid
-    const size_t one = bwd_ws_bytes(1, dispatch<RunBwdSegs>(p->N), p->N, p->K, p->M).total();
+    const size_t one = bwd_static_bytes(1, dispatch<RunBwdSegs>(p->N), p->N, p->K, p->M);
     if (one > OLS_STATIC_SCRATCH_BYTES)
       return fail(OLS_ERROR_INVALID_VALUE,
                   "the adjoint of this plan needs " + std::to_string(one) + " bytes of scratch per workgroup, more than "
                   "the " + std::to_string((size_t)OLS_STATIC_SCRATCH_BYTES) + " bytes of ols_backward_static");
-    while (grid > 1 && bwd_ws_bytes(grid, dispatch<RunBwdSegs>(p->N), p->N, p->K, p->M).total() > OLS_STATIC_SCRATCH_BYTES) --grid;
+    while (grid > 1 && bwd_static_bytes(grid, dispatch<RunBwdSegs>(p->N), p->N, p->K, p->M) > OLS_STATIC_SCRATCH_BYTES) --grid;
     void* base = nullptr;
     r = static_scratch_address(&base);
     if (r != OLS_SUCCESS) return r;
