@@ -167,8 +167,10 @@ ols_status_t ols_plan_set_hop(ols_plan_t plan, int32_t H);
  * resets the hop to that default and the tiling to one filter per unit and
  * the stage kernel's occupancy (ols_plan_set_tiling may change it after).
  * With y aligned to J output elements (always for J = 1), one or two phases
- * per sample are written as one element.  A plan with a stencil has no
- * ols_backward (UNSUPPORTED).
+ * per sample are written as one element.  A stencil with one phase is a
+ * convolution: up to N = 4096 it is applied to the segments' spectra instead
+ * of to staged outputs (results agree to rounding), one filter per unit.  A
+ * plan with a stencil has no ols_backward (UNSUPPORTED).
  * Errors: INVALID_VALUE (null plan or w, J, left, right out of range, filter
  * too long for the stencil), HIP.
  */
@@ -209,7 +211,7 @@ ols_status_t ols_plan_get_spectra(ols_plan_t plan, void* out, ols_stream_t strea
  * K*N_s*8 overflow), HIP (launch failure).  Allocates nothing.
  * Rows off the 128-byte grid (y not 128-byte aligned, or N_s not a multiple
  * of LS = 16, of 32 for float32 outputs), in calls of K*N_s >= 2^22 outputs
- * on plans that hold their delayed spectra and have no stencil: filter r is
+ * on plans that hold their delayed spectra and stage no stencil: filter r is
  * taken delayed by 0..LS-1 samples (the plan's precomputed spectrum times
  * the delay's phase) so that every store instruction of row r starts on a
  * 128-byte line, and the call runs with the hop rounded down to a multiple of

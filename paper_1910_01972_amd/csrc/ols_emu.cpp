@@ -164,6 +164,19 @@ void forward_range(const float2* s, int64_t Ns, const float2* F, float2* y, int 
   const int KG = (K + NF - 1) / NF;
   std::vector<std::array<float2, 16>> xs(GE::WG), A(GE::WG);
   UnitWalk w(u0, KG);  // the device kernels' walk
+  // a one-phase stencil is folded into the segments' spectra
+  Response resp{};
+  std::vector<float2> roots;
+  if (st && st->J == 1 && fold_stencil(N)) {
+    resp.T = st->T;
+    resp.L = st->L;
+    for (int d = 0; d < st->T; ++d) resp.w[d] = st->w[0][d];
+    for (int m = 0; m < N; ++m) {
+      const double a = 6.283185307179586476925286766559 * m / N;
+      roots.push_back(make_float2((float)std::cos(a), (float)-std::sin(a)));
+    }
+    st = nullptr;
+  }
   auto forward_tile = [&]() {
     for (int t = 0; t < GE::WG; ++t) {
       const int grp = t / GE::G, g = t % GE::G;
@@ -174,6 +187,12 @@ void forward_range(const float2* s, int64_t Ns, const float2* F, float2* y, int 
     }
     fwd_from<N, 0>(xs, G, tw);
     A = xs;
+    if (resp.T > 0)
+      for (int t = 0; t < GE::WG; ++t) {
+        float2 S[16];
+        stencil_response<N>(S, roots.data(), resp, t % GE::G);
+        for (int i = 0; i < 16; ++i) A[t][i] = cmul(A[t][i], S[i]);
+      }
   };
   forward_tile();
   for (int64_t u = u0; u < u1; ++u) {

@@ -275,6 +275,8 @@ constexpr int forward_lds() {
   return forward_bufs<GE, NF>() * GE::LDS + ((STAGE && GE::G <= 64) ? GE::SEGS * stage_stride<GE::N>() : 0);
 }
 
+// FOLD: the segments' spectra are multiplied by a one-phase stencil's transfer
+// function (apply_response).
 // STAGE: the outputs go through the non-local stencil stage (st) instead of
 // the plain store; the output rows then hold st->J * N_s elements.
 // shift_mask != 0 (output rows off the 128-byte grid): row r's filter is
@@ -284,12 +286,13 @@ constexpr int forward_lds() {
 // (delay_rows = K), a batched item has its rows' delayed spectra computed in
 // place (delay_rows = 0).
 template <int N, int NF, bool POWER = false, bool REAL = false, int SMODE = STORE_NT_WHOLE,
-          bool PF = prefetch_spectra<N, NF>(), bool STAGE = false, int WG = 0>
+          bool PF = prefetch_spectra<N, NF>(), bool STAGE = false, int WG = 0, bool FOLD = false>
 __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64_t Ns, const float2* __restrict__ F,
                                               void* __restrict__ yv, int K, int D, int H,
                                               const float2 (&tw)[Geo<N>::TWR], int64_t u0, int64_t u1, float2* lds,
                                               int& par, const Stencil* st = nullptr, int shift_mask = 0,
-                                              int delay_rows = 0) {
+                                              int delay_rows = 0, const Response* resp = nullptr,
+                                              const float2* __restrict__ root = nullptr) {
   using GE = Geo<N, WG>;
   const int tid = threadIdx.x;
   const int grp = tid / GE::G, g = tid - grp * GE::G;
@@ -312,6 +315,8 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
     const int64_t sg = t * GE::SEGS + grp;
     return GE::G >= 64 ? wave_uniform64(sg) : sg;
   };
+  float2 S[16];
+  if constexpr (FOLD) stencil_response<N>(S, to_global(root), *resp, g);
   // segment (pair) sg, forward transformed, into A (x is scratch)
   auto transform_segment = [&](float2 (&x)[16], int64_t sg) {
     if constexpr (REAL) load_segment_pair<N>(x, s_r, Ns, sg * step - D, H, g);
@@ -319,6 +324,10 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
     fwd_from<GE, 0>(x, lds, par, tw, grp, g);
 #pragma unroll
     for (int i = 0; i < 16; ++i) A[i] = x[i];
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) A[i] = cmul(A[i], S[i]);
+    }
   };
   // spectra of filter group q; filters past K (a ragged last group) reuse the
   // last filter's spectrum and are not stored
@@ -434,16 +443,18 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
   }
 }
 
-template <int N, int NF, bool POWER, bool REAL, int SMODE, bool STAGE, int WG>
+template <int N, int NF, bool POWER, bool REAL, int SMODE, bool STAGE, int WG, bool FOLD = false>
 __device__ __forceinline__ void forward_range(const void* __restrict__ sv, int64_t Ns, const float2* __restrict__ F,
                                               void* __restrict__ yv, int K, int D, int H,
                                               const float2* __restrict__ twt, int64_t u0, int64_t u1, float2* lds,
-                                              int& par, const Stencil* st = nullptr, int shift_mask = 0) {
+                                              int& par, const Stencil* st = nullptr, int shift_mask = 0,
+                                              const Response* resp = nullptr,
+                                              const float2* __restrict__ root = nullptr) {
   float2 tw[Geo<N>::TWR];
   load_lane_twiddles<N>(tw, twt, threadIdx.x % Geo<N>::G);
   // the stage's accumulators take the registers of the spectrum prefetch
-  forward_units<N, NF, POWER, REAL, SMODE, prefetch_spectra_single<N, NF, POWER, REAL>() && !STAGE, STAGE, WG>(
-      sv, Ns, F, yv, K, D, H, tw, u0, u1, lds, par, st, shift_mask, K);
+  forward_units<N, NF, POWER, REAL, SMODE, prefetch_spectra_single<N, NF, POWER, REAL>() && !STAGE, STAGE, WG,
+                FOLD>(sv, Ns, F, yv, K, D, H, tw, u0, u1, lds, par, st, shift_mask, K, resp, root);
 }
 
 // shift_mask: 0, or the row shift of output rows off the 128-byte line grid
@@ -460,6 +471,26 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ol
   int par = 0;
   forward_range<N, NF, POWER, REAL, STORE_NT_WHOLE, false, WG>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par, nullptr,
                                                                shift_mask);
+}
+
+// The forward kernel with a one-phase stencil folded into the segments'
+// spectra: one filter per unit.  Kernels of their own, because the transfer
+// function's 64 registers would otherwise be every forward kernel's.  The
+// backward difference on 2^23 x 32 x 256: staged like the other stencils 567
+// us, folded 437 (the plain forward 429).
+template <int N, bool POWER, bool REAL, int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_fold_kernel(
+    const void* __restrict__ s, int64_t Ns, const float2* __restrict__ F, void* __restrict__ y, int K, int D, int H,
+    int64_t ntiles, const float2* __restrict__ twt, int shift_mask, const Response resp,
+    const float2* __restrict__ root) {
+  __shared__ float2 lds[forward_lds<Geo<N, WG>, 1, false>()];
+  const int64_t U = ntiles * K;
+  const int64_t u0 = first_unit(U, gridDim.x, blockIdx.x);
+  const int64_t u1 = first_unit(U, gridDim.x, blockIdx.x + 1);
+  if (u0 >= u1) return;  // uniform over the workgroup
+  int par = 0;
+  forward_range<N, 1, POWER, REAL, STORE_NT_WHOLE, false, WG, true>(s, Ns, F, y, K, D, H, twt, u0, u1, lds, par,
+                                                                    nullptr, shift_mask, &resp, root);
 }
 
 // The forward kernel with the non-local post-processing stage (sec. 4): the
@@ -1408,6 +1439,8 @@ struct ols_plan_s {
   bool stencil_on = false;  // non-local stage (ols_plan_set_stencil)
   int stencil_R = 0;        // its reach ahead (taps after the sample)
   Stencil stencil{};
+  // the stage kernel; else a stencil is folded into the segments' spectra (Response)
+  bool staged() const { return stencil_on && (stencil.J > 1 || !fold_stencil(N)); }
   void* bwd_mem = nullptr;  // the adjoint's scratch, allocated by ols_plan_reserve_backward
   BwdWorkspace bwd{};       // carved from bwd_mem for the adjoint's full grid
   float2* spectra = nullptr;
@@ -1503,6 +1536,22 @@ struct Kern {
     }
     return real ? forward_fn_nf<1, true>(wg, power) : forward_fn_nf<1, false>(wg, power);
   }
+  // The forward with a folded one-phase stencil.
+  using FoldFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*, int,
+                          const Response, const float2*);
+  template <bool REAL>
+  static FoldFn fold_fn_real(bool power) {
+    return power ? ols_forward_fold_kernel<N, true, REAL, wide(1, REAL)>
+                 : ols_forward_fold_kernel<N, false, REAL, wide(1, REAL)>;
+  }
+  static FoldFn fold_fn(int flags) {
+    if constexpr (fold_stencil(N)) {
+      const bool power = (flags & OLS_POST_POWER) != 0;
+      return (flags & OLS_REAL) ? fold_fn_real<true>(power) : fold_fn_real<false>(power);
+    } else {
+      return nullptr;
+    }
+  }
   // The same for the kernel with the non-local stencil stage, in workgroups of
   // GE::WG threads (single waves measured 3-5 % slower on long calls at N =
   // 256 and 1024).
@@ -1538,7 +1587,8 @@ struct Kern {
     return (ntrans + segs - 1) / segs * ((p->K + c.nf - 1) / c.nf);
   }
   static Shape call_shape(const ols_plan_s* p, int64_t ntrans) {
-    if (p->stencil_on) return Shape{p->nf, GE::WG};
+    if (p->staged()) return Shape{p->nf, GE::WG};
+    if (p->stencil_on) return Shape{1, wide(1, (p->flags & OLS_REAL) != 0)};  // folded
     Shape c{p->nf, NARROW};
     if constexpr (N == 2048 || N == 4096) {
       // Plans that leave the tiling to the library: one filter per unit, with
@@ -1570,9 +1620,10 @@ struct Kern {
     // output rows off the 128-byte grid read the plan's spectra for each
     // row's delay (the call only reads the plan)
     const bool float_out = (p->flags & (OLS_REAL | OLS_POST_POWER)) != 0;
+    // (a folded stencil needs its reach ahead free of the delay too)
     const RowShift rs = row_shift_geometry(
-        y, Ns, N, p->D, p->H, float_out ? 4 : 8,
-        p->spectra_delays && !p->stencil_on && (int64_t)p->K * Ns >= SHIFT_MIN_OUTPUTS);
+        y, Ns, N - p->stencil_R, p->D, p->H, float_out ? 4 : 8,
+        p->spectra_delays && !p->staged() && (int64_t)p->K * Ns >= SHIFT_MIN_OUTPUTS);
     const float2* F = rs.mask ? p->spectra_delays : p->spectra;
     const int H = rs.H;
     const int64_t nseg = (Ns + H - 1) / H;
@@ -1581,24 +1632,35 @@ struct Kern {
     const int segs = c.wg / GE::G;
     const int64_t ntiles = (ntrans + segs - 1) / segs;
     const int64_t u = units(p, ntrans, c), most = slots(p->grid, c.wg), grid = u < most ? u : most;
-    if (p->stencil_on) {
+    if (p->staged()) {
       // J <= 2 phases go out as one element per sample when y is aligned to it
       Stencil sten = p->stencil;
       const uintptr_t el = (uintptr_t)sten.J * (float_out ? 4 : 8);
       sten.packed = sten.J <= 2 && (uintptr_t)y % el == 0;
       hipLaunchKernelGGL(stencil_fn(c.nf, p->flags), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, p->spectra, y,
                          p->K, p->D, p->H, ntiles, p->twiddles, sten);
+    } else if (p->stencil_on) {
+      Response resp{};
+      resp.T = p->stencil.T;
+      resp.L = p->stencil.L;
+      for (int d = 0; d < resp.T; ++d) resp.w[d] = p->stencil.w[0][d];
+      hipLaunchKernelGGL(fold_fn(p->flags), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, F, y, p->K, p->D, H,
+                         ntiles, p->twiddles, rs.mask, resp, p->roots);
     } else
       hipLaunchKernelGGL(forward_fn(c.nf, p->flags, c.wg), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, F, y,
                          p->K, p->D, H, ntiles, p->twiddles, rs.mask);
     return hipGetLastError();
   }
   // Workgroups of GE::WG threads per CU (or as many threads in smaller ones).
-  static hipError_t occupancy(int nf, int flags, bool stage, int* blocks_per_cu) {
+  // phases: outputs per sample of the stencil, 0 without one.
+  static hipError_t occupancy(int nf, int flags, int phases, int* blocks_per_cu) {
     int n = 0;
-    const int wg = stage ? GE::WG : wide(nf, (flags & OLS_REAL) != 0);
-    const hipError_t e = stage ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_fn(nf, flags), wg, 0)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, forward_fn(nf, flags, wg), wg, 0);
+    const bool fold = phases == 1 && fold_stencil(N), stage = phases > 0 && !fold;
+    const int wg = stage ? GE::WG : wide(fold ? 1 : nf, (flags & OLS_REAL) != 0);
+    const hipError_t e =
+        stage  ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_fn(nf, flags), wg, 0)
+        : fold ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fold_fn(flags), wg, 0)
+               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, forward_fn(nf, flags, wg), wg, 0);
     *blocks_per_cu = n / (GE::WG / wg);
     return e;
   }
@@ -1674,7 +1736,7 @@ struct RunForward {
 };
 template <int N>
 struct RunOccupancy {
-  static hipError_t run(int nf, int flags, bool stage, int* b) { return Kern<N>::occupancy(nf, flags, stage, b); }
+  static hipError_t run(int nf, int flags, int phases, int* b) { return Kern<N>::occupancy(nf, flags, phases, b); }
 };
 template <int N>
 struct RunBwdOccupancy {
@@ -1934,7 +1996,7 @@ ols_status_t ols_plan_ex(ols_plan_t* plan, const void* h, int32_t K, int32_t M, 
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "hipDeviceGetAttribute"); }
     p->nf = (flags & OLS_REAL) ? choose_nf_real(N, K) : choose_nf(N, K);
     int per_cu = 0;
-    e = dispatch<RunOccupancy>(N, p->nf, flags, false, &per_cu);
+    e = dispatch<RunOccupancy>(N, p->nf, flags, 0, &per_cu);
     if (e != hipSuccess) { destroy_plan(p); return hip_fail(e, "occupancy query"); }
     if (per_cu < 1) per_cu = 1;
     p->grid = p->full = per_cu * p->cus;
@@ -2025,7 +2087,7 @@ ols_status_t ols_plan_set_stencil(ols_plan_t p, int32_t J, int32_t L, int32_t R,
     // N = 2048 spill registers and measured 5-15 % slower
     const int nf = J != 0 ? 1 : ((p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K));
     int per_cu = 0;
-    hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, J != 0, &per_cu);
+    hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, (int)J, &per_cu);
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
     if (per_cu < 1) per_cu = 1;
     p->nf = nf;
@@ -2079,7 +2141,7 @@ ols_status_t ols_plan_set_tiling(ols_plan_t p, int32_t nf, int32_t wpc) {
     if (nf_auto) nf = (p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K);
     if (!nf_allowed(p, nf)) return fail(OLS_ERROR_INVALID_VALUE, "filters_per_unit must be 1 or 2 (2 only for N <= 4096, R2R N <= 2048)");
     int per_cu = 0;
-    hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, p->stencil_on, &per_cu);
+    hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, p->stencil_on ? p->stencil.J : 0, &per_cu);
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
     if (per_cu < 1) per_cu = 1;
     if (wpc == 0) wpc = per_cu;
@@ -2100,7 +2162,7 @@ ols_status_t ols_plan_get_tiling(ols_plan_t p, int32_t* nf, int32_t* wpc, int32_
   if (wpc) *wpc = p->grid / p->cus;
   if (max_wpc) {
     int per_cu = 0;
-    hipError_t e = dispatch<RunOccupancy>(p->N, p->nf, p->flags, p->stencil_on, &per_cu);
+    hipError_t e = dispatch<RunOccupancy>(p->N, p->nf, p->flags, p->stencil_on ? p->stencil.J : 0, &per_cu);
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
     *max_wpc = per_cu < 1 ? 1 : per_cu;
   }

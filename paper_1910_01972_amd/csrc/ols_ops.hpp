@@ -440,6 +440,45 @@ struct Stencil {
   float w[STENCIL_MAX_PHASES][STENCIL_MAX_TAPS];  // w[j][d + L]; zero past T and J
 };
 
+// A stencil with one output per sample is a convolution: it multiplies the
+// segment's spectrum by its transfer function
+//     S(k) = sum_d w[d] exp(+2 pi i k d / N),   d = -L .. T-1-L,
+// once per segment instead of staging every filter's output.  Circularly it
+// shifts by up to L back and R ahead, which the kept window leaves room for
+// (stencil_delay), so the outputs are those of the staged stencil, and the
+// power, R2R and row re-alignment apply as to a plain forward.  The function
+// stays in registers for all of a workgroup's segments.  N = 8192 has none left
+// and would gather it for every segment (2^24 samples, one filter: 146 us
+// against 97 staged), so it stages.
+OLS_HD constexpr bool fold_stencil(int N) { return N <= 4096; }
+struct Response {
+  int T;  // taps; 0: no stencil
+  int L;  // taps before the sample
+  float w[STENCIL_MAX_TAPS];
+};
+// S(k) for lane g's frequencies; root[m] = exp(-2 pi i m / N).
+template <int N, class P>
+OLS_HD void stencil_response(float2 (&S)[16], P root, const Response& st, int g) {
+  const int k0 = spectrum_index<N>(g, 0);  // register reg holds frequency k0 + reg * N / 16
+#pragma unroll
+  for (int reg = 0; reg < 16; ++reg) S[reg] = make_float2(0.f, 0.f);
+  for (int t = 0; t < st.T; ++t) {
+    const int d = t - st.L;
+    const float wt = st.w[t];
+    if (d == 0) {  // no load: a short call waits for each tap's gather
+#pragma unroll
+      for (int reg = 0; reg < 16; ++reg) S[reg].x += wt;
+      continue;
+    }
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg) {
+      const float2 z = load_c64(root, ((k0 + reg * (N / 16)) * d) & (N - 1));
+      S[reg].x = fmaf(wt, z.x, S[reg].x);
+      S[reg].y = fmaf(-wt, z.y, S[reg].y);
+    }
+  }
+}
+
 // LDS slots of one staged segment: position p at STENCIL_PAD + p, so every
 // tap of every position of the transform stays inside its own segment slots.
 template <int N>
@@ -606,9 +645,11 @@ OLS_HD void stage_store_packed(const float2* __restrict__ region, const S& st, P
 template <int N, bool POWER, bool REAL, int SMODE = STORE_PLAIN, class S, class P>
 OLS_HD void stage_store(const float2* __restrict__ region, const S& st, P yrow, int64_t Ns, int64_t out0, int D,
                         int H, int g) {
-  if (st.packed && st.J == 1) {
-    stage_store_packed<N, 1, POWER, REAL, SMODE>(region, st, yrow, Ns, out0, D, H, g);
-    return;
+  if constexpr (!fold_stencil(N)) {
+    if (st.packed && st.J == 1) {
+      stage_store_packed<N, 1, POWER, REAL, SMODE>(region, st, yrow, Ns, out0, D, H, g);
+      return;
+    }
   }
   if (st.packed && st.J == 2) {
     stage_store_packed<N, 2, POWER, REAL, SMODE>(region, st, yrow, Ns, out0, D, H, g);
