@@ -405,10 +405,9 @@ struct EmuItem {
   const float2* s;
   float2* y;
   std::vector<float2> F;
-  int64_t Ns, unit_begin, units, tile_begin = 0, ntiles = 0;
+  int64_t Ns, weight_begin = 0, weight = 0, units, tile_begin = 0, ntiles = 0;
   int K, M, N, D, H, nf;
   int shift_mask = 0;
-  int parts = 1;
 };
 
 template <int N>
@@ -696,7 +695,7 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
                     const int* K, const int* M, const int* N, const int* D, const int* H, int grid) {
   using namespace ols::emu;
   std::vector<EmuItem> items(n);
-  int64_t units = 0, tiles = 0;
+  int64_t units = 0, tiles = 0, weight = 0;
   for (int i = 0; i < n; ++i) {
     EmuItem& it = items[i];
     it.s = (const float2*)s[i];
@@ -714,25 +713,48 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
       it.D = D[i];
       it.H = H[i];
     }
-    it.nf = ols::choose_nf_batched(it.N, it.K);
     const int segs = 4096 / it.N;
     const int64_t nseg = (it.Ns + it.H - 1) / it.H;
     it.ntiles = (nseg + segs - 1) / segs;
-    it.units = it.ntiles * ((it.K + it.nf - 1) / it.nf);
+    it.weight = ols::batch_item_weight(it.ntiles, it.K);
+    weight += it.weight;
     if (dispatch<SpecN>(it.N, &it, (const float2*)h[i]) != 0) return 2;
+  }
+  const bool shares = ols::batch_shares(weight, grid);
+  for (EmuItem& it : items) {
+    it.nf = ols::choose_nf_batched(it.N, it.K, shares);
+    it.units = it.ntiles * ((it.K + it.nf - 1) / it.nf);
   }
   // the plan's kernel order: items by class (N, filters per unit), stable
   std::stable_sort(items.begin(), items.end(), [](const EmuItem& u, const EmuItem& v) {
     return u.N != v.N ? u.N < v.N : u.nf < v.nf;
   });
-  int64_t all_tiles = 0;
-  for (const EmuItem& it : items) all_tiles += it.ntiles;
+  int64_t before = 0;
   for (EmuItem& it : items) {
-    it.unit_begin = units;
     units += it.units;
-    it.parts = ols::batch_tile_parts(all_tiles, grid, (it.K + it.nf - 1) / it.nf);
+    it.weight_begin = before;
+    before += it.weight;
     it.tile_begin = tiles;
-    tiles += it.ntiles * it.parts;
+    tiles += it.ntiles;
+  }
+  if (shares) {
+    // equal shares of the weight, each a contiguous run of units
+    auto locate = [&](int64_t v, int* item) {
+      int i = 0;
+      while (i + 1 < n && items[i + 1].weight_begin <= v) ++i;
+      *item = i;
+      return ols::batch_unit_at(v - items[i].weight_begin, items[i].units, items[i].weight);
+    };
+    for (int64_t b = 0; b < grid; ++b) {
+      int i, end;
+      int64_t u = locate(weight * b / grid, &i);
+      const int64_t end_unit = locate(weight * (b + 1) / grid, &end);
+      for (; i < end || (i == end && u < end_unit); ++i, u = 0) {
+        const int64_t u1 = i == end ? end_unit : items[i].units;
+        if (u < u1 && dispatch<RangeN>(items[i].N, &items[i], u, u1) != 0) return 3;
+      }
+    }
+    return 0;
   }
   // the device schedule (first_batch_tile, next_batch_tile,
   // batch_workgroup_order): chunks of tiles dealt round-robin to the grid,
@@ -748,9 +770,10 @@ int ols_emu_batched(int n, const float* const* s, float* const* y, const int64_t
       ++runs;
       for (;;) {
         EmuItem& it = items[i];
-        if (t < it.tile_begin || t >= it.tile_begin + it.ntiles * it.parts) return 4;  // walk invariant
-        const ols::BatchEntry e = ols::batch_entry(t - it.tile_begin, (it.K + it.nf - 1) / it.nf, it.parts);
-        if (dispatch<RangeN>(it.N, &it, e.u0, e.u1) != 0) return 3;
+        if (t < it.tile_begin || t >= it.tile_begin + it.ntiles) return 4;  // walk invariant
+        const int64_t per_tile = it.units / it.ntiles;
+        const int64_t a = (t - it.tile_begin) * per_tile;
+        if (dispatch<RangeN>(it.N, &it, a, a + per_tile) != 0) return 3;
         t = ols::next_batch_tile(t, P);
         if (t >= tiles) break;
         while (i + 1 < n && items[i + 1].tile_begin <= t) ++i;

@@ -524,13 +524,14 @@ struct BatchItem {
   const float2* spectra;  // [K][N] in transform order, scaled by 1/N
   const void* h;          // the caller's filters [K][M] (read by the spectra step)
   int64_t Ns;
-  int64_t unit_begin;
+  int64_t weight_begin;  // weight of the items before this one, and its own (batch_item_weight)
+  int64_t weight;
   int64_t units;
   int32_t K, M, N, D, H, nf;
-  int64_t tile_begin;  // first entry of this item in the batch's tile list
+  int64_t tile_begin;  // first tile of this item in the batch's tile list
   int64_t ntiles;      // tiles of this item (units = ntiles * units per tile)
   int32_t shift_mask;  // rows off the 128-byte grid: filters delayed by row_delay with this mask
-  int32_t parts;       // entries of the tile list each tile is split into (batch_tile_parts)
+  int32_t pad;
 };
 
 // Values the batch setup computes on the device: totals over all items and
@@ -540,8 +541,9 @@ struct BatchHeader {
   int32_t status;       // ols_status_t of the device-side checks
   int32_t bad_item;     // first failing item (caller's numbering), -1 if none
   int32_t n;
-  int32_t pad;
-  int64_t total_tiles;  // entries of the tile list: the tiles of all items, times each item's parts
+  int32_t shares;       // the workgroups take equal shares of the weight (batch_shares), not whole tiles
+  int64_t total_tiles;  // segment tiles of all items
+  int64_t total_weight;
   int64_t total_tasks;  // spectrum tasks (one workgroup's filters of one item)
   int64_t spec_elems;   // complex64 elements of filter spectra the items need
 };
@@ -633,10 +635,10 @@ struct ItemShape {
   int64_t ntiles, units, spec, tasks;
 };
 
-__device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int N) {
+__device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int N, bool shares) {
   ItemShape r;
   r.N = N;
-  r.nf = choose_nf_batched(N, it.K);
+  r.nf = choose_nf_batched(N, it.K, shares);
   r.cls = batch_class(N, r.nf);
   r.D = default_delay(N, it.M);
   const RowShift rs = batch_row_shift(it.y, it.N_s, N, r.D);
@@ -654,8 +656,7 @@ __device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int 
 
 // Workgroup 0 lays out the batch; the others write the twiddle tables at the
 // same time.  A call of few items is bound by this kernel's serial chain: the
-// item loads, three scans and the stores.  grid: workgroups of the forward
-// launch (batch_tile_parts).
+// item loads, three scans and the stores.  grid: workgroups of the forward launch.
 constexpr int SETUP_TWIDDLE_BLOCKS = 32;
 __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ols_batch_item_t* __restrict__ in,
                                                                          BatchLayout L, int grid) {
@@ -682,7 +683,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
   int base[BATCH_CLASSES];
 #pragma unroll
   for (int c = 0; c < BATCH_CLASSES; ++c) base[c] = 0;
-  int64_t tiles[1] = {0};
+  int64_t weight[1] = {0}, total_weight[1];
   for (int i = i0; i < i1; ++i) {
     const ols_batch_item_t it = in[i];
     int N = 0;
@@ -691,10 +692,10 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
       atomicMin(&s_fail, ((unsigned long long)i << 8) | (unsigned)st);
       continue;
     }
-    const ItemShape s = item_shape(it, N);
+    const ItemShape s = item_shape(it, N, false);
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c) base[c] += c == s.cls;
-    tiles[0] += s.ntiles;
+    weight[0] += batch_item_weight(s.ntiles, it.K);
   }
   __syncthreads();
   if (s_fail != ~0ull) {  // uniform: no item is processed
@@ -702,7 +703,9 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
       L.hdr->status = (int32_t)(s_fail & 0xff);
       L.hdr->bad_item = (int32_t)(s_fail >> 8);
       L.hdr->n = n;
+      L.hdr->shares = 0;
       L.hdr->total_tiles = 0;
+      L.hdr->total_weight = 0;
       L.hdr->total_tasks = 0;
       L.hdr->spec_elems = 0;
     }
@@ -711,11 +714,18 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
 
   // 2. stable counting sort by class: exclusive prefix of every class's
   // counts over the threads, then class bases
-  int64_t all_tiles[1];
-  block_exclusive_scan(tiles, sh, all_tiles);
+  block_exclusive_scan(weight, sh, total_weight);
+  const bool shares = batch_shares(total_weight[0], grid);
   {
     int cls_total[BATCH_CLASSES];
     block_exclusive_scan(base, sh_cnt, cls_total);
+    // in shares N = 2048 has no filter pairs: its two classes become one
+    if (shares) {
+      constexpr int one = batch_class(2048, 1), two = batch_class(2048, 2);
+      base[one] += base[two];
+      cls_total[one] += cls_total[two];
+      cls_total[two] = 0;
+    }
     int acc = 0;
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c) {
@@ -727,7 +737,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     const ols_batch_item_t it = in[i];
     int N = 0;
     (void)batch_item_check(it.s, it.N_s, it.h, it.K, it.M, it.N, it.y, &N);
-    const ItemShape sh_ = item_shape(it, N);
+    const ItemShape sh_ = item_shape(it, N, shares);
     int pos = 0;
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c)
@@ -738,7 +748,8 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     b.spectra = nullptr;
     b.h = it.h;
     b.Ns = it.N_s;
-    b.unit_begin = 0;
+    b.weight_begin = 0;
+    b.weight = batch_item_weight(sh_.ntiles, it.K);
     b.units = sh_.units;
     b.K = it.K;
     b.M = it.M;
@@ -746,7 +757,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     b.D = sh_.D;
     b.H = sh_.H;
     b.shift_mask = sh_.shift_mask;
-    b.parts = batch_tile_parts(all_tiles[0], grid, (it.K + sh_.nf - 1) / sh_.nf);
+    b.pad = 0;
     b.nf = sh_.nf;
     b.tile_begin = 0;
     b.ntiles = sh_.ntiles;
@@ -755,12 +766,12 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
   }
   __syncthreads();  // the sorted table is complete (workgroup-scope visibility of global writes)
 
-  // 3. prefix sums in kernel order: tile list, units, spectra, spectrum tasks
+  // 3. prefix sums in kernel order: tile list, weights, spectra, spectrum tasks
   int64_t o[4] = {0, 0, 0, 0}, tot[4];
   for (int p = i0; p < i1; ++p) {
     const BatchItem& b = L.items[p];
-    o[0] += b.ntiles * b.parts;
-    o[1] += b.units;
+    o[0] += b.ntiles;
+    o[1] += b.weight;
     o[2] += (int64_t)b.K * b.N;
     o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
   }
@@ -769,11 +780,11 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
   for (int p = i0; p < i1; ++p) {
     BatchItem& b = L.items[p];
     b.tile_begin = o[0];
-    b.unit_begin = o[1];
+    b.weight_begin = o[1];
     b.spectra = fits ? L.spectra + o[2] : nullptr;
     L.task_begin[p] = o[3];
-    o[0] += b.ntiles * b.parts;
-    o[1] += b.units;
+    o[0] += b.ntiles;
+    o[1] += b.weight;
     o[2] += (int64_t)b.K * b.N;
     o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
   }
@@ -782,7 +793,9 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     L.hdr->status = fits ? 0 : (int32_t)OLS_ERROR_INVALID_VALUE;
     L.hdr->bad_item = -1;
     L.hdr->n = n;
+    L.hdr->shares = shares ? 1 : 0;
     L.hdr->total_tiles = tot[0];
+    L.hdr->total_weight = tot[1];
     L.hdr->total_tasks = tot[3];
     L.hdr->spec_elems = tot[2];
   }
@@ -872,7 +885,8 @@ __device__ __forceinline__ BatchItem read_item(gptr<const BatchItem> items, int 
   r.spectra = wave_uniform_ptr(items[i].spectra);
   r.h = wave_uniform_ptr(items[i].h);
   r.Ns = wave_uniform64(items[i].Ns);
-  r.unit_begin = wave_uniform64(items[i].unit_begin);
+  r.weight_begin = wave_uniform64(items[i].weight_begin);
+  r.weight = wave_uniform64(items[i].weight);
   r.units = wave_uniform64(items[i].units);
   r.K = __builtin_amdgcn_readfirstlane(items[i].K);
   r.M = __builtin_amdgcn_readfirstlane(items[i].M);
@@ -882,41 +896,60 @@ __device__ __forceinline__ BatchItem read_item(gptr<const BatchItem> items, int 
   r.nf = __builtin_amdgcn_readfirstlane(items[i].nf);
   r.tile_begin = wave_uniform64(items[i].tile_begin);
   r.ntiles = wave_uniform64(items[i].ntiles);
-  r.parts = __builtin_amdgcn_readfirstlane(items[i].parts);
   r.shift_mask = __builtin_amdgcn_readfirstlane(items[i].shift_mask);
   return r;
 }
 
-// Where a workgroup's walk over the tiles stands between class runs: its next
-// tile, the item it is in, and the parity of its next LDS exchange buffer
-// (passed by value so that no state goes through the stack).
+// Where a workgroup's walk stands between class runs (passed by value so that
+// no state goes through the stack): its next item and, dealt tiles, its next
+// tile; or, for a share of the weight, its next unit of that item and the
+// position (item, unit) where the share ends.  par: the parity of its next
+// LDS exchange buffer.
 struct BatchWalk {
   int64_t t;
   int i;
   int par;
+  int end_item;      // -1: dealt tiles
+  int64_t end_unit;  // dealt tiles: the number of tiles
+  __device__ __forceinline__ bool done() const {
+    return end_item < 0 ? t >= end_unit : i > end_item || (i == end_item && t >= end_unit);
+  }
 };
 
 template <int N, int NF>
 __device__ __attribute__((noinline)) BatchWalk batched_run(const BatchItem* __restrict__ items_in, int nitems,
-                                                           BatchWalk w, int64_t total_tiles,
-                                                           const float2* __restrict__ twt, float2* lds) {
+                                                           BatchWalk w, const float2* __restrict__ twt,
+                                                           float2* lds) {
   const gptr<const BatchItem> items = to_global(items_in);
-  int64_t t = w.t;
-  int i = w.i, par = w.par;
   const int64_t P = gridDim.x;
   float2 tw[Geo<N>::TWR];
   load_lane_twiddles<N>(tw, to_global(twt), threadIdx.x % Geo<N>::G);
   for (;;) {
-    const BatchItem it = read_item(items, i);
+    const BatchItem it = read_item(items, w.i);
     const int KG = (it.K + NF - 1) / NF;
-    const BatchEntry e = batch_entry(t - it.tile_begin, KG, it.parts);
-    forward_units<N, NF, false, false, STORE_NT_WHOLE>(it.s, it.Ns, it.spectra, it.y, it.K, it.D, it.H, tw, e.u0,
-                                                       e.u1, lds, par, nullptr, it.shift_mask);
-    t = next_batch_tile(t, P);
-    if (t >= total_tiles) return BatchWalk{t, i, par};
-    // t grows, so the item walk only moves forward (items without tiles are skipped)
-    i = find_item<4>(i, nitems, t, [&](int k) { return items[k].tile_begin; });
-    if (items[i].N != N || items[i].nf != NF) return BatchWalk{t, i, par};
+    int64_t u0, u1;
+    if (w.end_item < 0) {
+      u0 = (w.t - it.tile_begin) * KG;
+      u1 = u0 + KG;
+    } else {
+      u0 = w.t;
+      u1 = w.i == w.end_item ? w.end_unit : it.units;
+    }
+    if (u0 < u1)
+      forward_units<N, NF, false, false, STORE_NT_WHOLE>(it.s, it.Ns, it.spectra, it.y, it.K, it.D, it.H, tw, u0, u1,
+                                                         lds, w.par, nullptr, it.shift_mask);
+    // t grows (or the share's items do), so the walk only moves forward (items
+    // without tiles are skipped)
+    if (w.end_item < 0) {
+      w.t = next_batch_tile(w.t, P);
+      if (w.done()) return w;
+      w.i = find_item<4>(w.i, nitems, w.t, [&](int k) { return items[k].tile_begin; });
+    } else {
+      w.t = 0;
+      ++w.i;
+      if (w.done()) return w;
+    }
+    if (items[w.i].N != N || items[w.i].nf != NF) return w;
   }
 }
 
@@ -926,43 +959,59 @@ __device__ __attribute__((noinline)) BatchWalk batched_run(const BatchItem* __re
 
 template <int N>
 __device__ __forceinline__ BatchWalk batched_class(const BatchItem* __restrict__ items, int nitems, BatchWalk w,
-                                                   int64_t total_tiles, const float2* __restrict__ twt, float2* lds) {
+                                                   const float2* __restrict__ twt, float2* lds) {
   if constexpr (N <= BATCH_NF2_MAX_N) {
-    if (to_global(items)[w.i].nf == 2) return batched_run<N, 2>(items, nitems, w, total_tiles, twt, lds);
+    if (to_global(items)[w.i].nf == 2) return batched_run<N, 2>(items, nitems, w, twt, lds);
   }
-  return batched_run<N, 1>(items, nitems, w, total_tiles, twt, lds);
+  return batched_run<N, 1>(items, nitems, w, twt, lds);
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void ols_batched_kernel(BatchLayout L) {
   __shared__ float2 lds[2 * Geo<4096>::LDS];
   static_assert(Geo<256>::LDS == Geo<4096>::LDS && Geo<2048>::LDS == Geo<4096>::LDS, "same LDS footprint");
   if (L.hdr->status != 0) return;
-  const int64_t total_tiles = L.hdr->total_tiles;
   const BatchItem* __restrict__ items = L.items;
   const int nitems = L.n;
-  // Tiles of all items, in the setup's item order, dealt round-robin in
-  // chunks to the workgroups (first_batch_tile, next_batch_tile,
-  // batch_workgroup_order), each tile with all of its filters.  At any moment
-  // the whole grid works on neighbouring tiles of one or two items, so the L2s
-  // keep those items' filter spectra (balanced contiguous unit ranges spread
-  // the grid over all items at once and re-read the spectra from HBM: 19 %
-  // slower on the uneven batch).  The imbalance is at most one chunk per
-  // workgroup.
-  const int64_t P = gridDim.x;
-  BatchWalk w{first_batch_tile(batch_workgroup_order(blockIdx.x, P)), 0, 0};
+  const int64_t P = gridDim.x, b = batch_workgroup_order(blockIdx.x, P);
   const gptr<const BatchItem> gitems = to_global(items);
-  while (w.t < total_tiles) {
-    w.i = find_item<64>(w.i, nitems, w.t, [&](int k) { return gitems[k].tile_begin; });
+  BatchWalk w;
+  w.par = 0;
+  if (L.hdr->shares) {
+    // equal shares of the weight: [W b / P, W (b + 1) / P) as positions (item, unit)
+    const int64_t W = L.hdr->total_weight, w0 = W * b / P, w1 = W * (b + 1) / P;
+    auto begin = [&](int k) { return gitems[k].weight_begin; };
+    auto unit_at = [&](int k, int64_t v) {
+      return wave_uniform64(batch_unit_at(v - gitems[k].weight_begin, gitems[k].units, gitems[k].weight));
+    };
+    w.i = find_item<64>(0, nitems, w0, begin);
+    w.t = unit_at(w.i, w0);
+    w.end_item = find_item<64>(w.i, nitems, w1, begin);
+    w.end_unit = unit_at(w.end_item, w1);
+  } else {
+    // Tiles of all items, in the setup's item order, dealt round-robin to the
+    // workgroups (first_batch_tile, next_batch_tile, batch_workgroup_order),
+    // each tile with all of its filters.  At any moment the whole grid works on
+    // neighbouring tiles of one or two items, so the L2s keep those items'
+    // filter spectra (balanced contiguous unit ranges spread the grid over all
+    // items at once and re-read the spectra from HBM: 19 % slower on the uneven
+    // batch of 256 signals).
+    w.t = first_batch_tile(b);
+    w.i = 0;
+    w.end_item = -1;
+    w.end_unit = L.hdr->total_tiles;
+    if (!w.done()) w.i = find_item<64>(0, nitems, w.t, [&](int k) { return gitems[k].tile_begin; });
+  }
+  while (!w.done()) {
     // items of another class lay out the LDS buffers differently, and
     // single-wave transforms exchange without barriers: every wave must have
     // finished with the previous run's buffers
     __syncthreads();
     switch (gitems[w.i].N) {
-      case 256: w = batched_class<256>(items, nitems, w, total_tiles, L.tw[0], lds); break;
-      case 512: w = batched_class<512>(items, nitems, w, total_tiles, L.tw[1], lds); break;
-      case 1024: w = batched_class<1024>(items, nitems, w, total_tiles, L.tw[2], lds); break;
-      case 2048: w = batched_class<2048>(items, nitems, w, total_tiles, L.tw[3], lds); break;
-      default: w = batched_class<4096>(items, nitems, w, total_tiles, L.tw[4], lds); break;
+      case 256: w = batched_class<256>(items, nitems, w, L.tw[0], lds); break;
+      case 512: w = batched_class<512>(items, nitems, w, L.tw[1], lds); break;
+      case 1024: w = batched_class<1024>(items, nitems, w, L.tw[2], lds); break;
+      case 2048: w = batched_class<2048>(items, nitems, w, L.tw[3], lds); break;
+      default: w = batched_class<4096>(items, nitems, w, L.tw[4], lds); break;
     }
   }
 }

@@ -751,8 +751,13 @@ OLS_HD void store_valid_pair(const float2 (&x)[16], P yrow, int64_t Ns, int64_t 
 constexpr int BATCH_NF2_MAX_N = 2048;
 OLS_HD int choose_nf(int N, int K) { return (N >= 2048 && N <= 4096 && (K % 2 == 0 || K >= 9)) ? 2 : 1; }
 // The batched kernel's registers are set by its largest branch, so one filter
-// per unit saves nothing there and two measured faster at every N <= 2048.
-OLS_HD int choose_nf_batched(int N, int K) { return (N <= BATCH_NF2_MAX_N && (K % 2 == 0 || K >= 9)) ? 2 : 1; }
+// per unit saves nothing there, and two measured faster up to N = 1024 (64
+// uneven signals: 723 against 749 us).  At N = 2048 so too when tiles are dealt
+// whole (513 against 534), but not in shares, where one filter cuts finer (30
+// signals: 42.6 against 43.9; see batch_shares).
+OLS_HD int choose_nf_batched(int N, int K, bool shares) {
+  return (N <= (shares ? 1024 : BATCH_NF2_MAX_N) && (K % 2 == 0 || K >= 9)) ? 2 : 1;
+}
 // R2R (segment pairs) needs a few more registers per transform: two filters
 // per unit only up to N = 2048 as well.
 OLS_HD int choose_nf_real(int N, int K) { return N <= BATCH_NF2_MAX_N ? choose_nf(N, K) : 1; }
@@ -874,7 +879,7 @@ OLS_HD RowShift batch_row_shift(const void* y, int64_t Ns, int N, int D) {
 // class by class (stable within a class), so that each workgroup meets each
 // class in one run of tiles.
 constexpr int BATCH_CLASSES = 10;
-OLS_HD int batch_class(int N, int nf) { return 2 * (ilog2(N) - 8) + (nf - 1); }
+OLS_HD constexpr int batch_class(int N, int nf) { return 2 * (ilog2(N) - 8) + (nf - 1); }
 
 // Schedule of the batched kernel (the device kernel and the host emulator
 // both walk it through these functions).  Tiles of all items, numbered in the
@@ -885,23 +890,23 @@ OLS_HD int batch_class(int N, int nf) { return 2 * (ilog2(N) - 8) + (nf - 1); }
 // 4-18 % slower on the uneven batch.
 OLS_HD int64_t first_batch_tile(int64_t b) { return b; }
 OLS_HD int64_t next_batch_tile(int64_t t, int64_t P) { return t + P; }
-// A batch with fewer tiles than the grid has workgroups splits the filter
-// groups of each tile over several entries of the tile list (every entry
-// transforms its segments again): as many as fill the grid, at most one per
-// group.  Larger batches keep one entry per tile.
-OLS_HD int batch_tile_parts(int64_t tiles, int64_t grid, int groups) {
-  const int64_t p = tiles > 0 ? grid / tiles : 1;
-  return p < 1 ? 1 : (p > groups ? groups : (int)p);
-}
-// Units [u0, u1) of entry e (within its item): part e mod parts of tile e /
-// parts, whose `groups` units are split evenly.
-struct BatchEntry {
-  int64_t u0, u1;
-};
-OLS_HD BatchEntry batch_entry(int64_t e, int groups, int parts) {
-  const int64_t tile = e / parts;
-  const int q = (int)(e - tile * parts);
-  return BatchEntry{tile * groups + (int64_t)groups * q / parts, tile * groups + (int64_t)groups * (q + 1) / parts};
+// Dealing whole tiles suits batches of many tiles per workgroup.  With few,
+// the tiles' uneven cost (one transform of the segments and one per filter)
+// leaves workgroups idle: then workgroup b instead takes the b-th of P equal
+// shares of the batch's weight, contiguous in the kernel's item order, cut at
+// units; a tile cut between workgroups is transformed by each.  Weights count
+// transforms per lane.  Past BATCH_SHARE_WEIGHT transforms per workgroup the
+// spread of the shares over all items costs more spectrum reads than the
+// balance saves.  Measured, us, dealt -> shared, by transforms per workgroup: 6
+// 61 -> 34, 17 116 -> 87, 24 99.5 -> 86, 51 202 -> 168, 73 286 -> 252, 86 308 -> 291,
+// 95 327 -> 373, 193 722 -> 807.
+constexpr int BATCH_SHARE_WEIGHT = 88;
+OLS_HD int64_t batch_item_weight(int64_t ntiles, int K) { return ntiles * (1 + (int64_t)K); }
+OLS_HD bool batch_shares(int64_t total_weight, int64_t P) { return total_weight < BATCH_SHARE_WEIGHT * P; }
+// First unit of an item at or past weight off (0 <= off <= the item's weight;
+// within the shared batches' bounds the product stays small).
+OLS_HD int64_t batch_unit_at(int64_t off, int64_t units, int64_t weight) {
+  return weight > 0 ? off * units / weight : 0;
 }
 // Workgroup index b of launch index blk: the hardware deals workgroups to the
 // 8 XCDs round-robin by launch index, so consecutive b (consecutive chunks of
