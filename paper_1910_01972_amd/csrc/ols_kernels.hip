@@ -1176,6 +1176,138 @@ __device__ __forceinline__ void inv_single(float2 (&x)[16], float2* buf, const f
   }
 }
 
+// ---------------------------------------------------------------------------
+// Adjoint with two filters per unit (N = 4096).  A unit of ols_backward_kernel
+// waits in turn for its gradient window (HBM), its spectrum and its lags (L2 or
+// beyond), and for two exchanges, with two waves per SIMD to cover for each
+// other: 68 % of the VALU's time.  Here the transforms of two filters run side
+// by side: their loads are in flight together and they share each exchange's
+// barriers (2^22 x 16 x 512: adjoint kernel 264 -> 247 us, whole adjoint 282 ->
+// 266; Kern::bwd_duo says when).  A filter index past K (odd K) is transformed
+// like the last filter and then ignored.
+// ---------------------------------------------------------------------------
+// Exchanges of NF transforms, one buffer each.  An inverse's crossing read is
+// followed by a barrier; a forward transform's crossing write must come after
+// one (the caller's, or that of the inverse before it).
+template <class GE, int NF, int E, int KW, int KR>
+__device__ __forceinline__ void exchange_group(float2 (&x)[NF][16], float2* lds, int grp, int g) {
+  static_assert(GE::P <= 3, "one crossing exchange per transform");
+  constexpr int N = GE::N;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) lds_store<N, E, KW>(lds + f * GE::LDS, x[f], grp, g);
+  if constexpr (exchange_local<GE, E>()) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  else __syncthreads();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) lds_load<N, E, KR>(lds + f * GE::LDS, x[f], grp, g);
+  if constexpr (!exchange_local<GE, E>() && KR < KW) __syncthreads();
+  else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+
+template <class GE, int NF, int K>
+__device__ __forceinline__ void fwd_group(float2 (&x)[NF][16], float2* lds, const float2* tw, int grp, int g) {
+#pragma unroll
+  for (int f = 0; f < NF; ++f) run_pass<GE::N, K, false>(x[f], tw + GE::lane_tw_offset(K));
+  if constexpr (K + 1 < GE::P) {
+    exchange_group<GE, NF, K, K, K + 1>(x, lds, grp, g);
+    fwd_group<GE, NF, K + 1>(x, lds, tw, grp, g);
+  }
+}
+
+template <class GE, int NF, int K>
+__device__ __forceinline__ void inv_group(float2 (&x)[NF][16], float2* lds, const float2* tw, int grp, int g) {
+#pragma unroll
+  for (int f = 0; f < NF; ++f) inverse_pass<GE::N, K>(x[f], tw + GE::lane_tw_offset(K));
+  if constexpr (K > 0) {
+    exchange_group<GE, NF, K - 1, K, K - 1>(x, lds, grp, g);
+    inv_group<GE, NF, K - 1>(x, lds, tw, grp, g);
+  }
+}
+
+template <int N>
+__global__ __launch_bounds__(Geo<N>::WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_backward_duo_kernel(
+    const float2* __restrict__ s, const float2* __restrict__ gy, int64_t Ns, const float2* __restrict__ F, int K,
+    int M, int H, int64_t ntiles, const float2* __restrict__ twt, float2* __restrict__ ds,
+    float2* __restrict__ ws_ds, float2* __restrict__ part_dh, int want_ds, int want_dh) {
+  using GE = Geo<N>;
+  static_assert(GE::SEGS == 1, "one segment per workgroup");
+  __shared__ float2 lds[2 * GE::LDS];
+  const int g = threadIdx.x;
+  const int KP = (K + 1) / 2;
+  const int64_t P = gridDim.x, b = blockIdx.x;
+  const int64_t U = ntiles * KP;
+  const int64_t u0 = first_unit(U, P, b), u1 = first_unit(U, P, b + 1);
+  if (u0 >= u1) return;  // uniform over the workgroup
+
+  float2 tw[GE::TWR];
+  load_lane_twiddles<N>(tw, twt, g);
+  float2* part = part_dh + b * (int64_t)K * M;
+  if (want_dh)
+    for (int r = 0; r < K; ++r) zero_lags<N>(part + (int64_t)r * M, M, g);
+
+  const int64_t t_first = u0 / KP;
+  int64_t tile = t_first;
+  int q = (int)(u0 - tile * KP);
+  float2 A[16], acc[16], x[2][16], f[16];
+
+  auto start_tile = [&]() {
+    if (want_dh) {
+      float2 v[1][16];
+      load_window<N, true>(v[0], s, Ns, tile * H, H, g);
+      fwd_group<GE, 1, 0>(v, lds, tw, 0, g);
+      conj_scaled(A, v[0], 1.0f / (float)N);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = make_float2(0.f, 0.f);
+  };
+  auto finish_tile = [&]() {
+    if (!want_ds) return;
+    float2 v[1][16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[0][i] = acc[i];
+    inv_group<GE, 1, GE::P - 1>(v, lds, tw, 0, g);
+    const bool complete = tile * KP >= u0 && (tile + 1) * KP <= u1;
+    // the outputs, or this workgroup's part of them in its slot
+    const int slot = tile == t_first ? 0 : 1;
+    float2* const w = ws_ds + (b * 2 + slot) * (int64_t)N;
+    store_valid<N, STORE_BUFFER>(v[0], complete ? ds : w, complete ? Ns : (int64_t)H, complete ? tile * H : 0, 0, H, g);
+  };
+
+  start_tile();
+  for (int64_t u = u0; u < u1; ++u) {
+    if (q == KP) {
+      finish_tile();
+      q = 0;
+      ++tile;
+      start_tile();
+    }
+    const int r0 = 2 * q, r1 = r0 + 1 < K ? r0 + 1 : r0;
+    load_window<N, true>(x[0], gy + (int64_t)r0 * Ns, Ns, tile * H, N, g);
+    load_window<N, true>(x[1], gy + (int64_t)r1 * Ns, Ns, tile * H, N, g);
+    fwd_group<GE, 2, 0>(x, lds, tw, 0, g);
+    if (want_ds) {
+      load_spectrum<N, true>(f, F, r0, g);
+      acc_conj_product(acc, x[0], f);
+      if (r1 != r0) {
+        load_spectrum<N, true>(f, F, r1, g);
+        acc_conj_product(acc, x[1], f);
+      }
+    }
+    if (want_dh) {
+      product_pass<N>(x[0], A);
+      product_pass<N>(x[1], A);
+      exchange_group<GE, 2, GE::P - 2, GE::P - 1, GE::P - 2>(x, lds, 0, g);
+      inv_group<GE, 2, GE::P - 2>(x, lds, tw, 0, g);
+      add_lags<N, true>(part + (int64_t)r0 * M, x[0], M, g);
+      if (r1 != r0) add_lags<N, true>(part + (int64_t)r1 * M, x[1], M, g);
+    } else {
+      __syncthreads();  // the next unit's forward transforms write every block
+    }
+    ++q;
+  }
+  finish_tile();
+}
+
 // Synchronisation of the hand-over between the two groups of a pair: a fence
 // when the pair shares a wave, a barrier otherwise.
 template <int N>
@@ -1723,21 +1855,31 @@ struct Kern {
   static constexpr int BWD_WG = PAIRED ? BwdGeo<N>::WG : GE::WG;
   using BwdFn = void (*)(const float2*, const float2*, int64_t, const float2*, int, int, int, int64_t, const float2*,
                          float2*, float2*, float2*, int, int);
-  static BwdFn bwd_fn() {
+  static BwdFn bwd_fn(bool duo) {
     if constexpr (PAIRED) return ols_backward_pair_kernel<N>;
+    else if constexpr (N == 4096) return duo ? ols_backward_duo_kernel<N> : ols_backward_kernel<N>;
     else return ols_backward_kernel<N>;
   }
+  // Two filters per unit at N = 4096, where the longest workgroup then has so many
+  // fewer units that their cost, 1.86 times a one-filter unit's, pays: 2^22 x 16
+  // (37 and 19 units) 282 -> 266 us, but 500001 x 7 (2 and 2) 37.8 -> 44.3.
+  static bool bwd_duo(const ols_plan_s* p, int64_t ntiles, int64_t grid) {
+    if constexpr (N != 4096) return false;
+    const int64_t one = (ntiles * p->K + grid - 1) / grid, two = (ntiles * ((p->K + 1) / 2) + grid - 1) / grid;
+    return 15 * two <= 8 * one;
+  }
   static hipError_t bwd_occupancy(int* blocks_per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, bwd_fn(), BWD_WG, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, bwd_fn(false), BWD_WG, 0);
   }
   static hipError_t backward(const ols_plan_s* p, const BwdWorkspace& w, const float2* s, const float2* gy,
                              int64_t Ns, float2* ds, float2* dh, hipStream_t st) {
     const int64_t nseg = (Ns + p->H - 1) / p->H;
     const int64_t ntiles = (nseg + BWD_SEGS - 1) / BWD_SEGS;
-    const int upt = PAIRED ? (p->K + 1) / 2 : p->K;  // units per tile
+    const bool duo = bwd_duo(p, ntiles, w.grid);
+    const int upt = (PAIRED || duo) ? (p->K + 1) / 2 : p->K;  // units per tile
     const int64_t units = ntiles * upt;
     const int64_t grid = units < w.grid ? units : w.grid;
-    hipLaunchKernelGGL(bwd_fn(), dim3((unsigned)grid), dim3(BWD_WG), 0, st, s, gy, Ns, p->spectra, p->K, p->M, p->H,
+    hipLaunchKernelGGL(bwd_fn(duo), dim3((unsigned)grid), dim3(BWD_WG), 0, st, s, gy, Ns, p->spectra, p->K, p->M, p->H,
                        ntiles, p->twiddles, ds, w.ws_ds, w.part_dh, ds ? 1 : 0, dh ? 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

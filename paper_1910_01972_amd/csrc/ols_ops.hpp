@@ -33,6 +33,10 @@ __device__ __forceinline__ float buffer_load_f32(__amdgpu_buffer_rsrc_t rs, int 
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
 }
 
+// Hides how a lane offset was computed, so that the sixteen offsets derived from
+// it are added again at each use instead of held in registers over a loop.
+__device__ __forceinline__ void opaque(int& v) { asm volatile("" : "+v"(v)); }
+
 // Buffer over the elements of window [start, start + len) of an array of n that
 // exist, and the number of the window's elements before the first of them.
 // start is the same in every lane.
@@ -161,10 +165,10 @@ OLS_HD void load_segment_pair(float2 (&x)[16], P __restrict__ s, int64_t Ns, int
 template <int N>
 OLS_HD int spectrum_offset(int reg, int g) { return (((reg >> 1) * Geo<N>::G + g) << 1) + (reg & 1); }
 
-template <int N, class P>
+template <int N, bool LEAN = false, class P>
 OLS_HD void load_spectrum(float2 (&f)[16], P __restrict__ F, int r, int g) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  if constexpr (N == 2048) {
+  if constexpr (N == 2048 || LEAN) {
     // One lane offset and scalar strides instead of eight 64-bit lane
     // addresses: 2^23 x 32 431.5 -> 428.9 us, its power 377 -> 370.5.  At N =
     // 1024 and 4096 level or slower (2^18 x 16, N = 4096: 16.1 -> 17.4).
@@ -222,9 +226,10 @@ OLS_HD void spectrum_product(float2 (&x)[16], const float2 (&A)[16], const float
 // the uneven batch ran 13 % faster with every row on the grid).
 // How a kernel writes its outputs: plain per-lane predicated stores,
 // non-temporal predicated stores, or non-temporal stores for whole granules
-// only (buffer stores when G >= 64, predicated ones otherwise).  Kernels
-// near the register limit keep the cheaper forms.
-enum StoreMode { STORE_PLAIN = 0, STORE_NT = 1, STORE_NT_WHOLE = 2 };
+// only (buffer stores when G >= 64, predicated ones otherwise), or plain stores
+// through a buffer when G >= 64.  Kernels near the register limit keep the
+// cheaper forms.
+enum StoreMode { STORE_PLAIN = 0, STORE_NT = 1, STORE_NT_WHOLE = 2, STORE_BUFFER = 3 };
 
 // P: float* or gptr<float> (float2* or gptr<float2> for the complex form)
 template <int MODE, typename P>
@@ -362,9 +367,9 @@ OLS_HD void store_segment(T* __restrict__ yrow, int64_t Ns, int64_t out0, int D,
   }
 #endif
 #if defined(__HIP_DEVICE_COMPILE__)
-  // the paired adjoint's windows (2^22 x 16: N = 1024 222.5 -> 220, N = 2048 264 ->
-  // 261.5 us; at N = 4096 level, at N = 8192 more spills, 212 -> 217)
-  if constexpr (MODE == STORE_PLAIN && Geo<N>::G >= 64 && N <= 2048) {
+  // the adjoint's windows (2^22 x 16: N = 1024 222.5 -> 220, N = 2048 264 -> 261.5 us;
+  // at N = 8192 more spills, 212 -> 217)
+  if constexpr ((MODE == STORE_BUFFER || (MODE == STORE_PLAIN && N <= 2048)) && Geo<N>::G >= 64) {
     const __amdgpu_buffer_rsrc_t rs =
         make_rsrc(wave_uniform_ptr(yrow + out0), __builtin_amdgcn_readfirstlane(cnt * (int)sizeof(T)));
 #pragma unroll
@@ -680,13 +685,15 @@ OLS_HD void stage_store(const float2* __restrict__ region, const S& st, P yrow, 
 
 // x[reg] = src[start + p] for p = g + time_pos_const(reg) < lim and
 // start + p < N_s (start >= 0); zero elsewhere.
-template <int N>
+template <int N, bool LEAN = false>
 OLS_HD void load_window(float2 (&x)[16], const float2* __restrict__ src, int64_t Ns, int64_t start, int lim, int g) {
 #if defined(__HIP_DEVICE_COMPILE__)
   if constexpr (Geo<N>::G >= 64) {
     const WindowBuffer w = window_buffer(src, start, lim, Ns, 8);
+    int go = g * 8;
+    if constexpr (LEAN) opaque(go);
 #pragma unroll
-    for (int reg = 0; reg < 16; ++reg) x[reg] = buffer_load_c64(w.rs, (g + time_pos_const<N>(reg)) * 8);
+    for (int reg = 0; reg < 16; ++reg) x[reg] = buffer_load_c64(w.rs, go + time_pos_const<N>(reg) * 8);
     return;
   }
 #endif
@@ -714,8 +721,33 @@ OLS_HD void acc_conj_product(float2 (&acc)[16], const float2 (&G)[16], const flo
 // Lags 0 .. M-1 of a time-domain result: part[p] += x[reg] for p < M.  Every
 // lag is always owned by the same lane, so the read-modify-write needs no
 // synchronisation.
-template <int N>
+// LEAN (here, in load_window and load_spectrum): for a kernel without registers
+// for sixteen addresses and masks; through buffers, with offsets made again.
+template <int N, bool LEAN = false>
 OLS_HD void add_lags(float2* __restrict__ part, const float2 (&x)[16], int M, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (LEAN) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(wave_uniform_ptr(part), __builtin_amdgcn_readfirstlane(M * 8));
+    int go = g * 8;
+    opaque(go);
+    float2 old[4];
+#pragma unroll
+    for (int reg = 0; reg < 4; ++reg) old[reg] = buffer_load_c64(rs, go + time_pos_const<N>(reg) * 8);
+#pragma unroll
+    for (int reg = 0; reg < 4; ++reg) buffer_store<0>(cadd(old[reg], x[reg]), rs, go + time_pos_const<N>(reg) * 8);
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+      if (time_pos_const<N>(4 * q) < M) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) old[k] = buffer_load_c64(rs, go + time_pos_const<N>(4 * q + k) * 8);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          buffer_store<0>(cadd(old[k], x[4 * q + k]), rs, go + time_pos_const<N>(4 * q + k) * 8);
+      }
+    }
+    return;
+  }
+#endif
 #pragma unroll
   for (int reg = 0; reg < 16; ++reg) {
     const int p = g + time_pos_const<N>(reg);
