@@ -2002,36 +2002,49 @@ BatchLayout batch_layout(void* ws, size_t bytes, int n) {
   return L;
 }
 
-// Persistent grids of the batch kernels on the current device.
+// Persistent grids of the batch kernels on the current device, asked for once
+// per device (four runtime queries, a few microseconds of every short call).
+constexpr int kMaxDevices = 64;
+struct BatchGrids {
+  std::once_flag once;
+  hipError_t status = hipSuccess;
+  int batched = 0, spectra = 0;
+};
 hipError_t batch_grids(int* batched, int* spectra) {
-  int dev = 0, cus = 0, a = 0, b = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, ols_batched_kernel, 256, 0);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, ols_batch_spectra_kernel, 256, 0);
-  *batched = (a < 1 ? 1 : a) * cus;
-  *spectra = (b < 1 ? 1 : b) * cus;
-  return e;
+  static BatchGrids grids[kMaxDevices];
+  int dev = 0;
+  const hipError_t de = hipGetDevice(&dev);
+  if (de != hipSuccess) return de;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  BatchGrids& g = grids[dev];
+  std::call_once(g.once, [&] {
+    int cus = 0, a = 0, b = 0;
+    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, ols_batched_kernel, 256, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, ols_batch_spectra_kernel, 256, 0);
+    g.batched = (a < 1 ? 1 : a) * cus;
+    g.spectra = (b < 1 ? 1 : b) * cus;
+    g.status = e;
+  });
+  *batched = g.batched;
+  *spectra = g.spectra;
+  return g.status;
 }
 
 // The three launches of a batched call: setup, filter spectra, the persistent
 // forward.  Allocate nothing; capturable.
-hipError_t launch_batch(const ols_batch_item_t* dev_items, const BatchLayout& L, bool forward, hipStream_t st) {
-  int grid = 0, sgrid = 0;
-  hipError_t e = batch_grids(&grid, &sgrid);
+hipError_t launch_batch_setup(const ols_batch_item_t* dev_items, const BatchLayout& L, int grid, int spectra_grid,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(ols_batch_setup_kernel, dim3(1 + SETUP_TWIDDLE_BLOCKS), dim3(SETUP_THREADS), 0, st, dev_items, L,
+                     grid);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (dev_items) {
-    hipLaunchKernelGGL(ols_batch_setup_kernel, dim3(1 + SETUP_TWIDDLE_BLOCKS), dim3(SETUP_THREADS), 0, st, dev_items,
-                       L, grid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(ols_batch_spectra_kernel, dim3(sgrid), dim3(256), 0, st, L);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (forward) {
-    hipLaunchKernelGGL(ols_batched_kernel, dim3(grid), dim3(256), 0, st, L);
-    e = hipGetLastError();
-  }
-  return e;
+  hipLaunchKernelGGL(ols_batch_spectra_kernel, dim3(spectra_grid), dim3(256), 0, st, L);
+  return hipGetLastError();
+}
+hipError_t launch_batch_forward(const BatchLayout& L, int grid, hipStream_t st) {
+  hipLaunchKernelGGL(ols_batched_kernel, dim3(grid), dim3(256), 0, st, L);
+  return hipGetLastError();
 }
 
 bool ranges_overlap(const void* a, size_t an, const void* b, size_t bn) {
@@ -2109,7 +2122,6 @@ static __device__ __align__(256) unsigned char scratch[OLS_STATIC_SCRATCH_BYTES]
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_addr[kMaxDevices] = {};
 
@@ -2525,7 +2537,10 @@ ols_status_t ols_batched(const ols_batch_item_t* dev_items, int32_t n, void* wor
     if (ws_bytes < batch_offsets(n).spec + (size_t)n * OLS_MIN_FFT_LENGTH * sizeof(float2))
       return fail(OLS_ERROR_INVALID_VALUE, "workspace too small for n items");
     const BatchLayout L = batch_layout(workspace, ws_bytes, n);
-    const hipError_t e = launch_batch(dev_items, L, true, (hipStream_t)stream);
+    int grid = 0, sgrid = 0;
+    hipError_t e = batch_grids(&grid, &sgrid);
+    if (e == hipSuccess) e = launch_batch_setup(dev_items, L, grid, sgrid, (hipStream_t)stream);
+    if (e == hipSuccess) e = launch_batch_forward(L, grid, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "batched launch");
     return OLS_SUCCESS;
   } catch (...) {
@@ -2570,7 +2585,7 @@ ols_status_t ols_batch_plan(ols_batch_t* out, const ols_batch_item_t* items, int
     b->L = batch_layout(b->ws, bytes, n);
     if ((e = hipMemcpyAsync(b->dev_items, items, (size_t)n * sizeof(ols_batch_item_t), hipMemcpyHostToDevice, st)) != hipSuccess) { destroy_batch(b); return hip_fail(e, "item upload"); }
     // the same setup and spectra kernels as ols_batched, once
-    if ((e = launch_batch(b->dev_items, b->L, false, st)) != hipSuccess) { destroy_batch(b); return hip_fail(e, "batch setup launch"); }
+    if ((e = launch_batch_setup(b->dev_items, b->L, b->grid, sgrid, st)) != hipSuccess) { destroy_batch(b); return hip_fail(e, "batch setup launch"); }
     BatchHeader hd{};
     b->items_sorted.resize(n);
     b->order.resize(n);
@@ -2601,7 +2616,7 @@ ols_status_t ols_batch_plan(ols_batch_t* out, const ols_batch_item_t* items, int
 ols_status_t ols_batch_run(ols_batch_t b, ols_stream_t stream) {
   try {
     if (!b) return fail(OLS_ERROR_INVALID_VALUE, "batch is NULL");
-    const hipError_t e = launch_batch(nullptr, b->L, true, (hipStream_t)stream);
+    const hipError_t e = launch_batch_forward(b->L, b->grid, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "batched launch");
     return OLS_SUCCESS;
   } catch (...) {
