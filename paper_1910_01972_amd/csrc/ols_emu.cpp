@@ -307,9 +307,6 @@ int backward(const float2* s, int64_t Ns, const float2* gy, const float2* h, int
     const int64_t t_first = u0 / K;
     int64_t tile = t_first;
     int r = (int)(u0 - tile * K);
-    for (int t = 0; t < GE::WG; ++t)
-      for (int rr = 0; rr < K; ++rr)
-        zero_lags<N>(part.data() + ((b * GE::SEGS + t / GE::G) * (int64_t)K + rr) * M, M, t % GE::G);
     auto segof = [&](int t) { return tile * GE::SEGS + t / GE::G; };
     auto start_tile = [&]() {
       for (int t = 0; t < GE::WG; ++t)
@@ -359,9 +356,13 @@ int backward(const float2* s, int64_t Ns, const float2* gy, const float2* h, int
       }
       exchange_phase<N, GE::P - 2, GE::P - 1, GE::P - 2>(xs, G);
       inv_from<N, GE::P - 2>(xs, G, tw);
-      for (int t = 0; t < GE::WG; ++t)
-        add_lags<N>(part.data() + ((b * GE::SEGS + t / GE::G) * (int64_t)K + r) * M,
-                    *reinterpret_cast<float2(*)[16]>(xs[t].data()), M, t % GE::G);
+      for (int t = 0; t < GE::WG; ++t) {
+        float2* lags = part.data() + ((b * GE::SEGS + t / GE::G) * (int64_t)K + r) * M;
+        const float2(&x)[16] = *reinterpret_cast<float2(*)[16]>(xs[t].data());
+        // a workgroup's first K units each store their filter's lags
+        if (u - u0 < K) store_lags<N>(lags, x, M, t % GE::G);
+        else add_lags<N>(lags, x, M, t % GE::G);
+      }
       ++r;
     }
     finish_tile();

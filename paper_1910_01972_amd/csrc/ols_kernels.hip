@@ -1049,8 +1049,6 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_backward_kernel(
   float2 tw[GE::TWR];
   load_lane_twiddles<N>(tw, twt, g);
   float2* part = part_dh + (b * GE::SEGS + grp) * (int64_t)K * M;
-  if (want_dh)
-    for (int r = 0; r < K; ++r) zero_lags<N>(part + (int64_t)r * M, M, g);
 
   const int64_t t_first = u0 / K;
   int64_t tile = t_first;
@@ -1106,7 +1104,9 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_backward_kernel(
       product_pass<N>(x, A);
       exchange<GE, GE::P - 2, GE::P - 1, GE::P - 2>(x, lds, par, grp, g);
       inv_from<GE, GE::P - 2>(x, lds, par, tw, grp, g);
-      add_lags<N>(part + (int64_t)r * M, x, M, g);
+      // each filter's first unit here stores its lags
+      if (u - u0 < K) store_lags<N>(part + (int64_t)r * M, x, M, g);
+      else add_lags<N>(part + (int64_t)r * M, x, M, g);
     }
     ++r;
   }
@@ -1241,8 +1241,6 @@ __global__ __launch_bounds__(Geo<N>::WG) __attribute__((amdgpu_waves_per_eu(2)))
   float2 tw[GE::TWR];
   load_lane_twiddles<N>(tw, twt, g);
   float2* part = part_dh + b * (int64_t)K * M;
-  if (want_dh)
-    for (int r = 0; r < K; ++r) zero_lags<N>(part + (int64_t)r * M, M, g);
 
   const int64_t t_first = u0 / KP;
   int64_t tile = t_first;
@@ -1298,8 +1296,13 @@ __global__ __launch_bounds__(Geo<N>::WG) __attribute__((amdgpu_waves_per_eu(2)))
       product_pass<N>(x[1], A);
       exchange_group<GE, 2, GE::P - 2, GE::P - 1, GE::P - 2>(x, lds, 0, g);
       inv_group<GE, 2, GE::P - 2>(x, lds, tw, 0, g);
-      add_lags<N, true>(part + (int64_t)r0 * M, x[0], M, g);
-      if (r1 != r0) add_lags<N, true>(part + (int64_t)r1 * M, x[1], M, g);
+      if (u - u0 < KP) {
+        store_lags<N, true>(part + (int64_t)r0 * M, x[0], M, g);
+        if (r1 != r0) store_lags<N, true>(part + (int64_t)r1 * M, x[1], M, g);
+      } else {
+        add_lags<N, true>(part + (int64_t)r0 * M, x[0], M, g);
+        if (r1 != r0) add_lags<N, true>(part + (int64_t)r1 * M, x[1], M, g);
+      }
     } else {
       __syncthreads();  // the next unit's forward transforms write every block
     }
@@ -1341,8 +1344,6 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
   float2 tw[GE::TWR];
   load_lane_twiddles<N>(tw, twt, g);
   float2* part = part_dh + (b * BG::SEGS + grp) * (int64_t)K * M;
-  if (want_dh)
-    for (int r = 0; r < K; ++r) zero_lags<N>(part + (int64_t)r * M, M, g);
 
   const int64_t t_first = u0 / KP;
   int64_t tile = t_first;
@@ -1414,7 +1415,10 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
       // from overwriting the hand-over buffer before it has been read
       if constexpr (GE::G == 64) __syncthreads();
       inv_single<N, GE::P - 1>(x, xbuf, tw, grp, g);
-      if (r_own < K) add_lags<N>(part + (int64_t)r_own * M, x, M, g);
+      if (r_own < K) {
+        if (u - u0 < KP) store_lags<N>(part + (int64_t)r_own * M, x, M, g);
+        else add_lags<N>(part + (int64_t)r_own * M, x, M, g);
+      }
     }
     ++q;
   }
@@ -1427,13 +1431,18 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
 // independent; as a launch of their own for the windows and two for the slots
 // they took 12.7 + 6.9 + 5.0 us on the 2^22 x 16 x 512 adjoint and 4.2 + 3.0 +
 // 2.6 us on a 50000 x 4 x 64 one (whole adjoint, graph replays, us: 285.9 -> 282.0
-// and 21.6 -> 16.7; 512 threads 285.0 and 17.5, 1024 289.4 and 19.1; 32 lags per
-// workgroup leave it too few workgroups where K M is small, 2^22 x 16 x 64:
-// 226.9 against 221.3).
+// and 21.6 -> 16.7; 512 threads 285.0 and 17.5, 1024 289.4 and 19.1).
 constexpr int TAIL_THREADS = 256;
-constexpr int TAIL_SPLIT = 8;    // workgroups per tile boundary: at most 4 outputs per lane (H <= 8192)
-constexpr int TAIL_LAGS = 8;    // lags per workgroup of the dh part
-constexpr int TAIL_CHUNKS = TAIL_THREADS / TAIL_LAGS;  // chunks of slots summed at a time
+// Workgroups per tile boundary: at most 4 outputs of a segment per lane; fewer
+// than 4 leave short windows to one workgroup's serial loads (50000 x 4 x 64: 15.7
+// us with 4 or 8, 20.9 with one), 8 mostly repeat the boundary's arithmetic (2^22
+// x 16, N = 1024: 208 against 202).
+constexpr int tail_split(int N) { return N > 4096 ? 8 : 4; }
+// Lags per workgroup of the dh part, and chunks of slots summed at a time: 128
+// bytes of each slot where a workgroup of the adjoint has one slot (2^22 x 16 x
+// 512: 265 -> 259 us against 64 bytes), 64 where it has several (2^18 x 16, N =
+// 1024: 39 against 43).
+constexpr int tail_lags(int segs) { return segs == 1 ? 16 : 8; }
 
 // The boundary between workgroups b-1 and b of the adjoint kernel (the first
 // boundary inside a tile does the whole tile): sums the windows of the sharing
@@ -1455,7 +1464,7 @@ __device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float
   const int64_t slot_lo = first_unit(U, P, blo) / K == t ? 0 : 1;
   for (int sg = 0; sg < SEGS; ++sg) {
     const int64_t o0 = (t * SEGS + sg) * H;
-    for (int p = threadIdx.x + split * TAIL_THREADS; p < H; p += TAIL_SPLIT * TAIL_THREADS) {
+    for (int p = threadIdx.x + split * TAIL_THREADS; p < H; p += tail_split(N) * TAIL_THREADS) {
       if (o0 + p >= Ns) break;
       // the sharing workgroups' windows in workgroup order, loaded four at a
       // time so that the loads overlap
@@ -1489,30 +1498,69 @@ __device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float
   }
 }
 
-// dh[i] for TAIL_LAGS values of i: the slots in chunks of DH_CHUNK, each chunk
+// Which slots hold lags of filter r: those of the workgroups with a unit of it,
+// and of the groups that collect its parity in the paired adjoint.  The others
+// are not written, and a call of few units per workgroup (K filters, one unit
+// each, and K M values per slot) would otherwise spend its time clearing and
+// reading them.
+struct DhSlots {
+  int64_t U, P;  // units and workgroups of the adjoint kernel
+  int upt;       // units per tile
+  int fpu;       // filters per unit
+  int M;
+};
+
+// dh[i] for tail_lags values of i: the slots in chunks of DH_CHUNK, each chunk
 // in slot order by one thread per lag, then the chunk sums in chunk order
-// (TAIL_CHUNKS chunks at a time, handed over through LDS).
-__device__ __forceinline__ void dh_sums(const float2* __restrict__ part, int64_t nslots, int64_t KM,
+// (CHUNKS chunks at a time, handed over through LDS).
+template <int SEGS, bool PAIRED>
+__device__ __forceinline__ void dh_sums(const float2* __restrict__ part, const DhSlots sl, int64_t KM,
                                         float2* __restrict__ dh, int64_t block) {
-  __shared__ float2 sums[TAIL_CHUNKS][TAIL_LAGS];
-  const int lag = threadIdx.x % TAIL_LAGS, row = threadIdx.x / TAIL_LAGS;
-  const int64_t i = block * TAIL_LAGS + lag;
+  static_assert(DH_CHUNK % SEGS == 0, "a chunk holds whole workgroups' slots");
+  constexpr int LAGS = tail_lags(SEGS), CHUNKS = TAIL_THREADS / LAGS;
+  __shared__ float2 sums[CHUNKS][LAGS];
+  const int lag = threadIdx.x % LAGS, row = threadIdx.x / LAGS;
+  const int64_t i = block * LAGS + lag;
+  const int64_t nslots = sl.P * SEGS;
+  const int r = (int)(i / sl.M), q = r / sl.fpu;
+  // workgroups own base or base + 1 consecutive units
+  const int64_t base = sl.U / sl.P, rem = sl.U - base * sl.P;
+  const bool all = base >= sl.upt;  // every workgroup has a unit of every filter
   float2 total = make_float2(0.f, 0.f);
-  for (int64_t c0 = 0; c0 * DH_CHUNK < nslots; c0 += TAIL_CHUNKS) {
+  for (int64_t c0 = 0; c0 * DH_CHUNK < nslots; c0 += CHUNKS) {
     const int64_t s0 = (c0 + row) * DH_CHUNK;
+    int64_t b = s0 / SEGS;
+    // first unit of workgroup b: its place in its tile, and what is left of
+    // the division (carried from one workgroup to the next)
+    const int64_t u0 = first_unit(sl.U, sl.P, b);
+    int64_t left = sl.U * b - u0 * sl.P;
+    int m = (int)(u0 % sl.upt);
+    bool here[DH_CHUNK / SEGS];
+#pragma unroll
+    for (int w = 0; w < DH_CHUNK / SEGS; ++w, ++b) {
+      left += rem;
+      const bool more = left >= sl.P;
+      left -= more ? sl.P : 0;
+      const int len = (int)(base < sl.upt ? base : sl.upt) + (more ? 1 : 0);
+      const int d = q >= m ? q - m : q - m + sl.upt;
+      here[w] = i < KM && b < sl.P && (all || d < len);
+      m += len;
+      m -= m >= sl.upt ? sl.upt : 0;
+    }
     float2 v[DH_CHUNK];
 #pragma unroll
-    for (int k = 0; k < DH_CHUNK; ++k)
-      v[k] = (i < KM && s0 + k < nslots) ? part[(s0 + k) * KM + i] : make_float2(0.f, 0.f);
+    for (int k = 0; k < DH_CHUNK; ++k) {
+      const bool mine = here[k / SEGS] && (!PAIRED || ((k ^ r) & 1) == 0);
+      v[k] = mine ? part[(s0 + k) * KM + i] : make_float2(0.f, 0.f);
+    }
     float2 a = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int k = 0; k < DH_CHUNK; ++k)
-      if (s0 + k < nslots) a = cadd(a, v[k]);
+    for (int k = 0; k < DH_CHUNK; ++k) a = cadd(a, v[k]);
     sums[row][lag] = a;
     __syncthreads();
     if (row == 0) {
-      const int64_t left = dh_chunks(nslots) - c0;
-      const int n = left < TAIL_CHUNKS ? (int)left : TAIL_CHUNKS;
+      const int64_t chunks = dh_chunks(nslots) - c0;
+      const int n = chunks < CHUNKS ? (int)chunks : CHUNKS;
       for (int c = 0; c < n; ++c) total = cadd(total, sums[c][lag]);
     }
     __syncthreads();
@@ -1522,13 +1570,14 @@ __device__ __forceinline__ void dh_sums(const float2* __restrict__ part, int64_t
 
 // Workgroups [0, ndh) sum dh, which takes longer where there are many slots, the
 // others fix ds (either may be absent).
-template <int N, int SEGS>
+template <int N, int SEGS, bool PAIRED>
 __global__ __launch_bounds__(TAIL_THREADS) void ols_backward_tail_kernel(
     const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K, int H, int64_t ntiles, int64_t P,
-    int64_t ndh, const float2* __restrict__ part, int64_t nslots, int64_t KM, float2* __restrict__ dh) {
+    int64_t ndh, const float2* __restrict__ part, const DhSlots sl, int64_t KM, float2* __restrict__ dh) {
   const int64_t blk = blockIdx.x;
-  if (blk < ndh) dh_sums(part, nslots, KM, dh, blk);
-  else ds_fixup<N, SEGS>(ws_ds, ds, Ns, K, H, ntiles, P, (blk - ndh) / TAIL_SPLIT + 1, (int)((blk - ndh) % TAIL_SPLIT));
+  if (blk < ndh) dh_sums<SEGS, PAIRED>(part, sl, KM, dh, blk);
+  else ds_fixup<N, SEGS>(ws_ds, ds, Ns, K, H, ntiles, P, (blk - ndh) / tail_split(N) + 1,
+                         (int)((blk - ndh) % tail_split(N)));
 }
 
 // Plain fill with zero (used instead of a memset so callers may capture it).
@@ -1885,10 +1934,12 @@ struct Kern {
     if (e != hipSuccess) return e;
     // split tiles' windows and the dh slots
     const int64_t KM = (int64_t)p->K * p->M;
-    const int64_t nfix = ds ? (grid - 1) * TAIL_SPLIT : 0, ndh = dh ? (KM + TAIL_LAGS - 1) / TAIL_LAGS : 0;
+    constexpr int LAGS = tail_lags(BWD_SEGS);
+    const int64_t nfix = ds ? (grid - 1) * tail_split(N) : 0, ndh = dh ? (KM + LAGS - 1) / LAGS : 0;
     if (nfix + ndh > 0) {
-      hipLaunchKernelGGL((ols_backward_tail_kernel<N, BWD_SEGS>), dim3((unsigned)(nfix + ndh)), dim3(TAIL_THREADS), 0,
-                         st, w.ws_ds, ds, Ns, upt, p->H, ntiles, grid, ndh, w.part_dh, grid * BWD_SEGS, KM, dh);
+      const DhSlots sl{units, grid, upt, (PAIRED || duo) ? 2 : 1, p->M};
+      hipLaunchKernelGGL((ols_backward_tail_kernel<N, BWD_SEGS, PAIRED>), dim3((unsigned)(nfix + ndh)), dim3(TAIL_THREADS), 0,
+                         st, w.ws_ds, ds, Ns, upt, p->H, ntiles, grid, ndh, w.part_dh, sl, KM, dh);
       e = hipGetLastError();
     }
     return e;
@@ -2006,29 +2057,37 @@ BatchLayout batch_layout(void* ws, size_t bytes, int n) {
 // per device (four runtime queries, a few microseconds of every short call).
 constexpr int kMaxDevices = 64;
 struct BatchGrids {
-  std::once_flag once;
-  hipError_t status = hipSuccess;
+  bool known = false;
   int batched = 0, spectra = 0;
 };
+std::mutex g_grids_mutex;
+BatchGrids g_grids[kMaxDevices];
 hipError_t batch_grids(int* batched, int* spectra) {
-  static BatchGrids grids[kMaxDevices];
   int dev = 0;
-  const hipError_t de = hipGetDevice(&dev);
-  if (de != hipSuccess) return de;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  BatchGrids& g = grids[dev];
-  std::call_once(g.once, [&] {
-    int cus = 0, a = 0, b = 0;
-    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, ols_batched_kernel, 256, 0);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, ols_batch_spectra_kernel, 256, 0);
-    g.batched = (a < 1 ? 1 : a) * cus;
-    g.spectra = (b < 1 ? 1 : b) * cus;
-    g.status = e;
-  });
-  *batched = g.batched;
-  *spectra = g.spectra;
-  return g.status;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool keep = dev >= 0 && dev < kMaxDevices;
+  if (keep) {
+    std::lock_guard<std::mutex> lock(g_grids_mutex);
+    if (g_grids[dev].known) {
+      *batched = g_grids[dev].batched;
+      *spectra = g_grids[dev].spectra;
+      return hipSuccess;
+    }
+  }
+  int cus = 0, a = 0, b = 0;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, ols_batched_kernel, 256, 0);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, ols_batch_spectra_kernel, 256, 0);
+  *batched = (a < 1 ? 1 : a) * cus;
+  *spectra = (b < 1 ? 1 : b) * cus;
+  if (e == hipSuccess && keep) {
+    std::lock_guard<std::mutex> lock(g_grids_mutex);
+    g_grids[dev].batched = *batched;
+    g_grids[dev].spectra = *spectra;
+    g_grids[dev].known = true;
+  }
+  return e;
 }
 
 // The three launches of a batched call: setup, filter spectra, the persistent

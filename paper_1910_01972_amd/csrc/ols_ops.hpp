@@ -755,12 +755,24 @@ OLS_HD void add_lags(float2* __restrict__ part, const float2 (&x)[16], int M, in
   }
 }
 
-template <int N>
-OLS_HD void zero_lags(float2* __restrict__ part, int M, int g) {
+// The same for a workgroup's first unit of a filter: stored, nothing to add to.
+template <int N, bool LEAN = false>
+OLS_HD void store_lags(float2* __restrict__ part, const float2 (&x)[16], int M, int g) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (LEAN) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(wave_uniform_ptr(part), __builtin_amdgcn_readfirstlane(M * 8));
+    int go = g * 8;
+    opaque(go);
+#pragma unroll
+    for (int reg = 0; reg < 16; ++reg)
+      if (time_pos_const<N>(reg) < M) buffer_store<0>(x[reg], rs, go + time_pos_const<N>(reg) * 8);
+    return;
+  }
+#endif
 #pragma unroll
   for (int reg = 0; reg < 16; ++reg) {
     const int p = g + time_pos_const<N>(reg);
-    if (p < M) part[p] = make_float2(0.f, 0.f);
+    if (p < M) part[p] = x[reg];
   }
 }
 
