@@ -83,7 +83,7 @@ __device__ __forceinline__ void exchange_nf(float2 (&x)[NF][16], float2* lds, in
   if constexpr (NF == 1) {
     exchange<GE, E, KW, KR>(x[0], lds, par, grp, g);
   } else {
-    static_assert(GE::P <= 3 && KR < KW, "one crossing exchange of an inverse transform");
+    static_assert(KR < KW, "an inverse transform");
 #pragma unroll
     for (int f = 0; f < NF; ++f) lds_store<N, E, KW>(lds + f * GE::LDS, x[f], grp, g);
     if constexpr (exchange_local<GE, E>()) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -1712,7 +1712,8 @@ bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 template <int N>
 struct Kern {
   using GE = Geo<N>;
-  static constexpr bool HAS_NF2 = N <= 4096;
+  static constexpr bool HAS_NF2 = N <= 4096;       // selectable (ols_plan_set_tiling)
+  static constexpr bool CALL_NF2 = HAS_NF2 || N == 8192;  // for some calls (call_shape)
 
   // the plan's spectra, and its spectra for every row delay if it holds them
   static hipError_t spectra(const ols_plan_s* p, const void* h, hipStream_t st) {
@@ -1757,7 +1758,7 @@ struct Kern {
   }
   static ForwardFn forward_fn(int nf, int flags, int wg) {
     const bool power = (flags & OLS_POST_POWER) != 0, real = (flags & OLS_REAL) != 0;
-    if constexpr (HAS_NF2) {
+    if constexpr (CALL_NF2) {
       if (nf == 2 && !real) return forward_fn_nf<2, false>(wg, power);
       // R2R takes two filters per unit only up to N = 2048 (choose_nf_real)
       if constexpr (N <= BATCH_NF2_MAX_N) {
@@ -1835,6 +1836,14 @@ struct Kern {
         const bool pairs = (u1 > S && units(p, ntrans, c) <= S) || (N == 4096 && u1 >= N4096_NF2_UNITS * S);
         if (!pairs) c.nf = 1;
       }
+    }
+    if constexpr (N == 8192) {
+      // pairs only where they give every workgroup one unit and single filters do
+      // not (2^20 x 2 18.3 -> 14.4 us, 2^18 x 8 17.8 -> 14.4, 2^17 x 16 17.6 ->
+      // 14.5); elsewhere the pair kernel, without prefetched spectra, is 3-30 % slower
+      const int64_t S = slots(p->full, NARROW);
+      const Shape two{2, NARROW};
+      if (p->nf_auto && !(p->flags & OLS_REAL) && units(p, ntrans, c) > S && units(p, ntrans, two) <= S) c = two;
     }
     // 256-thread workgroups, where they pay, from WIDE_UNITS units each on
     // (N = 512, 2^20 x 8: 4.3 units, 20.7 against 20.1 us with 64 threads;

@@ -30,6 +30,7 @@ CASES = [
     (2048, 24, 256, 65536, "real"), (2048, 24, 256, 262147, "real"), (2048, 10, 100, 100003, "power"),
     (2048, 5, 100, 400003, "real power"),
     (4096, 16, 512, 60000, ""), (4096, 16, 512, 131072, ""), (4096, 16, 512, 300001, ""), (4096, 16, 512, 950003, ""),
+    (8192, 8, 2000, 1 << 18, ""), (8192, 3, 2000, 700001, ""), (8192, 9, 1500, 200003, "power"), (8192, 8, 2000, 500001, ""),
 ]
 
 
