@@ -319,9 +319,10 @@ ols_status_t ols_batched_workspace_size(const ols_batch_item_t* host_items, int3
  * ols_batched -- y_i = s_i * h_i,r for every item i and filter r (eq. 1, zero
  * history), all items in one call.  Enqueues three kernels on `stream` and
  * allocates nothing, so the call can be captured in a hipGraph and replayed:
- *   1. setup (one workgroup): reads the DEVICE item array, repeats the item
+ *   1. setup: one workgroup reads the DEVICE item array, repeats the item
  *      checks, chooses each N, orders the items by (N, filters per unit) and
- *      lays out the tile list and the spectra in the workspace;
+ *      lays out the tile list and the spectra in the workspace, while others
+ *      write the twiddle tables there;
  *   2. the filter spectra of every item, FFT_N(pad h)/N, into the workspace
  *      (so a replay sees the filters' current values); an item whose output
  *      rows are off the 128-byte grid gets each filter delayed by its row's
@@ -416,9 +417,8 @@ ols_status_t ols_plan_get_launch(ols_plan_t plan, int32_t* grid, int32_t* block,
  * (segments per workgroup = number of segments / grid).
  *   filters_per_unit   1 or 2 inverse transforms interleaved per unit
  *                      (2 only for N <= 4096, and N <= 2048 for R2R);
- *                      0 restores the library's choice: the most filters a
- *                      unit may take is reported, each call takes what its
- *                      size needs
+ *                      0 restores the library's choice: one value is
+ *                      reported, each call takes what its size needs
  *   workgroups_per_cu  1 .. the kernel's occupancy; 0 = the occupancy
  * The workgroup count leaves the output bit-identical; the filters-per-unit
  * choice selects another kernel instance, whose results may differ in the

@@ -512,11 +512,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ol
 // Batched forward: many signals, each with its own filters (K_i, M_i), FFT
 // length N_i in {256, ..., 4096} and hop, in one persistent launch.  The
 // items' segment tiles are numbered consecutively (item i owns tiles
-// [tile_begin_i, tile_begin_i + ntiles_i)) and dealt round-robin to the
-// workgroups; for each tile a workgroup switches on its item's (N, filters
-// per unit) to the same range body as the single-signal kernel, over all of
-// the tile's units.  Every N <= 4096 uses 256 threads and the same LDS
-// footprint, so one launch covers them all.
+// [tile_begin_i, tile_begin_i + ntiles_i)); the workgroups take whole tiles
+// round-robin, or equal shares of the units where tiles are few
+// (batch_shares), switching on the item's (N, filters per unit) to the same
+// range body as the single-signal kernel.  Every N <= 4096 uses 256 threads
+// and the same LDS footprint, so one launch covers them all.
 // ---------------------------------------------------------------------------
 struct BatchItem {
   const float2* s;
@@ -635,11 +635,16 @@ struct ItemShape {
   int64_t ntiles, units, spec, tasks;
 };
 
+// The fields that follow from how the workgroups divide the batch.
+__device__ __forceinline__ void shape_units(ItemShape& r, int K, bool shares) {
+  r.nf = choose_nf_batched(r.N, K, shares);
+  r.cls = batch_class(r.N, r.nf);
+  r.units = r.ntiles * ((K + r.nf - 1) / r.nf);
+}
+
 __device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int N, bool shares) {
   ItemShape r;
   r.N = N;
-  r.nf = choose_nf_batched(N, it.K, shares);
-  r.cls = batch_class(N, r.nf);
   r.D = default_delay(N, it.M);
   const RowShift rs = batch_row_shift(it.y, it.N_s, N, r.D);
   r.shift_mask = rs.mask;
@@ -648,20 +653,49 @@ __device__ __forceinline__ ItemShape item_shape(const ols_batch_item_t& it, int 
   const int segs = 4096 / N;  // transforms per 256-thread workgroup
   const int64_t nseg = (it.N_s + H - 1) / H;
   r.ntiles = (nseg + segs - 1) / segs;
-  r.units = r.ntiles * ((it.K + r.nf - 1) / r.nf);
+  shape_units(r, it.K, shares);
   r.spec = (int64_t)it.K * N;
   r.tasks = (it.K + segs - 1) / segs;
   return r;
 }
 
+__device__ __forceinline__ BatchItem batch_item(const ols_batch_item_t& it, const ItemShape& sh) {
+  BatchItem b;
+  b.s = (const float2*)it.s;
+  b.y = (float2*)it.y;
+  b.spectra = nullptr;
+  b.h = it.h;
+  b.Ns = it.N_s;
+  b.weight_begin = 0;
+  b.weight = batch_item_weight(sh.ntiles, it.K);
+  b.units = sh.units;
+  b.K = it.K;
+  b.M = it.M;
+  b.N = sh.N;
+  b.D = sh.D;
+  b.H = sh.H;
+  b.shift_mask = sh.shift_mask;
+  b.pad = 0;
+  b.nf = sh.nf;
+  b.tile_begin = 0;
+  b.ntiles = sh.ntiles;
+  return b;
+}
+
 // Workgroup 0 lays out the batch; the others write the twiddle tables at the
 // same time.  A call of few items is bound by this kernel's serial chain: the
-// item loads, three scans and the stores.  grid: workgroups of the forward launch.
+// item loads, the checks, three scans and the stores.  Up to SETUP_THREADS
+// items, one per thread, it is kept short: an item is read and checked once and
+// stays in its thread's registers, and the sums in kernel order go through LDS,
+// where more items go through the workspace (calls of 24 items 34.3 -> 32.1 us,
+// of 2 27.1 -> 25.0, graph replays).
+// grid: workgroups of the forward launch.
 constexpr int SETUP_TWIDDLE_BLOCKS = 32;
 __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ols_batch_item_t* __restrict__ in,
                                                                          BatchLayout L, int grid) {
   __shared__ int sh_cnt[BATCH_CLASSES * SETUP_WAVES];
   __shared__ int64_t sh[4 * SETUP_WAVES];
+  __shared__ int64_t sorted[4][SETUP_THREADS];
   __shared__ unsigned long long s_fail;
   const int t = threadIdx.x, n = L.n;
   if (blockIdx.x > 0) {
@@ -684,15 +718,17 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
 #pragma unroll
   for (int c = 0; c < BATCH_CLASSES; ++c) base[c] = 0;
   int64_t weight[1] = {0}, total_weight[1];
+  ols_batch_item_t it{};
+  ItemShape s{};
   for (int i = i0; i < i1; ++i) {
-    const ols_batch_item_t it = in[i];
+    it = in[i];
     int N = 0;
     const int st = batch_item_check(it.s, it.N_s, it.h, it.K, it.M, it.N, it.y, &N);
     if (st != 0) {
       atomicMin(&s_fail, ((unsigned long long)i << 8) | (unsigned)st);
       continue;
     }
-    const ItemShape s = item_shape(it, N, false);
+    s = item_shape(it, N, false);
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c) base[c] += c == s.cls;
     weight[0] += batch_item_weight(s.ntiles, it.K);
@@ -733,60 +769,77 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
       acc += cls_total[c];
     }
   }
-  for (int i = i0; i < i1; ++i) {
-    const ols_batch_item_t it = in[i];
-    int N = 0;
-    (void)batch_item_check(it.s, it.N_s, it.h, it.K, it.M, it.N, it.y, &N);
-    const ItemShape sh_ = item_shape(it, N, shares);
+  auto position = [&](int cls) {
     int pos = 0;
 #pragma unroll
     for (int c = 0; c < BATCH_CLASSES; ++c)
-      if (c == sh_.cls) pos = base[c]++;
-    BatchItem b;
-    b.s = (const float2*)it.s;
-    b.y = (float2*)it.y;
-    b.spectra = nullptr;
-    b.h = it.h;
-    b.Ns = it.N_s;
-    b.weight_begin = 0;
-    b.weight = batch_item_weight(sh_.ntiles, it.K);
-    b.units = sh_.units;
-    b.K = it.K;
-    b.M = it.M;
-    b.N = N;
-    b.D = sh_.D;
-    b.H = sh_.H;
-    b.shift_mask = sh_.shift_mask;
-    b.pad = 0;
-    b.nf = sh_.nf;
-    b.tile_begin = 0;
-    b.ntiles = sh_.ntiles;
-    L.items[pos] = b;
-    L.order[pos] = i;
-  }
-  __syncthreads();  // the sorted table is complete (workgroup-scope visibility of global writes)
+      if (c == cls) pos = base[c]++;
+    return pos;
+  };
 
   // 3. prefix sums in kernel order: tile list, weights, spectra, spectrum tasks
   int64_t o[4] = {0, 0, 0, 0}, tot[4];
-  for (int p = i0; p < i1; ++p) {
-    const BatchItem& b = L.items[p];
-    o[0] += b.ntiles;
-    o[1] += b.weight;
-    o[2] += (int64_t)b.K * b.N;
-    o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
-  }
-  block_exclusive_scan(o, sh, tot);
-  const bool fits = tot[2] <= L.spec_capacity;
-  for (int p = i0; p < i1; ++p) {
-    BatchItem& b = L.items[p];
-    b.tile_begin = o[0];
-    b.weight_begin = o[1];
-    b.spectra = fits ? L.spectra + o[2] : nullptr;
-    L.task_begin[p] = o[3];
-    o[0] += b.ntiles;
-    o[1] += b.weight;
-    o[2] += (int64_t)b.K * b.N;
-    o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
+  bool fits;
+  if (chunk == 1) {
+    int pos = 0;
+    if (t < n) {
+      shape_units(s, it.K, shares);
+      pos = position(s.cls);
+      sorted[0][pos] = s.ntiles;
+      sorted[1][pos] = batch_item_weight(s.ntiles, it.K);
+      sorted[2][pos] = s.spec;
+      sorted[3][pos] = s.tasks;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = t < n ? sorted[k][t] : 0;
+    block_exclusive_scan(o, sh, tot);
+    fits = tot[2] <= L.spec_capacity;
+    if (t < n) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sorted[k][t] = o[k];
+      L.task_begin[t] = o[3];
+    }
+    __syncthreads();
+    if (t < n) {
+      BatchItem b = batch_item(it, s);
+      b.tile_begin = sorted[0][pos];
+      b.weight_begin = sorted[1][pos];
+      b.spectra = fits ? L.spectra + sorted[2][pos] : nullptr;
+      L.items[pos] = b;
+      L.order[pos] = t;
+    }
+  } else {
+    for (int i = i0; i < i1; ++i) {
+      it = in[i];
+      int N = 0;
+      (void)batch_item_check(it.s, it.N_s, it.h, it.K, it.M, it.N, it.y, &N);
+      s = item_shape(it, N, shares);
+      const int pos = position(s.cls);
+      L.items[pos] = batch_item(it, s);
+      L.order[pos] = i;
+    }
+    __syncthreads();  // the sorted table is complete (workgroup-scope visibility of global writes)
+    for (int p = i0; p < i1; ++p) {
+      const BatchItem& b = L.items[p];
+      o[0] += b.ntiles;
+      o[1] += b.weight;
+      o[2] += (int64_t)b.K * b.N;
+      o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
+    }
+    block_exclusive_scan(o, sh, tot);
+    fits = tot[2] <= L.spec_capacity;
+    for (int p = i0; p < i1; ++p) {
+      BatchItem& b = L.items[p];
+      b.tile_begin = o[0];
+      b.weight_begin = o[1];
+      b.spectra = fits ? L.spectra + o[2] : nullptr;
+      L.task_begin[p] = o[3];
+      o[0] += b.ntiles;
+      o[1] += b.weight;
+      o[2] += (int64_t)b.K * b.N;
+      o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
+    }
   }
   if (t == 0) {
     L.task_begin[n] = tot[3];
@@ -854,26 +907,19 @@ __global__ __launch_bounds__(256) void ols_batch_spectra_kernel(BatchLayout L) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched forward: many signals, each with its own filters (K_i, M_i), FFT
-// length N_i in {256, ..., 4096} and hop, in one persistent launch.  The
-// items' segment tiles are numbered consecutively (item i owns tiles
-// [tile_begin_i, tile_begin_i + ntiles_i)) and dealt round-robin to the
-// workgroups; for each tile a workgroup switches on its item's (N, filters
-// per unit) to the same range body as the single-signal kernel, over all of
-// the tile's units.  Every N <= 4096 uses 256 threads and the same LDS
-// footprint, so one launch covers them all.
+// Batched forward: the persistent kernel and its bodies.
 // ---------------------------------------------------------------------------
 
 // Each (N, filters per unit) body is its own non-inlined function, so its
 // registers are allocated on their own and the kernel needs only the
 // maximum, not the sum, over the branches it may take.  A body runs the
-// workgroup's tiles t, t + P, t + 2P, ... for as long as their items keep its
-// (N, filters per unit): the lane twiddles are loaded once per run, and
-// consecutive tiles of one class need no barrier between them (the same
-// exchange protocol as consecutive tiles of the single-signal kernel).  The
-// setup orders the items by class, so a workgroup meets each class in one
-// run.  Returns the workgroup's first tile of another class (or past the
-// end); i follows the item walk.
+// workgroup's tiles t, t + P, t + 2P, ..., or the units of its share, for as
+// long as their items keep its (N, filters per unit): the lane twiddles are
+// loaded once per run, and consecutive tiles of one class need no barrier
+// between them (the same exchange protocol as consecutive tiles of the
+// single-signal kernel).  The setup orders the items by class, so a workgroup
+// meets each class in one run.  Returns the walk at the first item of another
+// class (or past the end).
 // The fields of one item, read through a global pointer (see gptr).  The
 // whole workgroup works on one item at a time (i is uniform), so the fields
 // are declared wave-uniform: address arithmetic stays scalar and the store
@@ -1027,9 +1073,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void o
 //   dh_r     += first M lags of IFFT(conj(S_j)/N * G_r), S_j = FFT(s[jH .. jH+H-1])
 // Units are (tile, filter) with the filter inner, split into balanced ranges.
 // A tile whose filters are split between workgroups leaves partial ds windows
-// in ws_ds (slot 0 for a range's first tile, 1 for its last); a fixup kernel
-// adds them in workgroup order.  dh lags accumulate in each workgroup's own
-// slot of part_dh ([grid][SEGS][K][M]) and are reduced in a fixed order.
+// in ws_ds (slot 0 for a range's first tile, 1 for its last).  dh lags
+// accumulate in each workgroup's own slot of part_dh ([grid][SEGS][K][M]).
+// ols_backward_tail_kernel adds the windows in workgroup order and the slots
+// that hold a filter's lags in a fixed order.
 // Nothing is atomic, so the result is deterministic.
 // ---------------------------------------------------------------------------
 template <int N>

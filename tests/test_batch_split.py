@@ -71,7 +71,7 @@ def test_shared_and_dealt(log2_ns, K):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [1, 5, 64, 65, 257, 600])
+@pytest.mark.parametrize("n", [1, 5, 64, 65, 256, 257, 600])
 def test_item_counts(n):
     torch = pytest.importorskip("torch")
     from paper_1910_01972_amd import ols
