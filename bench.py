@@ -644,7 +644,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": rec["kernel"] if rec else f"ols_forward_kernel<{info['N']}>",
+            "kernel": prof["kernel"] if prof else f"ols_forward_kernel<{info['N']}>",
             "kernel_ms": kernel_ms,
             "launch_ms": launch_spread(launch_ms),
             "alg_bytes_per_launch": alg_bytes,
