@@ -275,6 +275,21 @@ constexpr int forward_lds() {
   return forward_bufs<GE, NF>() * GE::LDS + ((STAGE && GE::G <= 64) ? GE::SEGS * stage_stride<GE::N>() : 0);
 }
 
+// Waves in step.  A call that writes as fast as the HBM takes it (segments of
+// few aliased samples, or a stage of two phases) is 5-10 % faster when the
+// waves of a workgroup store together: apart, their 512-byte pieces of two
+// neighbouring segments arrive at different times, and the launch falls into a
+// slower state of the write stream.  One barrier per unit keeps them together:
+// in complex forwards whose workgroups hold several transforms of more than a
+// wave (call_shape says when), 2^22 x 32 x 64, N = 2048: 227 -> 208 us, and in
+// the staged kernels up to N = 4096 (two phases, us, N = 2048, 2^23 x 32 x 256:
+// 817 -> 771; N = 4096, 2^23 x 32 x 500: 838 -> 807; at N = 8192 slower, 136 ->
+// 144).  Not in the batched bodies (WG = 0).
+template <class GE, int NF, bool POWER, bool REAL, int WG>
+constexpr bool step_forward() { return NF == 1 && !POWER && !REAL && GE::G > 64 && WG > GE::G; }
+template <class GE>
+constexpr bool step_stage() { return GE::G > 64 && GE::N <= 4096; }
+
 // FOLD: the segments' spectra are multiplied by a one-phase stencil's transfer
 // function (apply_response).
 // STAGE: the outputs go through the non-local stencil stage (st) instead of
@@ -415,6 +430,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
         seg = segment_of(w.tile);
         transform_segment(nxt[0], seg);
       }
+      if constexpr (step_forward<GE, NF, POWER, REAL, WG>()) __syncthreads();
       inverse_of_products<GE, NF>(cur, A, lds, par, tw, grp, g);
       if (u + 1 < u1) load_group(nxt, w.next_group(KG));
       __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of the stores
@@ -436,6 +452,10 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
         transform_segment(xa[0], seg);
       }
       load_group(xa, w.rg);
+      if constexpr (STAGE && step_stage<GE>()) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the spectra, and the previous unit's stores
+        __syncthreads();
+      }
       inverse_of_products<GE, NF>(xa, A, lds, par, tw, grp, g);
       store_group(xa, w.rg, seg);
       w.leave();
@@ -1807,6 +1827,9 @@ struct Kern {
     const bool power = (flags & OLS_POST_POWER) != 0, real = (flags & OLS_REAL) != 0;
     if constexpr (CALL_NF2) {
       if (nf == 2 && !real) return forward_fn_nf<2, false>(wg, power);
+      if constexpr (N == 2048) {
+        if (wg == GE::WG && !real && !power) return ols_forward_kernel<N, 1, false, false, GE::WG>;
+      }
       // R2R takes two filters per unit only up to N = 2048 (choose_nf_real)
       if constexpr (N <= BATCH_NF2_MAX_N) {
         if (nf == 2) return forward_fn_nf<2, true>(wg, power);
@@ -1864,7 +1887,8 @@ struct Kern {
     const int segs = c.wg / GE::G;
     return (ntrans + segs - 1) / segs * ((p->K + c.nf - 1) / c.nf);
   }
-  static Shape call_shape(const ols_plan_s* p, int64_t ntrans) {
+  // on_grid: the output rows need no delayed filters.
+  static Shape call_shape(const ols_plan_s* p, int64_t ntrans, bool on_grid) {
     if (p->staged()) return Shape{p->nf, GE::WG};
     if (p->stencil_on) return Shape{1, wide(1, (p->flags & OLS_REAL) != 0)};  // folded
     Shape c{p->nf, NARROW};
@@ -1900,6 +1924,22 @@ struct Kern {
     constexpr int WIDE_UNITS = N <= 512 ? 8 : 4;
     const Shape w{c.nf, wide(c.nf, (p->flags & OLS_REAL) != 0)};
     if (w.wg != NARROW && units(p, ntrans, w) >= WIDE_UNITS * slots(p->full, w.wg)) c = w;
+    if constexpr (N == 2048) {
+      // Banks of many short filters, which write as fast as the HBM takes it: two
+      // segments per workgroup, their waves in step (step_forward).  us, 128 -> 256
+      // threads: 2^22 x 32 x 64 227 -> 208, 2^23 x 32 x 32 439 -> 416, 3000000 x 32 x
+      // 112 171 -> 158, 2^19 x 32 x 32 35.0 -> 32.8.  Other calls are bound by the
+      // transforms as well and keep the narrow ones: from 128 aliased samples on
+      // (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444), fewer filters
+      // (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113 against 120), rows off
+      // the 128-byte grid (2^23 + 1, x 32 x 64: 485 against 492), and few units per
+      // workgroup (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5).
+      constexpr int STEP_FILTERS = 24, STEP_ALIASED = 128, STEP_UNITS = 6;
+      const Shape step{1, GE::WG};
+      if (c.nf == 1 && !(p->flags & (OLS_REAL | OLS_POST_POWER)) && on_grid && p->K >= STEP_FILTERS &&
+          N - p->H < STEP_ALIASED && units(p, ntrans, step) >= STEP_UNITS * slots(p->full, step.wg))
+        c = step;
+    }
     return c;
   }
   static hipError_t forward(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
@@ -1914,7 +1954,7 @@ struct Kern {
     const int H = rs.H;
     const int64_t nseg = (Ns + H - 1) / H;
     const int64_t ntrans = (p->flags & OLS_REAL) ? (nseg + 1) / 2 : nseg;  // R2R: segment pairs
-    const Shape c = call_shape(p, ntrans);
+    const Shape c = call_shape(p, ntrans, rs.mask == 0);
     const int segs = c.wg / GE::G;
     const int64_t ntiles = (ntrans + segs - 1) / segs;
     const int64_t u = units(p, ntrans, c), most = slots(p->grid, c.wg), grid = u < most ? u : most;

@@ -27,6 +27,7 @@ CASES = [
     (512, 8, 32, 40001, ""), (512, 8, 32, 2200000, ""), (512, 9, 32, 300001, "power"),
     (1024, 5, 64, 962, ""), (1024, 16, 64, 300000, ""), (1024, 8, 30, 300001, "real"), (1024, 8, 30, 2300001, "real"),
     (2048, 32, 256, 50000, ""), (2048, 32, 256, 65536, ""), (2048, 32, 256, 131073, ""), (2048, 9, 300, 600001, ""),
+    (2048, 24, 64, 524288, ""), (2048, 25, 100, 600016, ""), (2048, 24, 64, 262144, ""), (2048, 32, 20, 400001, ""),
     (2048, 24, 256, 65536, "real"), (2048, 24, 256, 262147, "real"), (2048, 10, 100, 100003, "power"),
     (2048, 5, 100, 400003, "real power"),
     (4096, 16, 512, 60000, ""), (4096, 16, 512, 131072, ""), (4096, 16, 512, 300001, ""), (4096, 16, 512, 950003, ""),
