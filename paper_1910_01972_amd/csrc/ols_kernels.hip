@@ -283,12 +283,15 @@ constexpr int forward_lds() {
 // in complex forwards whose workgroups hold several transforms of more than a
 // wave (call_shape says when), 2^22 x 32 x 64, N = 2048: 227 -> 208 us, and in
 // the staged kernels up to N = 4096 (two phases, us, N = 2048, 2^23 x 32 x 256:
-// 817 -> 771; N = 4096, 2^23 x 32 x 500: 838 -> 807; at N = 8192 slower, 136 ->
-// 144).  Not in the batched bodies (WG = 0).
+// 817 -> 771; N = 4096, 2^23 x 32 x 500: 838 -> 807; R2R, N = 2048, 2^22 x 32 x
+// 100: 231 -> 218).  Not where the transforms and taps bind more than the stores:
+// with the power (half the bytes; 2^23 x 32 x 256 675 against 692, 700304 x 33 x
+// 30 59.4 against 63.0), R2R at N = 4096 (112.0 against 114.7), at N = 8192 (136
+// against 144), and not in the batched bodies (WG = 0).
 template <class GE, int NF, bool POWER, bool REAL, int WG>
 constexpr bool step_forward() { return NF == 1 && !POWER && !REAL && GE::G > 64 && WG > GE::G; }
-template <class GE>
-constexpr bool step_stage() { return GE::G > 64 && GE::N <= 4096; }
+template <class GE, bool POWER, bool REAL>
+constexpr bool step_stage() { return GE::G > 64 && !POWER && GE::N <= (REAL ? 2048 : 4096); }
 
 // FOLD: the segments' spectra are multiplied by a one-phase stencil's transfer
 // function (apply_response).
@@ -452,7 +455,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
         transform_segment(xa[0], seg);
       }
       load_group(xa, w.rg);
-      if constexpr (STAGE && step_stage<GE>()) {
+      if constexpr (STAGE && step_stage<GE, POWER, REAL>()) {
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the spectra, and the previous unit's stores
         __syncthreads();
       }
