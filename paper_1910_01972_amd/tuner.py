@@ -9,8 +9,10 @@ times the forward kernel on a synthetic signal and keeps the fastest; then,
 for that N, it times the tilings of the forward kernel -- filters per work
 unit (1 or 2 interleaved inverse transforms) and persistent workgroups per
 compute unit, which sets the number of consecutive segments each workgroup
-owns -- and keeps the fastest.  Results are cached in a JSON file keyed by the
-GPU's architecture name, M and K.
+owns -- and keeps the fastest, the library's own tiling among them.  That one
+is no fixed setting (each call takes the filters per unit that its size needs),
+so it is timed and cached as itself, and a plan for which it won keeps it.
+Results are cached in a JSON file keyed by the GPU's architecture name, M and K.
 
     python -m paper_1910_01972_amd.tuner --M 512 --K 8          # tune one cell
     python -m paper_1910_01972_amd.tuner --sweep                # the 12-cell sweep on 2^25 samples
@@ -87,9 +89,11 @@ def tilings(plan) -> list:
 
 def tune(M: int, K: int, Ns: int = 1 << 22, reps: int = 10, candidates=CANDIDATES, max_n: int = 8192,
          data=None, tile: bool = True) -> dict:
-    """Time every candidate N >= M (N <= max_n) with the default tiling, then
-    every tiling at the fastest N; returns the best configuration and all
-    timings (ms per launch)."""
+    """Time every candidate N >= M (N <= max_n) with the library's tiling, then
+    that ("auto") and every fixed tiling at the fastest N; returns the best
+    configuration and all timings (ms per launch).  automatic: the library's
+    tiling was the fastest (filters_per_unit and workgroups_per_cu are then what
+    the plan reports for it)."""
     from .ols import OLSPlan
     s, h = data if data is not None else synthetic(Ns, K, M, seed=M * 1000 + K)
     Ns = int(s.shape[0])
@@ -107,22 +111,24 @@ def tune(M: int, K: int, Ns: int = 1 << 22, reps: int = 10, candidates=CANDIDATE
     plan = OLSPlan(h, N=best)
     default = plan.tiling()
     cfg = (default["filters_per_unit"], default["workgroups_per_cu"])
-    tiling_ms = {f"{cfg[0]}x{cfg[1]}": times[best]}
+    tiling_ms = {"auto": times[best]}
     if tile:
+        # timed beside the others; a tiling that reads the same as the plan's is
+        # another one once it is fixed
+        tiling_ms["auto"] = _time_forward(plan, s, y, reps)
         for nf, wpc in tilings(plan):
-            key = f"{nf}x{wpc}"
-            if key in tiling_ms:
-                continue
             plan.set_tiling(nf, wpc)
-            tiling_ms[key] = _time_forward(plan, s, y, reps)
-        key = min(tiling_ms, key=tiling_ms.get)
+            tiling_ms[f"{nf}x{wpc}"] = _time_forward(plan, s, y, reps)
+    key = min(tiling_ms, key=tiling_ms.get)
+    automatic = key == "auto"
+    if not automatic:
         cfg = tuple(int(v) for v in key.split("x"))
     H = plan.info()["H"]
     cus = plan.launch()["cus"]
     plan.close()
     nseg = -(-Ns // H)
-    return {"M": M, "K": K, "Ns": Ns, "N": best, "filters_per_unit": cfg[0], "workgroups_per_cu": cfg[1],
-            "segments_per_workgroup": nseg / (cfg[1] * cus), "ms": times, "tiling_ms": tiling_ms}
+    return {"M": M, "K": K, "Ns": Ns, "N": best, "automatic": automatic, "filters_per_unit": cfg[0],
+            "workgroups_per_cu": cfg[1], "segments_per_workgroup": nseg / (cfg[1] * cus), "ms": times, "tiling_ms": tiling_ms}
 
 
 class TuneCache:
@@ -136,14 +142,21 @@ class TuneCache:
     def key(self, M: int, K: int, max_n: int) -> str:
         return f"{_arch()}|M={M}|K={K}|max={max_n}"
 
+    @staticmethod
+    def _usable(entry) -> bool:
+        """False for no entry, one of an FFT length alone, and one without
+        "automatic" that names two filters per unit at N = 2048 or 4096: its
+        time may be that of the library's tiling, which mostly runs one there."""
+        return isinstance(entry, dict) and ("automatic" in entry or entry["filters_per_unit"] != 2
+                                            or entry["N"] not in (2048, 4096))
+
     def config(self, M: int, K: int, max_n: int = 8192, **kw) -> dict:
-        """Tuned {N, filters_per_unit, workgroups_per_cu} for (M, K), measured
-        once and cached."""
+        """Tuned {N, automatic, filters_per_unit, workgroups_per_cu} for (M, K),
+        measured once and cached."""
         k = self.key(M, K, max_n)
-        if not isinstance(self.data.get(k), dict):
+        if not self._usable(self.data.get(k)):
             r = tune(M, K, max_n=max_n, **kw)
-            self.data[k] = {"N": r["N"], "filters_per_unit": r["filters_per_unit"],
-                            "workgroups_per_cu": r["workgroups_per_cu"]}
+            self.data[k] = {f: r[f] for f in ("N", "automatic", "filters_per_unit", "workgroups_per_cu") if f in r}
             os.makedirs(os.path.dirname(self.path) or ".", exist_ok=True)
             with open(self.path, "w") as f:
                 json.dump(self.data, f, indent=1)
@@ -158,7 +171,8 @@ class TuneCache:
         K, M = int(h.shape[0]), int(h.shape[1])
         c = self.config(M, K, **kw)
         p = OLSPlan(h, N=c["N"])
-        p.set_tiling(c["filters_per_unit"], c["workgroups_per_cu"])
+        if not c.get("automatic", False):
+            p.set_tiling(c["filters_per_unit"], c["workgroups_per_cu"])
         return p
 
     def batched_fft_length(self, M: int, K: int) -> int:
@@ -187,7 +201,8 @@ def sweep(reps: int = 10, tune_ns: int = 1 << 22):
         for _ in range(2):
             plan.set_tiling(0, 0)
             ms_default = min(ms_default, _time_forward(plan, s, y, max(reps, 20), warmup=20))
-            plan.set_tiling(t["filters_per_unit"], t["workgroups_per_cu"])
+            if not t["automatic"]:
+                plan.set_tiling(t["filters_per_unit"], t["workgroups_per_cu"])
             ms = min(ms, _time_forward(plan, s, y, max(reps, 20), warmup=20))
         auto = OLSPlan(h, N=0)
         auto_n = auto.info()["N"]
