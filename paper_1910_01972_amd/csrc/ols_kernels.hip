@@ -547,8 +547,7 @@ struct BatchItem {
   const float2* spectra;  // [K][N] in transform order, scaled by 1/N
   const void* h;          // the caller's filters [K][M] (read by the spectra step)
   int64_t Ns;
-  int64_t weight_begin;  // weight of the items before this one, and its own (batch_item_weight)
-  int64_t weight;
+  int64_t weight_begin;  // weight of the items before this one (batch_item_weight)
   int64_t units;
   int32_t K, M, N, D, H, nf;
   int64_t tile_begin;  // first tile of this item in the batch's tile list
@@ -556,6 +555,8 @@ struct BatchItem {
   int32_t shift_mask;  // rows off the 128-byte grid: filters delayed by row_delay with this mask
   int32_t pad;
 };
+// The workspaces that programs hold are sized by it (batch_offsets).
+static_assert(sizeof(BatchItem) == 104, "the workspace of a batched call keeps its size");
 
 // Values the batch setup computes on the device: totals over all items and
 // the outcome of its checks.  Every later kernel of a batched call reads
@@ -690,7 +691,6 @@ __device__ __forceinline__ BatchItem batch_item(const ols_batch_item_t& it, cons
   b.h = it.h;
   b.Ns = it.N_s;
   b.weight_begin = 0;
-  b.weight = batch_item_weight(sh.ntiles, it.K);
   b.units = sh.units;
   b.K = it.K;
   b.M = it.M;
@@ -846,7 +846,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
     for (int p = i0; p < i1; ++p) {
       const BatchItem& b = L.items[p];
       o[0] += b.ntiles;
-      o[1] += b.weight;
+      o[1] += batch_item_weight(b.ntiles, b.K);
       o[2] += (int64_t)b.K * b.N;
       o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
     }
@@ -859,7 +859,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void ols_batch_setup_kernel(const ol
       b.spectra = fits ? L.spectra + o[2] : nullptr;
       L.task_begin[p] = o[3];
       o[0] += b.ntiles;
-      o[1] += b.weight;
+      o[1] += batch_item_weight(b.ntiles, b.K);
       o[2] += (int64_t)b.K * b.N;
       o[3] += (b.K + 4096 / b.N - 1) / (4096 / b.N);
     }
@@ -955,7 +955,6 @@ __device__ __forceinline__ BatchItem read_item(gptr<const BatchItem> items, int 
   r.h = wave_uniform_ptr(items[i].h);
   r.Ns = wave_uniform64(items[i].Ns);
   r.weight_begin = wave_uniform64(items[i].weight_begin);
-  r.weight = wave_uniform64(items[i].weight);
   r.units = wave_uniform64(items[i].units);
   r.K = __builtin_amdgcn_readfirstlane(items[i].K);
   r.M = __builtin_amdgcn_readfirstlane(items[i].M);
@@ -1050,7 +1049,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void o
     const int64_t W = L.hdr->total_weight, w0 = W * b / P, w1 = W * (b + 1) / P;
     auto begin = [&](int k) { return gitems[k].weight_begin; };
     auto unit_at = [&](int k, int64_t v) {
-      return wave_uniform64(batch_unit_at(v - gitems[k].weight_begin, gitems[k].units, gitems[k].weight));
+      return wave_uniform64(batch_unit_at(v - gitems[k].weight_begin, gitems[k].units,
+                                          batch_item_weight(gitems[k].ntiles, gitems[k].K)));
     };
     w.i = find_item<64>(0, nitems, w0, begin);
     w.t = unit_at(w.i, w0);
