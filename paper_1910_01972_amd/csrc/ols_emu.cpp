@@ -154,6 +154,16 @@ std::vector<float2> spectra(const float2* h, int K, int M, const std::vector<flo
   return F;
 }
 
+// exp(-2 pi i m / N), m < N, as the plan's table holds them.
+inline std::vector<double2> roots(int N) {
+  std::vector<double2> root(N);
+  for (int m = 0; m < N; ++m) {
+    const long double t = 2.0L * 3.14159265358979323846264338327950288L * m / N;
+    root[m] = make_double2((double)cosl(t), (double)-sinl(t));
+  }
+  return root;
+}
+
 // Units [u0, u1) of one signal through the kernel's per-lane code (the body
 // of the device range function); a unit is one tile and NF filters.
 template <int N>
@@ -166,15 +176,12 @@ void forward_range(const float2* s, int64_t Ns, const float2* F, float2* y, int 
   UnitWalk w(u0, KG);  // the device kernels' walk
   // a one-phase stencil is folded into the segments' spectra
   Response resp{};
-  std::vector<float2> roots;
+  std::vector<double2> root;
   if (st && st->J == 1 && fold_stencil(N)) {
     resp.T = st->T;
     resp.L = st->L;
     for (int d = 0; d < st->T; ++d) resp.w[d] = st->w[0][d];
-    for (int m = 0; m < N; ++m) {
-      const double a = 6.283185307179586476925286766559 * m / N;
-      roots.push_back(make_float2((float)std::cos(a), (float)-std::sin(a)));
-    }
+    root = roots(N);
     st = nullptr;
   }
   auto forward_tile = [&]() {
@@ -190,7 +197,7 @@ void forward_range(const float2* s, int64_t Ns, const float2* F, float2* y, int 
     if (resp.T > 0)
       for (int t = 0; t < GE::WG; ++t) {
         float2 S[16];
-        stencil_response<N>(S, roots.data(), resp, t % GE::G);
+        stencil_response<N>(S, root.data(), resp, t % GE::G);
         for (int i = 0; i < 16; ++i) A[t][i] = cmul(A[t][i], S[i]);
       }
   };
@@ -614,6 +621,23 @@ struct RunGeo {
   }
 };
 
+// Transfer function of a one-phase stencil in natural frequency order.
+template <int N>
+struct RunResponse {
+  static int run(const Stencil* st, float2* out) {
+    const std::vector<double2> root = roots(N);
+    Response resp{};
+    resp.T = st->T;
+    resp.L = st->L;
+    for (int t = 0; t < st->T; ++t) resp.w[t] = st->w[0][t];
+    for (int g = 0; g < Geo<N>::G; ++g) {
+      float2 S[16];
+      stencil_response<N>(S, root.data(), resp, g);
+      for (int reg = 0; reg < 16; ++reg) out[spectrum_index<N>(g, reg)] = S[reg];
+    }
+    return 0;
+  }
+};
 }  // namespace emu
 }  // namespace ols
 
@@ -653,6 +677,18 @@ int ols_emu_forward_stencil(int N, const float* s, int64_t Ns, const float* h, i
     for (int d = 0; d < st.T; ++d) st.w[j][d] = w[j * st.T + d];
   return ols::emu::dispatch<ols::emu::RunFwd>(N, (const float2*)s, Ns, (const float2*)h, K, M, D, H, grid, (float2*)y,
                                               post, (const ols::Stencil*)&st);
+}
+
+// out[N] = transfer function S(k) of the one-phase stencil w[T] reaching L
+// back, as the fold applies it to the segments' spectra.
+int ols_emu_stencil_response(int N, int T, int L, const float* w, float* out) {
+  if (T < 1 || T > ols::STENCIL_MAX_TAPS || L < 0 || L >= T) return 1;
+  ols::Stencil st{};
+  st.J = 1;
+  st.L = L;
+  st.T = T;
+  for (int t = 0; t < T; ++t) st.w[0][t] = w[t];
+  return ols::emu::dispatch<ols::emu::RunResponse>(N, (const ols::Stencil*)&st, (float2*)out);
 }
 
 // First kept position of a plan with a stencil reaching L back and R ahead

@@ -95,6 +95,16 @@ OLS_HD float2 load_c64(P p, int64_t i) {
   const f32x2 v = rebind_ptr<const f32x2>(p)[i];
   return make_float2(v.x, v.y);
 }
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+template <class P>
+OLS_HD double2 load_c128(P p, int64_t i) {
+  static_assert(sizeof(*p) == sizeof(double2), "a table of complex128");
+  const f64x2 v = rebind_ptr<const f64x2>(p)[i];
+  return make_double2(v.x, v.y);
+}
+OLS_HD double2 cmul64(double2 a, double2 b) {
+  return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+}
 
 // ---------------------------------------------------------------------------
 // Compile-time geometry of one N-point transform, in workgroups of WG_ threads

@@ -171,14 +171,13 @@ __device__ __forceinline__ void filter_transform(float2 (&x)[16], const void* __
   fwd_from<GE, 0>(x, lds, par, tw, grp, g);
 }
 
-// root[m] = exp(-2 pi i m / N), m < N, evaluated in float64 and rounded once
-// (plan creation).
-__global__ void ols_roots_kernel(float2* __restrict__ root, int N) {
+// root[m] = exp(-2 pi i m / N), m < N, in float64 (plan creation).
+__global__ void ols_roots_kernel(double2* __restrict__ root, int N) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= N) return;
   double sn, cs;
   sincospi(2.0 * (double)m / (double)N, &sn, &cs);
-  root[m] = make_float2((float)cs, (float)(-sn));
+  root[m] = make_double2(cs, -sn);
 }
 
 // The spectra of the plan's filters, and (Fd != nullptr, gridDim.y delays) the
@@ -195,7 +194,7 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_filter_spectra_kernel(const vo
                                                                         float2* __restrict__ F,
                                                                         float2* __restrict__ Fd,
                                                                         const float2* __restrict__ twt,
-                                                                        const float2* __restrict__ root, int diff,
+                                                                        const double2* __restrict__ root, int diff,
                                                                         int real) {
   using GE = Geo<N>;
   __shared__ float2 lds[2 * GE::LDS];
@@ -210,7 +209,10 @@ __global__ __launch_bounds__(Geo<N>::WG) void ols_filter_spectra_kernel(const vo
   if (!Fd) return;
   if (d > 0) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = cmul(x[i], root[(spectrum_index<N>(g, i) * d) & (N - 1)]);
+    for (int i = 0; i < 16; ++i) {
+      const double2 z = root[(spectrum_index<N>(g, i) * d) & (N - 1)];
+      x[i] = cmul(x[i], make_float2((float)z.x, (float)z.y));
+    }
   }
   store_spectrum<N>(x, Fd + (int64_t)d * K * N, r, g);
 }
@@ -310,7 +312,7 @@ __device__ __forceinline__ void forward_units(const void* __restrict__ sv, int64
                                               const float2 (&tw)[Geo<N>::TWR], int64_t u0, int64_t u1, float2* lds,
                                               int& par, const Stencil* st = nullptr, int shift_mask = 0,
                                               int delay_rows = 0, const Response* resp = nullptr,
-                                              const float2* __restrict__ root = nullptr) {
+                                              const double2* __restrict__ root = nullptr) {
   using GE = Geo<N, WG>;
   const int tid = threadIdx.x;
   const int grp = tid / GE::G, g = tid - grp * GE::G;
@@ -472,7 +474,7 @@ __device__ __forceinline__ void forward_range(const void* __restrict__ sv, int64
                                               const float2* __restrict__ twt, int64_t u0, int64_t u1, float2* lds,
                                               int& par, const Stencil* st = nullptr, int shift_mask = 0,
                                               const Response* resp = nullptr,
-                                              const float2* __restrict__ root = nullptr) {
+                                              const double2* __restrict__ root = nullptr) {
   float2 tw[Geo<N>::TWR];
   load_lane_twiddles<N>(tw, twt, threadIdx.x % Geo<N>::G);
   // the stage's accumulators take the registers of the spectrum prefetch
@@ -505,7 +507,7 @@ template <int N, bool POWER, bool REAL, int WG>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_fold_kernel(
     const void* __restrict__ s, int64_t Ns, const float2* __restrict__ F, void* __restrict__ y, int K, int D, int H,
     int64_t ntiles, const float2* __restrict__ twt, int shift_mask, const Response resp,
-    const float2* __restrict__ root) {
+    const double2* __restrict__ root) {
   __shared__ float2 lds[forward_lds<Geo<N, WG>, 1, false>()];
   const int64_t U = ntiles * K;
   const int64_t u0 = first_unit(U, gridDim.x, blockIdx.x);
@@ -1747,7 +1749,7 @@ struct ols_plan_s {
   float2* spectra_delays = nullptr;  // [delay_ls][K][N]: the spectra delayed by 0 .. delay_ls-1 samples
   int delay_ls = 0;                   // outputs per 128-byte line (0: no delayed spectra, rows not re-aligned)
   float2* twiddles = nullptr;
-  float2* roots = nullptr;  // exp(-2 pi i m / N), m < N; part of the twiddles' allocation
+  double2* roots = nullptr;  // exp(-2 pi i m / N), m < N; part of the twiddles' allocation
 };
 
 struct ols_batch_s {
@@ -1842,7 +1844,7 @@ struct Kern {
   }
   // The forward with a folded one-phase stencil.
   using FoldFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*, int,
-                          const Response, const float2*);
+                          const Response, const double2*);
   template <bool REAL>
   static FoldFn fold_fn_real(bool power) {
     return power ? ols_forward_fold_kernel<N, true, REAL, wide(1, REAL)>
@@ -2366,9 +2368,10 @@ ols_status_t ols_plan_ex(ols_plan_t* plan, const void* h, int32_t K, int32_t M, 
 
     std::vector<float2> tw = dispatch<RunTwiddles>(N);
     // the twiddle tables and, behind them, the N-th roots of unity
-    e = hipMalloc(&p->twiddles, (tw.size() + N) * sizeof(float2));
+    const size_t tw_bytes = round256(tw.size() * sizeof(float2));
+    e = hipMalloc(&p->twiddles, tw_bytes + N * sizeof(double2));
     if (e != hipSuccess) { destroy_plan(p); (void)hipGetLastError(); return fail(OLS_ERROR_OUT_OF_MEMORY, "twiddle allocation"); }
-    p->roots = p->twiddles + tw.size();
+    p->roots = (double2*)((char*)p->twiddles + tw_bytes);
     e = hipMalloc(&p->spectra, (size_t)K * N * sizeof(float2));
     if (e != hipSuccess) { destroy_plan(p); (void)hipGetLastError(); return fail(OLS_ERROR_OUT_OF_MEMORY, "spectra allocation"); }
     // the spectra for every row delay, when they fit the budget

@@ -37,6 +37,7 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_stencil_delay.restype = I32
         L.ols_emu_stencil_hop.argtypes = [I32, I32, I32]
         L.ols_emu_stencil_hop.restype = I32
+        L.ols_emu_stencil_response.argtypes = [I32, I32, I32, P, P]
         L.ols_emu_batch_geometry.argtypes = [I32, I32, P, I64, P]
         L.ols_emu_batch_geometry.restype = None
         L.ols_emu_row_shift.argtypes = [P, I64, I32, I32, I32]
@@ -45,6 +46,7 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_row_shift.restype = I32
         L.ols_emu_cost_model.argtypes = [I32, I32, I32]
         L.ols_emu_cost_model.restype = I32
+        L.ols_emu_stencil_response.restype = I32
         for f in (L.ols_emu_forward, L.ols_emu_spectra, L.ols_emu_lds_report, L.ols_emu_geometry):
             f.restype = I32
         _emu = L
@@ -221,6 +223,16 @@ def wave_block(N: int) -> int:
     if emu().ols_emu_wave_block(N, out) != 0:
         raise ValueError(N)
     return int(out[0])
+
+
+def stencil_response(N: int, w, left: int) -> np.ndarray:
+    """Transfer function (complex64 [N], natural order) of a one-phase stencil
+    as the fold multiplies the segments' spectra by it."""
+    w = np.ascontiguousarray(w, dtype=np.float32)
+    out = np.empty(N, dtype=np.complex64)
+    if emu().ols_emu_stencil_response(N, w.size, left, _ptr(w), _ptr(out)) != 0:
+        raise ValueError((N, w.size, left))
+    return out
 
 
 def batched(items, grid: int):
