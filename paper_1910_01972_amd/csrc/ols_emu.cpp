@@ -621,7 +621,8 @@ struct RunGeo {
   }
 };
 
-// Transfer function of a one-phase stencil in natural frequency order.
+// Transfer function of a one-phase stencil, and the phases of a delay, in
+// natural frequency order.
 template <int N>
 struct RunResponse {
   static int run(const Stencil* st, float2* out) {
@@ -638,6 +639,20 @@ struct RunResponse {
     return 0;
   }
 };
+template <int N>
+struct RunDelay {
+  static int run(int d, float2* out) {
+    const std::vector<double2> root = roots(N);
+    float2 x[16], y[16];
+    for (int i = 0; i < 16; ++i) x[i] = make_float2(1.0f, 0.0f);
+    for (int g = 0; g < Geo<N>::G; ++g) {
+      delay_spectrum<N>(y, x, root.data(), d, g);
+      for (int reg = 0; reg < 16; ++reg) out[spectrum_index<N>(g, reg)] = y[reg];
+    }
+    return 0;
+  }
+};
+
 }  // namespace emu
 }  // namespace ols
 
@@ -690,6 +705,14 @@ int ols_emu_stencil_response(int N, int T, int L, const float* w, float* out) {
   for (int t = 0; t < T; ++t) st.w[0][t] = w[t];
   return ols::emu::dispatch<ols::emu::RunResponse>(N, (const ols::Stencil*)&st, (float2*)out);
 }
+
+// out[N] = phases of a delay by d samples, as the delayed spectra take them.
+int ols_emu_delay_phases(int N, int d, float* out) {
+  return ols::emu::dispatch<ols::emu::RunDelay>(N, d, (float2*)out);
+}
+
+// Workgroup rows of the launch that computes a bank's spectra and their delays.
+int ols_emu_delay_rows(int blocks, int delays, int cus) { return ols::delay_rows(blocks, delays, cus); }
 
 // First kept position of a plan with a stencil reaching L back and R ahead
 // (the host plan code's rule; the hop is N - D - R).

@@ -180,41 +180,45 @@ __global__ void ols_roots_kernel(double2* __restrict__ root, int N) {
   root[m] = make_double2(cs, -sn);
 }
 
-// The spectra of the plan's filters, and (Fd != nullptr, gridDim.y delays) the
-// same spectra delayed by d = blockIdx.y samples for output rows off the
-// 128-byte grid: Fd[d][r] = F[r] * exp(-2 pi i k d / N), in the same storage
-// order (the phase from the exact integer k * d mod N).  Computed with the
-// spectra, so that a forward call only reads the plan.  Every delay transforms
-// the filters again: K / SEGS workgroups leave most CUs idle, and one launch
-// with the phases read from the table replaces two, the second of which
-// evaluated a float64 sine and cosine per value (16 filters, N = 4096, per
-// filter update: 5.7 + 6.4 us and a launch gap -> 6.4 us).
+// The spectra of the plan's filters, and (Fd != nullptr) the same spectra
+// delayed by d = 0 .. delays - 1 samples for output rows off the 128-byte grid:
+// Fd[d][r] = F[r] * exp(-2 pi i k d / N), in the same storage order.  Computed
+// with the spectra, so that a forward call only reads the plan.  Workgroup row
+// blockIdx.y takes the delays d = blockIdx.y, + gridDim.y, ...: of a small bank
+// each delay transforms the filters again, because K / SEGS workgroups leave
+// most CUs idle, and a bank that fills the chip transforms them once (Kern::
+// spectra chooses).  The delays' stores bind then, where a transform and sixteen
+// scattered table reads per delay had (us per filter update, one launch per
+// delay and the table / this: 250 x 100, N = 8192 171 / 56; 64 x 2000, N = 8192
+// 47 / 24; 16 x 512, N = 4096 8.8 / 7.5).
 template <int N>
 __global__ __launch_bounds__(Geo<N>::WG) void ols_filter_spectra_kernel(const void* __restrict__ h, int K, int M,
                                                                         float2* __restrict__ F,
-                                                                        float2* __restrict__ Fd,
+                                                                        float2* __restrict__ Fd, int delays,
                                                                         const float2* __restrict__ twt,
                                                                         const double2* __restrict__ root, int diff,
                                                                         int real) {
   using GE = Geo<N>;
   __shared__ float2 lds[2 * GE::LDS];
   const int grp = threadIdx.x / GE::G, g = threadIdx.x - grp * GE::G;
-  const int r0 = blockIdx.x * GE::SEGS, r = r0 + grp, d = blockIdx.y;
+  const int r0 = blockIdx.x * GE::SEGS, r = r0 + grp;
   float2 x[16];
   filter_transform<N>(x, h, K, M, twt, diff, real, r0, lds);
   if (r >= K) return;
 #pragma unroll
   for (int i = 0; i < 16; ++i) x[i] = cscale(x[i], 1.0f / (float)N);
-  if (d == 0) store_spectrum<N>(x, F, r, g);
+  if (blockIdx.y == 0) store_spectrum<N>(x, F, r, g);
   if (!Fd) return;
-  if (d > 0) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const double2 z = root[(spectrum_index<N>(g, i) * d) & (N - 1)];
-      x[i] = cmul(x[i], make_float2((float)z.x, (float)z.y));
+  for (int d = blockIdx.y; d < delays; d += gridDim.y) {
+    float2* const out = Fd + (int64_t)d * K * N;
+    if (d == 0) {
+      store_spectrum<N>(x, out, r, g);
+      continue;
     }
+    float2 y[16];
+    delay_spectrum<N>(y, x, root, d, g);
+    store_spectrum<N>(y, out, r, g);
   }
-  store_spectrum<N>(x, Fd + (int64_t)d * K * N, r, g);
 }
 
 // Natural-order copy of the spectra: out[r][k] = F[r][spectrum_offset(reg, g)]
@@ -1790,8 +1794,9 @@ struct Kern {
   // the plan's spectra, and its spectra for every row delay if it holds them
   static hipError_t spectra(const ols_plan_s* p, const void* h, hipStream_t st) {
     const int blocks = (p->K + GE::SEGS - 1) / GE::SEGS;
-    hipLaunchKernelGGL(ols_filter_spectra_kernel<N>, dim3(blocks, p->spectra_delays ? p->delay_ls : 1), dim3(GE::WG), 0,
-                       st, h, p->K, p->M, p->spectra, p->spectra_delays, p->twiddles, p->roots,
+    const int rows = p->spectra_delays ? delay_rows(blocks, p->delay_ls, p->cus) : 1;
+    hipLaunchKernelGGL(ols_filter_spectra_kernel<N>, dim3(blocks, rows), dim3(GE::WG), 0, st, h, p->K, p->M,
+                       p->spectra, p->spectra_delays, p->delay_ls, p->twiddles, p->roots,
                        (p->flags & OLS_POST_DERIVATIVE) ? 1 : 0, (p->flags & OLS_REAL) ? 1 : 0);
     return hipGetLastError();
   }

@@ -474,6 +474,18 @@ OLS_HD double2 delay_root(P root, int k0, int d) { return load_c128(root, (k0 * 
 template <int N, class P>
 OLS_HD double2 delay_step(P root, int d) { return load_c128(root, (d * (N / 16)) & (N - 1)); }
 
+// x times the phases of a delay by d samples.
+template <int N, class P>
+OLS_HD void delay_spectrum(float2 (&y)[16], const float2 (&x)[16], P root, int d, int g) {
+  double2 z = delay_root<N>(root, spectrum_index<N>(g, 0), d);
+  const double2 u = delay_step<N>(root, d);
+#pragma unroll
+  for (int reg = 0; reg < 16; ++reg) {
+    y[reg] = cmul(x[reg], make_float2((float)z.x, (float)z.y));
+    z = cmul64(z, u);
+  }
+}
+
 // S(k) for lane g's frequencies, summed in float64 and rounded once.  Tap t
 // advances by d = t - L.  Of its sixteen phases z u^reg only z u^a, a < 4, are
 // formed: u^4 = (-i)^d, so the taps of equal t mod 4 share the rest, a radix-4
@@ -831,6 +843,13 @@ OLS_HD void store_valid_pair(const float2 (&x)[16], P yrow, int64_t Ns, int64_t 
                          [&](int reg) { return POWER ? x[reg].x * x[reg].x : x[reg].x; });
   store_segment<N, MODE>(yrow, Ns, out0 + H, D, H, g,
                          [&](int reg) { return POWER ? x[reg].y * x[reg].y : x[reg].y; });
+}
+
+// Workgroup rows of the spectra launch, which share out a bank's delays: enough
+// for two workgroups per CU, at most one row per delay.
+OLS_HD int delay_rows(int blocks, int delays, int cus) {
+  const int rows = (2 * cus + blocks - 1) / blocks;
+  return rows < delays ? rows : delays;
 }
 
 // Filters per work unit of the forward kernels: two interleaved transforms

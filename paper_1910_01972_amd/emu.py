@@ -38,6 +38,8 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_stencil_hop.argtypes = [I32, I32, I32]
         L.ols_emu_stencil_hop.restype = I32
         L.ols_emu_stencil_response.argtypes = [I32, I32, I32, P, P]
+        L.ols_emu_delay_phases.argtypes = [I32, I32, P]
+        L.ols_emu_delay_rows.argtypes = [I32, I32, I32]
         L.ols_emu_batch_geometry.argtypes = [I32, I32, P, I64, P]
         L.ols_emu_batch_geometry.restype = None
         L.ols_emu_row_shift.argtypes = [P, I64, I32, I32, I32]
@@ -46,7 +48,8 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_row_shift.restype = I32
         L.ols_emu_cost_model.argtypes = [I32, I32, I32]
         L.ols_emu_cost_model.restype = I32
-        L.ols_emu_stencil_response.restype = I32
+        for f in (L.ols_emu_stencil_response, L.ols_emu_delay_phases, L.ols_emu_delay_rows):
+            f.restype = I32
         for f in (L.ols_emu_forward, L.ols_emu_spectra, L.ols_emu_lds_report, L.ols_emu_geometry):
             f.restype = I32
         _emu = L
@@ -232,6 +235,14 @@ def stencil_response(N: int, w, left: int) -> np.ndarray:
     out = np.empty(N, dtype=np.complex64)
     if emu().ols_emu_stencil_response(N, w.size, left, _ptr(w), _ptr(out)) != 0:
         raise ValueError((N, w.size, left))
+    return out
+
+
+def delay_phases(N: int, d: int) -> np.ndarray:
+    """Phases (complex64 [N], natural order) of the spectra delayed by d samples."""
+    out = np.empty(N, dtype=np.complex64)
+    if emu().ols_emu_delay_phases(N, d, _ptr(out)) != 0:
+        raise ValueError(N)
     return out
 
 
