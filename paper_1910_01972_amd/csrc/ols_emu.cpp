@@ -16,6 +16,7 @@
 #include <array>
 #include <cmath>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 #include <limits>
 #include <map>
@@ -303,8 +304,10 @@ int backward(const float2* s, int64_t Ns, const float2* gy, const float2* h, int
   const int64_t U = ntiles * K;
   if (grid > U) grid = (int)U;
   const int64_t P = grid;
-  std::vector<float2> ws((size_t)P * 2 * GE::SEGS * N, make_float2(0.f, 0.f));
-  std::vector<float2> part((size_t)P * GE::SEGS * K * M, make_float2(0.f, 0.f));
+  // NaN: a window or slot that no workgroup wrote must not be read
+  const float2 poison = make_float2(std::numeric_limits<float>::quiet_NaN(), std::numeric_limits<float>::quiet_NaN());
+  std::vector<float2> ws((size_t)P * 2 * GE::SEGS * N, poison);
+  std::vector<float2> part((size_t)P * GE::SEGS * K * M, poison);
   Group<N> G;
   G.poison();
   std::vector<std::array<float2, 16>> xs(GE::WG), A(GE::WG), acc(GE::WG);
@@ -374,37 +377,53 @@ int backward(const float2* s, int64_t Ns, const float2* gy, const float2* h, int
     }
     finish_tile();
   }
-  // split-tile fixup, exactly as the device kernel
-  for (int64_t bnd = 1; bnd < P; ++bnd) {
-    const int64_t ub = first_unit(U, P, bnd);
-    if (ub % K == 0) continue;
-    const int64_t t = ub / K;
-    if (first_unit(U, P, bnd - 1) > t * K) continue;
-    const int64_t blo = owner_of_unit(U, P, t * K), bhi = owner_of_unit(U, P, (t + 1) * K - 1);
-    for (int i = 0; i < GE::SEGS * H; ++i) {
-      const int sg = i / H, p = i - sg * H;
-      const int64_t o = (t * GE::SEGS + sg) * H + p;
-      if (o >= Ns) continue;
+  // the tail, exactly as the device kernel
+  const int64_t KM = (int64_t)K * M, nslots = P * GE::SEGS, nch = dh_chunks(nslots);
+  const TailShape ts = tail_shape(GE::SEGS, H, ntiles, K, P, KM, true, true);
+  for (int64_t unit = 0; unit < ts.nfix; ++unit) {
+    const SplitTile st = split_tile(U, P, K, ts.by_tile != 0, unit);
+    if (st.t < 0) continue;
+    for (int e = 0; e < GE::SEGS * H && st.t * GE::SEGS * H + e < Ns; ++e) {
+      const int sg = e / H, p = e - sg * H;
       float2 a = make_float2(0.f, 0.f);
-      for (int64_t bb = blo; bb <= bhi; ++bb) {
-        const int slot = first_unit(U, P, bb) / K == t ? 0 : 1;
+      for (int64_t bb = st.blo; bb <= st.bhi; ++bb) {
+        const int slot = first_unit(U, P, bb) / K == st.t ? 0 : 1;
         a = cadd(a, ws[((bb * 2 + slot) * GE::SEGS + sg) * (int64_t)N + p]);
       }
-      ds[o] = a;
+      ds[st.t * GE::SEGS * H + e] = a;
     }
   }
-  const int64_t KM = (int64_t)K * M, nslots = P * GE::SEGS, nch = dh_chunks(nslots);
+  const DhSlots sl{U, P, K, 1, M};
   for (int64_t i = 0; i < KM; ++i) {
     float2 a = make_float2(0.f, 0.f);
     for (int64_t c = 0; c < nch; ++c) {
+      bool here[DH_CHUNK / GE::SEGS];
+      dh_workgroups(here, sl, c * DH_CHUNK / GE::SEGS, (int)(i / M));
       float2 cs = make_float2(0.f, 0.f);
-      for (int64_t sl = c * DH_CHUNK; sl < std::min<int64_t>(nslots, (c + 1) * DH_CHUNK); ++sl)
-        cs = cadd(cs, part[sl * KM + i]);
+      for (int k = 0; k < DH_CHUNK; ++k)
+        if (here[k / GE::SEGS] && dh_group<false>(k, (int)(i / M))) cs = cadd(cs, part[(c * DH_CHUNK + k) * KM + i]);
       a = cadd(a, cs);
     }
     dh[i] = a;
   }
   return G.guards_ok() ? 0 : 3;
+}
+
+// out[slot][r]: the tail reads filter r's lags from this slot (P workgroups of
+// SEGS groups; K filters).
+template <int SEGS>
+void dh_slots(const DhSlots& sl, bool paired, int K, uint8_t* out) {
+  for (int64_t c = 0; c < dh_chunks(sl.P * SEGS); ++c)
+    for (int r = 0; r < K; ++r) {
+      bool here[DH_CHUNK / SEGS];
+      dh_workgroups(here, sl, c * DH_CHUNK / SEGS, r);
+      for (int k = 0; k < DH_CHUNK; ++k) {
+        const int64_t slot = c * DH_CHUNK + k;
+        const bool read = here[k / SEGS] && (paired ? dh_group<true>(k, r) : dh_group<false>(k, r));
+        if (slot < sl.P * SEGS) out[slot * K + r] = read;
+        else if (read) std::abort();  // a slot past the last
+      }
+    }
 }
 
 // Batched: the same unit table, equal shares per workgroup, binary search for
@@ -745,6 +764,37 @@ int ols_emu_backward(int N, const float* s, int64_t Ns, const float* gy, const f
                      int grid, float* ds, float* dh) {
   return ols::emu::dispatch<ols::emu::RunBwd>(N, (const float2*)s, Ns, (const float2*)gy, (const float2*)h, K, M, D,
                                               H, grid, (float2*)ds, (float2*)dh);
+}
+
+// The adjoint's tail for units of fpu filters (upt units per tile, U in all) on
+// P workgroups of segs groups.  dh_slots: out[P * segs][K] = 1 where a slot
+// is read for a filter.
+int ols_emu_dh_slots(int64_t U, int64_t P, int upt, int fpu, int segs, int paired, int K, uint8_t* out) {
+  const ols::DhSlots sl{U, P, upt, fpu, 1};
+  switch (segs) {
+    case 1: ols::emu::dh_slots<1>(sl, paired != 0, K, out); return 0;
+    case 2: ols::emu::dh_slots<2>(sl, paired != 0, K, out); return 0;
+    case 4: ols::emu::dh_slots<4>(sl, paired != 0, K, out); return 0;
+    case 8: ols::emu::dh_slots<8>(sl, paired != 0, K, out); return 0;
+    case 16: ols::emu::dh_slots<16>(sl, paired != 0, K, out); return 0;
+  }
+  return 1;
+}
+// out = t, blo, bhi of one unit of the ds part (split_tile).
+void ols_emu_split_tile(int64_t U, int64_t P, int64_t upt, int by_tile, int64_t unit, int64_t* out) {
+  const ols::SplitTile st = ols::split_tile(U, P, upt, by_tile != 0, unit);
+  out[0] = st.t;
+  out[1] = st.blo;
+  out[2] = st.bhi;
+}
+// out = nfix, split, by_tile, ndh, lags per workgroup (tail_shape, both gradients).
+void ols_emu_tail_shape(int segs, int H, int64_t ntiles, int64_t upt, int64_t grid, int64_t KM, int64_t* out) {
+  const ols::TailShape t = ols::tail_shape(segs, H, ntiles, upt, grid, KM, true, true);
+  out[0] = t.nfix;
+  out[1] = t.split;
+  out[2] = t.by_tile;
+  out[3] = t.ndh;
+  out[4] = (int64_t)1 << t.lags_log2;
 }
 
 // Batched forward through the kernel dataflow.  Per item: s, y (host), N_s,

@@ -1503,141 +1503,82 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
 
 // What is left after the adjoint kernel, in one launch: the partial ds windows
 // of tiles split between workgroups, and the dh slots.  Both are bound by
-// memory latency (few loads per lane, all in flight at once), and they are
-// independent; as a launch of their own for the windows and two for the slots
-// they took 12.7 + 6.9 + 5.0 us on the 2^22 x 16 x 512 adjoint and 4.2 + 3.0 +
-// 2.6 us on a 50000 x 4 x 64 one (whole adjoint, graph replays, us: 285.9 -> 282.0
-// and 21.6 -> 16.7; 512 threads 285.0 and 17.5, 1024 289.4 and 19.1).
-constexpr int TAIL_THREADS = 256;
-// Workgroups per tile boundary: at most 4 outputs of a segment per lane; fewer
-// than 4 leave short windows to one workgroup's serial loads (50000 x 4 x 64: 15.7
-// us with 4 or 8, 20.9 with one), 8 mostly repeat the boundary's arithmetic (2^22
-// x 16, N = 1024: 208 against 202).
-constexpr int tail_split(int N) { return N > 4096 ? 8 : 4; }
-// Lags per workgroup of the dh part, and chunks of slots summed at a time: 128
-// bytes of each slot where a workgroup of the adjoint has one slot (2^22 x 16 x
-// 512: 265 -> 259 us against 64 bytes), 64 where it has several (2^18 x 16, N =
-// 1024: 39 against 43).
-constexpr int tail_lags(int segs) { return segs == 1 ? 16 : 8; }
+// memory latency, and they are independent; as a launch of their own for the
+// windows and two for the slots they took 12.7 + 6.9 + 5.0 us on the 2^22 x 16 x
+// 512 adjoint and 4.2 + 3.0 + 2.6 us on a 50000 x 4 x 64 one (whole adjoint,
+// graph replays, us: 285.9 -> 282.0 and 21.6 -> 16.7; 512 threads 285.0 and 17.5,
+// 1024 289.4 and 19.1).  How the work is cut decides how many loads each lane
+// waits for in turn: see tail_shape.
 
-// The boundary between workgroups b-1 and b of the adjoint kernel (the first
-// boundary inside a tile does the whole tile): sums the windows of the sharing
-// workgroups in workgroup order.  SEGS transforms per tile, K units per tile
+// The windows of one split tile (split_tile), summed in workgroup order; part
+// `part` of `split` workgroups.  SEGS transforms per tile, upt units per tile
 // (the filters, or the filter pairs of the paired adjoint).
 template <int N, int SEGS>
-__device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K,
-                                         int H, int64_t ntiles, int64_t P, int64_t b, int split) {
-  const int64_t U = ntiles * K;
-  const int64_t ub = first_unit(U, P, b);
-  if (ub % K == 0) return;
-  const int64_t t = ub / K;
-  if (first_unit(U, P, b - 1) > t * K) return;
-  const int64_t blo = owner_of_unit(U, P, t * K), bhi = owner_of_unit(U, P, (t + 1) * K - 1);
+__device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns,
+                                         int64_t upt, int H, int64_t U, int64_t P, const SplitTile st, int part,
+                                         int split) {
   // Slot of each sharing workgroup's window (0: the tile is its first, 1: its
   // last): every workgroup after blo starts inside tile t; blo may have
   // started in an earlier tile.  Hoisted out of the element loop (64-bit
   // divisions).
-  const int64_t slot_lo = first_unit(U, P, blo) / K == t ? 0 : 1;
-  for (int sg = 0; sg < SEGS; ++sg) {
-    const int64_t o0 = (t * SEGS + sg) * H;
-    for (int p = threadIdx.x + split * TAIL_THREADS; p < H; p += tail_split(N) * TAIL_THREADS) {
-      if (o0 + p >= Ns) break;
-      // the sharing workgroups' windows in workgroup order, loaded four at a
-      // time so that the loads overlap
+  const int64_t slot_lo = first_unit(U, P, st.blo) / upt == st.t ? 0 : 1;
+  const int64_t o0 = st.t * SEGS * H;  // the tile's segments are consecutive outputs
+  for (int e = threadIdx.x + part * TAIL_THREADS; e < SEGS * H; e += split * TAIL_THREADS) {
+    if (o0 + e >= Ns) break;
+    const int sg = SEGS == 1 ? 0 : e / H, p = e - sg * H;
+    // several windows at a time, so that their loads overlap
+    auto sum = [&](auto width) {
+      constexpr int W = decltype(width)::value;
       float2 a = make_float2(0.f, 0.f);
-      int64_t bb = blo;
-      for (; bb + 4 <= bhi + 1; bb += 4) {
-        float2 v[4];
+      for (int64_t bb = st.blo; bb <= st.bhi; bb += W) {
+        float2 v[W];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int64_t slot = bb + k == blo ? slot_lo : 0;
-          v[k] = ws_ds[(((bb + k) * 2 + slot) * SEGS + sg) * (int64_t)N + p];
+        for (int k = 0; k < W; ++k) {
+          const int64_t slot = bb + k == st.blo ? slot_lo : 0;
+          if (bb + k <= st.bhi) v[k] = ws_ds[(((bb + k) * 2 + slot) * SEGS + sg) * (int64_t)N + p];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) a = cadd(a, v[k]);
+        for (int k = 0; k < W; ++k)
+          if (bb + k <= st.bhi) a = cadd(a, v[k]);
       }
-      if (bb <= bhi) {
-        // the last one to three windows
-        float2 v[3];
-        const int rem = (int)(bhi + 1 - bb);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const int64_t slot = bb + k == blo ? slot_lo : 0;
-          v[k] = k < rem ? ws_ds[(((bb + k) * 2 + slot) * SEGS + sg) * (int64_t)N + p] : make_float2(0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-          if (k < rem) a = cadd(a, v[k]);
-      }
-      ds[o0 + p] = a;
-    }
+      return a;
+    };
+    ds[o0 + e] = st.bhi - st.blo < 4 ? sum(std::integral_constant<int, 4>()) : sum(std::integral_constant<int, 8>());
   }
 }
 
-// Which slots hold lags of filter r: those of the workgroups with a unit of it,
-// and of the groups that collect its parity in the paired adjoint.  The others
-// are not written, and a call of few units per workgroup (K filters, one unit
-// each, and K M values per slot) would otherwise spend its time clearing and
-// reading them.
-struct DhSlots {
-  int64_t U, P;  // units and workgroups of the adjoint kernel
-  int upt;       // units per tile
-  int fpu;       // filters per unit
-  int M;
-};
-
-// dh[i] for tail_lags values of i: the slots in chunks of DH_CHUNK, each chunk
+// dh[i] for LAGS values of i: the slots in chunks of DH_CHUNK, each chunk
 // in slot order by one thread per lag, then the chunk sums in chunk order
 // (CHUNKS chunks at a time, handed over through LDS).
-template <int SEGS, bool PAIRED>
+template <int SEGS, bool PAIRED, int LAGS>
 __device__ __forceinline__ void dh_sums(const float2* __restrict__ part, const DhSlots sl, int64_t KM,
-                                        float2* __restrict__ dh, int64_t block) {
+                                        float2* __restrict__ dh, int64_t block, float2* sums) {
   static_assert(DH_CHUNK % SEGS == 0, "a chunk holds whole workgroups' slots");
-  constexpr int LAGS = tail_lags(SEGS), CHUNKS = TAIL_THREADS / LAGS;
-  __shared__ float2 sums[CHUNKS][LAGS];
+  constexpr int CHUNKS = TAIL_THREADS / LAGS;
   const int lag = threadIdx.x % LAGS, row = threadIdx.x / LAGS;
   const int64_t i = block * LAGS + lag;
   const int64_t nslots = sl.P * SEGS;
-  const int r = (int)(i / sl.M), q = r / sl.fpu;
-  // workgroups own base or base + 1 consecutive units
-  const int64_t base = sl.U / sl.P, rem = sl.U - base * sl.P;
-  const bool all = base >= sl.upt;  // every workgroup has a unit of every filter
+  const int r = (int)(i / sl.M);
   float2 total = make_float2(0.f, 0.f);
   for (int64_t c0 = 0; c0 * DH_CHUNK < nslots; c0 += CHUNKS) {
     const int64_t s0 = (c0 + row) * DH_CHUNK;
-    int64_t b = s0 / SEGS;
-    // first unit of workgroup b: its place in its tile, and what is left of
-    // the division (carried from one workgroup to the next)
-    const int64_t u0 = first_unit(sl.U, sl.P, b);
-    int64_t left = sl.U * b - u0 * sl.P;
-    int m = (int)(u0 % sl.upt);
     bool here[DH_CHUNK / SEGS];
-#pragma unroll
-    for (int w = 0; w < DH_CHUNK / SEGS; ++w, ++b) {
-      left += rem;
-      const bool more = left >= sl.P;
-      left -= more ? sl.P : 0;
-      const int len = (int)(base < sl.upt ? base : sl.upt) + (more ? 1 : 0);
-      const int d = q >= m ? q - m : q - m + sl.upt;
-      here[w] = i < KM && b < sl.P && (all || d < len);
-      m += len;
-      m -= m >= sl.upt ? sl.upt : 0;
-    }
+    dh_workgroups(here, sl, s0 / SEGS, r);
     float2 v[DH_CHUNK];
 #pragma unroll
     for (int k = 0; k < DH_CHUNK; ++k) {
-      const bool mine = here[k / SEGS] && (!PAIRED || ((k ^ r) & 1) == 0);
+      const bool mine = i < KM && here[k / SEGS] && dh_group<PAIRED>(k, r);
       v[k] = mine ? part[(s0 + k) * KM + i] : make_float2(0.f, 0.f);
     }
     float2 a = make_float2(0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < DH_CHUNK; ++k) a = cadd(a, v[k]);
-    sums[row][lag] = a;
+    sums[threadIdx.x] = a;
     __syncthreads();
     if (row == 0) {
       const int64_t chunks = dh_chunks(nslots) - c0;
       const int n = chunks < CHUNKS ? (int)chunks : CHUNKS;
-      for (int c = 0; c < n; ++c) total = cadd(total, sums[c][lag]);
+      for (int c = 0; c < n; ++c) total = cadd(total, sums[c * LAGS + lag]);
     }
     __syncthreads();
   }
@@ -1648,12 +1589,25 @@ __device__ __forceinline__ void dh_sums(const float2* __restrict__ part, const D
 // others fix ds (either may be absent).
 template <int N, int SEGS, bool PAIRED>
 __global__ __launch_bounds__(TAIL_THREADS) void ols_backward_tail_kernel(
-    const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int K, int H, int64_t ntiles, int64_t P,
-    int64_t ndh, const float2* __restrict__ part, const DhSlots sl, int64_t KM, float2* __restrict__ dh) {
+    const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int H, const float2* __restrict__ part,
+    const DhSlots sl, int64_t KM, float2* __restrict__ dh, const TailShape ts) {
   const int64_t blk = blockIdx.x;
-  if (blk < ndh) dh_sums<SEGS, PAIRED>(part, sl, KM, dh, blk);
-  else ds_fixup<N, SEGS>(ws_ds, ds, Ns, K, H, ntiles, P, (blk - ndh) / tail_split(N) + 1,
-                         (int)((blk - ndh) % tail_split(N)));
+  if (blk < ts.ndh) {
+    // workgroups that share the slots' 128-byte lines on one XCD (41272 x 34 x
+    // 128, N = 256, dh: 38.3 us in launch order, 36.1 so)
+    __shared__ float2 sums[TAIL_THREADS];
+    const int64_t b = ts.lags_log2 < 4 ? batch_workgroup_order(blk, ts.ndh) : blk;
+    switch (ts.lags_log2) {
+      case 1: dh_sums<SEGS, PAIRED, 2>(part, sl, KM, dh, b, sums); break;
+      case 2: dh_sums<SEGS, PAIRED, 4>(part, sl, KM, dh, b, sums); break;
+      case 3: dh_sums<SEGS, PAIRED, 8>(part, sl, KM, dh, b, sums); break;
+      default: dh_sums<SEGS, PAIRED, 16>(part, sl, KM, dh, b, sums); break;
+    }
+    return;
+  }
+  const SplitTile st = split_tile(sl.U, sl.P, sl.upt, ts.by_tile != 0, (blk - ts.ndh) / ts.split);
+  if (st.t >= 0)
+    ds_fixup<N, SEGS>(ws_ds, ds, Ns, sl.upt, H, sl.U, sl.P, st, (int)((blk - ts.ndh) % ts.split), ts.split);
 }
 
 // Plain fill with zero (used instead of a memset so callers may capture it).
@@ -2040,12 +1994,12 @@ struct Kern {
     if (e != hipSuccess) return e;
     // split tiles' windows and the dh slots
     const int64_t KM = (int64_t)p->K * p->M;
-    constexpr int LAGS = tail_lags(BWD_SEGS);
-    const int64_t nfix = ds ? (grid - 1) * tail_split(N) : 0, ndh = dh ? (KM + LAGS - 1) / LAGS : 0;
-    if (nfix + ndh > 0) {
+    const TailShape ts = tail_shape(BWD_SEGS, p->H, ntiles, upt, grid, KM, ds != nullptr, dh != nullptr);
+    const int64_t blocks = ts.ndh + ts.nfix * ts.split;
+    if (blocks > 0) {
       const DhSlots sl{units, grid, upt, (PAIRED || duo) ? 2 : 1, p->M};
-      hipLaunchKernelGGL((ols_backward_tail_kernel<N, BWD_SEGS, PAIRED>), dim3((unsigned)(nfix + ndh)), dim3(TAIL_THREADS), 0,
-                         st, w.ws_ds, ds, Ns, upt, p->H, ntiles, grid, ndh, w.part_dh, sl, KM, dh);
+      hipLaunchKernelGGL((ols_backward_tail_kernel<N, BWD_SEGS, PAIRED>), dim3((unsigned)blocks), dim3(TAIL_THREADS), 0,
+                         st, w.ws_ds, ds, Ns, p->H, w.part_dh, sl, KM, dh, ts);
       e = hipGetLastError();
     }
     return e;

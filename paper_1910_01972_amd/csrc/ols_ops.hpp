@@ -1054,4 +1054,110 @@ struct UnitWalk {
 OLS_HD int64_t first_unit(int64_t U, int64_t P, int64_t b) { return U * b / P; }
 OLS_HD int64_t owner_of_unit(int64_t U, int64_t P, int64_t u) { return ((u + 1) * P + U - 1) / U - 1; }
 
+// ---------------------------------------------------------------------------
+// Tail of the adjoint: split tiles' ds windows and the dh slots.
+// ---------------------------------------------------------------------------
+// Unit `unit` of the ds part: a tile whose filters are split between
+// workgroups blo .. bhi, or none (t < 0).  A unit is a tile, or the boundary
+// between workgroups unit and unit + 1, of which the first inside a tile
+// stands for it.
+struct SplitTile {
+  int64_t t, blo, bhi;
+};
+OLS_HD SplitTile split_tile(int64_t U, int64_t P, int64_t upt, bool by_tile, int64_t unit) {
+  int64_t t = unit;
+  if (!by_tile) {
+    const int64_t ub = first_unit(U, P, unit + 1);
+    t = ub / upt;
+    if (ub == t * upt || first_unit(U, P, unit) > t * upt) return SplitTile{-1, 0, 0};
+  }
+  const int64_t blo = owner_of_unit(U, P, t * upt), bhi = owner_of_unit(U, P, (t + 1) * upt - 1);
+  return SplitTile{blo == bhi ? -1 : t, blo, bhi};
+}
+
+// Which slots hold lags of filter r: those of the workgroups with a unit of it,
+// and of the groups that collect its parity in the paired adjoint.  The others
+// are not written, and a call of few units per workgroup (K filters, one unit
+// each, and K M values per slot) would otherwise spend its time clearing and
+// reading them.
+struct DhSlots {
+  int64_t U, P;  // units and workgroups of the adjoint kernel
+  int upt;       // units per tile
+  int fpu;       // filters per unit
+  int M;
+};
+// here[w]: workgroup b + w has a unit of filter r.
+template <int NW>
+OLS_HD void dh_workgroups(bool (&here)[NW], const DhSlots& sl, int64_t b, int r) {
+  // workgroups own base or base + 1 consecutive units
+  const int64_t base = sl.U / sl.P, rem = sl.U - base * sl.P;
+  const bool all = base >= sl.upt;  // every workgroup has a unit of every filter
+  const int q = r / sl.fpu;
+  // first unit of workgroup b: its place in its tile, and what is left of
+  // the division (carried from one workgroup to the next)
+  const int64_t u0 = first_unit(sl.U, sl.P, b);
+  int64_t left = sl.U * b - u0 * sl.P;
+  int m = (int)(u0 % sl.upt);
+#pragma unroll
+  for (int w = 0; w < NW; ++w, ++b) {
+    left += rem;
+    const bool more = left >= sl.P;
+    left -= more ? sl.P : 0;
+    const int len = (int)(base < sl.upt ? base : sl.upt) + (more ? 1 : 0);
+    const int d = q >= m ? q - m : q - m + sl.upt;
+    here[w] = b < sl.P && (all || d < len);
+    m += len;
+    m -= m >= sl.upt ? sl.upt : 0;
+  }
+}
+// Group `group` of a workgroup collects filter r.
+template <bool PAIRED>
+OLS_HD bool dh_group(int group, int r) { return !PAIRED || ((group ^ r) & 1) == 0; }
+
+// How the tail's work is cut, for latency: a lane waits in turn for each of
+// its ds outputs (their windows load together) and for each round of chunks of
+// its dh lag.
+//   ds   nfix units (split_tile), the tiles where they are fewer than the
+//        boundaries, none where every tile has one workgroup, with `split`
+//        workgroups each: at least four, eight for windows of more than 16
+//        outputs per lane, and as many as a launch of TAIL_FIX_GROUPS allows (a
+//        thousand workgroups that find nothing to do take 1.4 us), up to one
+//        output per lane.
+//   dh   2^lags_log2 lags per workgroup: 128 bytes of each slot where a
+//        workgroup of the adjoint has one slot (2^22 x 16 x 512: 265 -> 259 us
+//        against 64 bytes), 64 where it has several (2^18 x 16, N = 1024: 39
+//        against 43), fewer while the chunks take several rounds and the launch
+//        has not TAIL_DH_GROUPS workgroups.
+// Four workgroups per boundary and the full width throughout (us, adjoint,
+// that / this): many workgroups per tile, 4356 x 59 x 1, N = 4096, ds 29.7 / 15.0;
+// many segments per tile, 2882696 x 6 x 3, N = 256, ds 57.7 / 43.2; many slots,
+// 2628819 x 1 x 12, N = 256, dh 47.2 / 34.5.
+constexpr int TAIL_THREADS = 256;
+constexpr int64_t TAIL_FIX_GROUPS = 1024, TAIL_DH_GROUPS = 512;
+struct TailShape {
+  int64_t nfix, ndh;  // units of the ds part, workgroups of the dh part (a multiple of the 8 XCDs)
+  int split, by_tile, lags_log2;
+};
+OLS_HD TailShape tail_shape(int segs, int H, int64_t ntiles, int64_t upt, int64_t grid, int64_t KM, bool ds, bool dh) {
+  TailShape t{0, 0, 1, 0, 0};
+  if (ds && grid > 1 && upt > 1 && ntiles % grid != 0) {
+    t.by_tile = ntiles < grid - 1;
+    t.nfix = t.by_tile ? ntiles : grid - 1;
+    const int64_t one = ((int64_t)segs * H + TAIL_THREADS - 1) / TAIL_THREADS;  // one output per lane
+    int64_t split = TAIL_FIX_GROUPS / t.nfix;
+    const int least = one > 16 ? 8 : 4;
+    split = split < least ? least : split;
+    t.split = (int)(split < one ? split : one);
+  }
+  if (dh) {
+    t.lags_log2 = segs == 1 ? 4 : 3;
+    const int64_t chunks = dh_chunks(grid * segs);
+    while (t.lags_log2 > 1 && chunks > (TAIL_THREADS >> t.lags_log2) && (KM >> t.lags_log2) < TAIL_DH_GROUPS)
+      --t.lags_log2;
+    const int64_t lags = (int64_t)1 << t.lags_log2;
+    t.ndh = ((KM + lags - 1) / lags + 7) / 8 * 8;
+  }
+  return t;
+}
+
 }  // namespace ols

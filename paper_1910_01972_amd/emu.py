@@ -37,6 +37,12 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_stencil_delay.restype = I32
         L.ols_emu_stencil_hop.argtypes = [I32, I32, I32]
         L.ols_emu_stencil_hop.restype = I32
+        L.ols_emu_dh_slots.argtypes = [I64, I64, I32, I32, I32, I32, I32, P]
+        L.ols_emu_dh_slots.restype = I32
+        L.ols_emu_split_tile.argtypes = [I64, I64, I64, I32, I64, P]
+        L.ols_emu_split_tile.restype = None
+        L.ols_emu_tail_shape.argtypes = [I32, I32, I64, I64, I64, I64, P]
+        L.ols_emu_tail_shape.restype = None
         L.ols_emu_stencil_response.argtypes = [I32, I32, I32, P, P]
         L.ols_emu_delay_phases.argtypes = [I32, I32, P]
         L.ols_emu_delay_rows.argtypes = [I32, I32, I32]
@@ -226,6 +232,27 @@ def wave_block(N: int) -> int:
     if emu().ols_emu_wave_block(N, out) != 0:
         raise ValueError(N)
     return int(out[0])
+
+
+def dh_slots(U: int, P: int, upt: int, fpu: int, segs: int, paired: bool, K: int) -> np.ndarray:
+    """Which of the adjoint's P x segs dh slots its tail reads for each of K filters."""
+    out = np.zeros((P * segs, K), dtype=np.uint8)
+    if emu().ols_emu_dh_slots(U, P, upt, fpu, segs, int(paired), K, _ptr(out)) != 0:
+        raise ValueError(segs)
+    return out.astype(bool)
+
+
+def split_tile(U: int, P: int, upt: int, by_tile: bool, unit: int):
+    """(tile, first, last workgroup) of one unit of the tail's ds part, or None."""
+    out = (ctypes.c_int64 * 3)()
+    emu().ols_emu_split_tile(U, P, upt, int(by_tile), unit, out)
+    return tuple(out) if out[0] >= 0 else None
+
+
+def tail_shape(segs: int, H: int, ntiles: int, upt: int, grid: int, KM: int) -> dict:
+    out = (ctypes.c_int64 * 5)()
+    emu().ols_emu_tail_shape(segs, H, ntiles, upt, grid, KM, out)
+    return dict(zip(("nfix", "split", "by_tile", "ndh", "lags"), out))
 
 
 def stencil_response(N: int, w, left: int) -> np.ndarray:
