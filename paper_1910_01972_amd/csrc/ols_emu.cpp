@@ -759,6 +759,26 @@ void ols_emu_row_shift_geometry(const void* y, int64_t Ns, int N, int D, int H, 
   out[1] = rs.mask;
 }
 
+// out = filters per unit, threads per workgroup of a forward call (forward_shape).
+// flags: 1 the library chose nf, 2 R2R, 4 power, 8 rows on the grid, 16 rows re-aligned.
+void ols_emu_forward_shape(int N, int K, int H, int nf, int flags, int64_t ntrans, int64_t full, int32_t* out) {
+  ols::ForwardCall c{};
+  c.N = N;
+  c.K = K;
+  c.H = H;
+  c.nf = nf;
+  c.nf_auto = flags & 1;
+  c.real = flags & 2;
+  c.power = flags & 4;
+  c.on_grid = flags & 8;
+  c.realigned = flags & 16;
+  c.ntrans = ntrans;
+  c.full = full;
+  const ols::ForwardShape s = ols::forward_shape(c);
+  out[0] = s.nf;
+  out[1] = s.wg;
+}
+
 // Adjoint through the kernel dataflow: ds[N_s], dh[K][M].
 int ols_emu_backward(int N, const float* s, int64_t Ns, const float* gy, const float* h, int K, int M, int D, int H,
                      int grid, float* ds, float* dh) {

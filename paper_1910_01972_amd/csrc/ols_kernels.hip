@@ -287,7 +287,7 @@ constexpr int forward_lds() {
 // neighbouring segments arrive at different times, and the launch falls into a
 // slower state of the write stream.  One barrier per unit keeps them together:
 // in complex forwards whose workgroups hold several transforms of more than a
-// wave (call_shape says when), 2^22 x 32 x 64, N = 2048: 227 -> 208 us, and in
+// wave (forward_shape says when), 2^22 x 32 x 64, N = 2048: 227 -> 208 us, and in
 // the staged kernels up to N = 4096 (two phases, us, N = 2048, 2^23 x 32 x 256:
 // 817 -> 771; N = 4096, 2^23 x 32 x 500: 838 -> 807; R2R, N = 2048, 2^22 x 32 x
 // 100: 231 -> 218).  Not where the transforms and taps bind more than the stores:
@@ -1694,7 +1694,7 @@ struct ols_plan_s {
   int block = 0;  // threads per workgroup
   int segs = 0;   // segments per tile
   int nf = 1;     // filters per work unit of the forward kernel
-  bool nf_auto = true;  // nf is the library's choice: calls may take fewer (Kern::call_shape)
+  bool nf_auto = true;  // nf is the library's choice: calls may take another (forward_shape)
   int flags = 0;  // OLS_POST_* and OLS_REAL
   bool stencil_on = false;  // non-local stage (ols_plan_set_stencil)
   int stencil_R = 0;        // its reach ahead (taps after the sample)
@@ -1743,7 +1743,7 @@ template <int N>
 struct Kern {
   using GE = Geo<N>;
   static constexpr bool HAS_NF2 = N <= 4096;       // selectable (ols_plan_set_tiling)
-  static constexpr bool CALL_NF2 = HAS_NF2 || N == 8192;  // for some calls (call_shape)
+  static constexpr bool CALL_NF2 = HAS_NF2 || N == 8192;  // for some calls (forward_shape)
 
   // the plan's spectra, and its spectra for every row delay if it holds them
   static hipError_t spectra(const ols_plan_s* p, const void* h, hipStream_t st) {
@@ -1761,22 +1761,8 @@ struct Kern {
     hipLaunchKernelGGL(ols_spectra_natural_kernel<N>, dim3((unsigned)blocks), dim3(threads), 0, st, F, K, out);
     return hipGetLastError();
   }
-  // Threads per workgroup of the forward kernels: one transform, or one wave
-  // of narrower ones, is the smallest (NARROW).  A unit then holds one segment,
-  // so short calls spread over more CUs, long ones end more evenly, and a
-  // barrier joins only the waves of one transform.  Measured against 256
-  // threads (us, complex, one GPU): N = 1024, 2^20 x 1 8.0 -> 7.0, 2^13 x 4
-  // 6.2 -> 4.9, 2^22 x 64 438 -> 427; N = 2048, 2^18 x 7 11.4 -> 10.4,
-  // 2^21 x 7 33.9 -> 31.1, 2^23 x 32 (one filter per unit) 447 -> 433.  Long
-  // calls keep 256 threads where the spectra are loaded without prefetch or
-  // fit in L1, because the segments of such a workgroup read each spectrum
-  // through one L1 at the same time: two filters per unit at N = 2048 (2^23 x
-  // 32: 441 against 452 with 128), R2R at N = 1024 (2^23 x 16: 114.5 against
-  // 120.7), and N <= 512 (2^22 x 8, N = 512: 57.1 against 61.4).
-  static constexpr int NARROW = GE::G <= 64 ? 64 : GE::G;
-  static constexpr int wide(int nf, bool real) {
-    return (N <= 512 || (N == 1024 && real) || (N == 2048 && nf == 2)) ? GE::WG : NARROW;
-  }
+  static constexpr int NARROW = narrow_threads(N);
+  static constexpr int wide(int nf, bool real) { return wide_threads(N, nf, real); }
   // Forward kernel instance for (filters per unit, power epilogue, R2R, workgroup).
   using ForwardFn = void (*)(const void*, int64_t, const float2*, void*, int, int, int, int64_t, const float2*, int);
   template <int NF, bool REAL, int WG>
@@ -1839,72 +1825,11 @@ struct Kern {
     }
     return stencil_fn_nf<1>(power, real);
   }
-  // How one call runs: filters per unit and threads per workgroup.  A choice of
-  // the call's size and the plan's occupancy, not of the grid set by
-  // ols_plan_set_tiling.
-  struct Shape {
-    int nf, wg;
-  };
-  // Workgroups of wg threads that stand for `groups` of GE::WG threads.
-  static int64_t slots(int groups, int wg) { return (int64_t)groups * (GE::WG / wg); }
-  static int64_t units(const ols_plan_s* p, int64_t ntrans, Shape c) {
-    const int segs = c.wg / GE::G;
-    return (ntrans + segs - 1) / segs * ((p->K + c.nf - 1) / c.nf);
-  }
-  // on_grid: the output rows need no delayed filters.
-  static Shape call_shape(const ols_plan_s* p, int64_t ntrans, bool on_grid) {
-    if (p->staged()) return Shape{p->nf, GE::WG};
-    if (p->stencil_on) return Shape{1, wide(1, (p->flags & OLS_REAL) != 0)};  // folded
-    Shape c{p->nf, NARROW};
-    if constexpr (N == 2048 || N == 4096) {
-      // Plans that leave the tiling to the library: one filter per unit, with
-      // prefetched spectra and twice the units (us, two -> one filter,
-      // workgroups of one transform: N = 2048, 2^18 x 32 24.6 -> 20.5, 2^20
-      // x 32 65.2 -> 58.7; N = 4096, 2^15 x 16 9.1 -> 7.3, 2^18 x 16 19.3 ->
-      // 16.9), except where two filters give every workgroup one unit and one
-      // filter does not (2^16 x 32, N = 2048: 10.0 against 12.6), and from
-      // N4096_NF2_UNITS units per workgroup at N = 4096, where the pair's
-      // shared barriers count (2^23 x 32: 446 against 457).
-      if (p->nf_auto && c.nf == 2) {
-        constexpr int N4096_NF2_UNITS = 8;
-        const int64_t S = slots(p->full, NARROW), u1 = units(p, ntrans, Shape{1, NARROW});
-        const bool pairs = (u1 > S && units(p, ntrans, c) <= S) || (N == 4096 && u1 >= N4096_NF2_UNITS * S);
-        if (!pairs) c.nf = 1;
-      }
-    }
-    if constexpr (N == 8192) {
-      // pairs only where they give every workgroup one unit and single filters do
-      // not (2^20 x 2 18.3 -> 14.4 us, 2^18 x 8 17.8 -> 14.4, 2^17 x 16 17.6 ->
-      // 14.5); elsewhere the pair kernel, without prefetched spectra, is 3-30 % slower
-      const int64_t S = slots(p->full, NARROW);
-      const Shape two{2, NARROW};
-      if (p->nf_auto && !(p->flags & OLS_REAL) && units(p, ntrans, c) > S && units(p, ntrans, two) <= S) c = two;
-    }
-    // 256-thread workgroups, where they pay, from WIDE_UNITS units each on
-    // (N = 512, 2^20 x 8: 4.3 units, 20.7 against 20.1 us with 64 threads;
-    // R2R N = 1024, 2^19 x 8: 2.1 units, 12.3 against 11.9, 2^21 x 8: 4.1 units,
-    // 20.6 against 21.5; N = 2048, two filters, 2^18 x 32: 2.3 units, 26.0 against
-    // 24.6, 2^19 x 32: 4.6 units, 36.9 against 37.5)
-    constexpr int WIDE_UNITS = N <= 512 ? 8 : 4;
-    const Shape w{c.nf, wide(c.nf, (p->flags & OLS_REAL) != 0)};
-    if (w.wg != NARROW && units(p, ntrans, w) >= WIDE_UNITS * slots(p->full, w.wg)) c = w;
-    if constexpr (N == 2048) {
-      // Banks of many short filters, which write as fast as the HBM takes it: two
-      // segments per workgroup, their waves in step (step_forward).  us, 128 -> 256
-      // threads: 2^22 x 32 x 64 227 -> 208, 2^23 x 32 x 32 439 -> 416, 3000000 x 32 x
-      // 112 171 -> 158, 2^19 x 32 x 32 35.0 -> 32.8.  Other calls are bound by the
-      // transforms as well and keep the narrow ones: from 128 aliased samples on
-      // (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444), fewer filters
-      // (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113 against 120), rows off
-      // the 128-byte grid (2^23 + 1, x 32 x 64: 485 against 492), and few units per
-      // workgroup (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5).
-      constexpr int STEP_FILTERS = 24, STEP_ALIASED = 128, STEP_UNITS = 6;
-      const Shape step{1, GE::WG};
-      if (c.nf == 1 && !(p->flags & (OLS_REAL | OLS_POST_POWER)) && on_grid && p->K >= STEP_FILTERS &&
-          N - p->H < STEP_ALIASED && units(p, ntrans, step) >= STEP_UNITS * slots(p->full, step.wg))
-        c = step;
-    }
-    return c;
+  // How one call runs (forward_shape; the stage and the fold have one shape each).
+  static ForwardShape call_shape(const ols_plan_s* p, const ForwardCall& call) {
+    if (p->staged()) return ForwardShape{p->nf, GE::WG};
+    if (p->stencil_on) return ForwardShape{1, wide(1, call.real)};  // folded
+    return forward_shape(call);
   }
   static hipError_t forward(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
     // output rows off the 128-byte grid read the plan's spectra for each
@@ -1918,10 +1843,22 @@ struct Kern {
     const int H = rs.H;
     const int64_t nseg = (Ns + H - 1) / H;
     const int64_t ntrans = (p->flags & OLS_REAL) ? (nseg + 1) / 2 : nseg;  // R2R: segment pairs
-    const Shape c = call_shape(p, ntrans, rs.mask == 0);
+    ForwardCall call{};
+    call.N = N;
+    call.K = p->K;
+    call.H = H;
+    call.nf = p->nf;
+    call.nf_auto = p->nf_auto;
+    call.real = (p->flags & OLS_REAL) != 0;
+    call.power = (p->flags & OLS_POST_POWER) != 0;
+    call.on_grid = (uintptr_t)y % SHIFT_LINE == 0 && Ns % (SHIFT_LINE / (float_out ? 4 : 8)) == 0;
+    call.realigned = rs.mask != 0;
+    call.ntrans = ntrans;
+    call.full = p->full;
+    const ForwardShape c = call_shape(p, call);
     const int segs = c.wg / GE::G;
     const int64_t ntiles = (ntrans + segs - 1) / segs;
-    const int64_t u = units(p, ntrans, c), most = slots(p->grid, c.wg), grid = u < most ? u : most;
+    const int64_t u = call.units(c), most = (int64_t)p->grid * (GE::WG / c.wg), grid = u < most ? u : most;
     if (p->staged()) {
       // J <= 2 phases go out as one element per sample when y is aligned to it
       Stencil sten = p->stencil;

@@ -984,6 +984,96 @@ OLS_HD RowShift batch_row_shift(const void* y, int64_t Ns, int N, int D) {
   return row_shift_geometry(y, Ns, N, D, N - D, 8, true);
 }
 
+// ---------------------------------------------------------------------------
+// How one forward call runs: filters per unit and threads per workgroup.  A
+// choice of the call's size and the plan's occupancy, not of the grid set by
+// ols_plan_set_tiling.
+// ---------------------------------------------------------------------------
+// Threads per workgroup.  One transform, or one wave of narrower ones, is the
+// smallest (narrow).  A unit then holds one segment, so short calls spread over
+// more CUs, long ones end more evenly, and a barrier joins only the waves of one
+// transform.  Measured against 256 threads (us, complex, one GPU): N = 1024,
+// 2^20 x 1 8.0 -> 7.0, 2^13 x 4 6.2 -> 4.9, 2^22 x 64 438 -> 427; N = 2048, 2^18
+// x 7 11.4 -> 10.4, 2^21 x 7 33.9 -> 31.1, 2^23 x 32 (one filter per unit) 447 ->
+// 433.  Long calls keep 256 threads (base) where the spectra are loaded without
+// prefetch or fit in L1, because the segments of such a workgroup read each
+// spectrum through one L1 at the same time: two filters per unit at N = 2048
+// (2^23 x 32: 441 against 452 with 128), R2R at N = 1024 (2^23 x 16: 114.5
+// against 120.7), and N <= 512 (2^22 x 8, N = 512: 57.1 against 61.4).
+OLS_HD constexpr int base_threads(int N) { return N / 16 >= 256 ? N / 16 : 256; }
+OLS_HD constexpr int narrow_threads(int N) { return N / 16 <= 64 ? 64 : N / 16; }
+OLS_HD constexpr int wide_threads(int N, int nf, bool real) {
+  return (N <= 512 || (N == 1024 && real) || (N == 2048 && nf == 2)) ? base_threads(N) : narrow_threads(N);
+}
+struct ForwardShape {
+  int nf, wg;
+};
+struct ForwardCall {
+  int N, K, H;         // H: the call's hop
+  int nf;              // the plan's filters per unit
+  bool nf_auto;        // they are the library's choice
+  bool real, power;
+  bool on_grid;        // output rows on the 128-byte grid
+  bool realigned;      // off it, with delayed filters (row_shift_geometry)
+  int64_t ntrans;      // transforms: segments, or segment pairs (R2R)
+  int64_t full;        // workgroups of base_threads at full occupancy
+  // Workgroups of wg threads that fill the device, and the units they share.
+  OLS_HD int64_t slots(int wg) const { return full * (base_threads(N) / wg); }
+  OLS_HD int64_t units(ForwardShape s) const {
+    const int segs = s.wg / (N / 16);
+    return (ntrans + segs - 1) / segs * ((K + s.nf - 1) / s.nf);
+  }
+  // Units of the longest workgroup.
+  OLS_HD int64_t longest(ForwardShape s) const { return (units(s) + slots(s.wg) - 1) / slots(s.wg); }
+  OLS_HD bool at_least(ForwardShape s, int per_workgroup) const { return units(s) >= per_workgroup * slots(s.wg); }
+};
+OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
+  const int N = c.N, narrow = narrow_threads(N), base = base_threads(N);
+  ForwardShape s{c.nf, narrow};
+  const ForwardShape one{1, narrow}, two{2, narrow};
+  // Plans that leave the tiling to the library: one filter per unit, with
+  // prefetched spectra and twice the units (us, two -> one filter, workgroups of
+  // one transform: N = 2048, 2^18 x 32 24.6 -> 20.5, 2^20 x 32 65.2 -> 58.7; N =
+  // 4096, 2^15 x 16 9.1 -> 7.3, 2^18 x 16 19.3 -> 16.9), except where two
+  // filters give every workgroup one unit and one filter does not (2^16 x 32, N
+  // = 2048: 10.0 against 12.6; N = 8192, whose pair kernel has no prefetched
+  // spectra and is 3-30 % slower elsewhere: 2^20 x 2 18.3 -> 14.4, 2^18 x 8
+  // 17.8 -> 14.4).
+  const bool one_unit = c.units(one) > c.slots(narrow) && c.units(two) <= c.slots(narrow);
+  if (c.nf_auto && c.nf == 2 && N == 2048 && !one_unit) s.nf = 1;
+  if (c.nf_auto && c.nf == 2 && N == 4096) {
+    // Two filters from N4096_NF2_UNITS units per workgroup on, where the pair's
+    // shared barriers count (2^23 x 32: 446 against 457).
+    constexpr int N4096_NF2_UNITS = 8;
+    if (!one_unit && !c.at_least(one, N4096_NF2_UNITS)) s.nf = 1;
+  }
+  if (c.nf_auto && N == 8192 && !c.real && one_unit) s.nf = 2;
+  // base_threads, where they pay, from 8 (N <= 512) or 4 units each on (N = 512,
+  // 2^20 x 8: 4.3 units, 20.7 against 20.1 us with 64 threads; R2R N = 1024, 2^19
+  // x 8: 2.1 units, 12.3 against 11.9, 2^21 x 8: 4.1 units, 20.6 against 21.5; N =
+  // 2048, two filters, 2^18 x 32: 2.3 units, 26.0 against 24.6, 2^19 x 32: 4.6
+  // units, 36.9 against 37.5)
+  const ForwardShape w{s.nf, wide_threads(N, s.nf, c.real)}, b{s.nf, base};
+  if (w.wg != narrow && c.at_least(w, N <= 512 ? 8 : 4)) s = w;
+  const int aliased = N - c.H;
+  if (N == 2048 && s.nf == 1) {
+    // Two segments per workgroup, their waves in step (step_forward).  us, 128 ->
+    // 256 threads:
+    //   - banks of many short filters on the grid, which write as fast as the HBM
+    //     takes it: 2^22 x 32 x 64 227 -> 208, 2^23 x 32 x 32 439 -> 406, 3000000 x
+    //     32 x 112 169 -> 154, 2^19 x 32 x 32 35.0 -> 32.8.  Not from 128 aliased
+    //     samples on (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444),
+    //     with fewer filters (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113
+    //     against 120), off the grid (2^23 + 1 x 32 x 64 485 against 492) or few
+    //     units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5).
+    constexpr int STEP_ALIASED = 128, STEP_UNITS = 6;
+    const bool shorts = aliased < STEP_ALIASED, complex = !c.real && !c.power;
+    const bool step = complex && c.on_grid && shorts && c.K >= 24;
+    if (step && c.at_least(b, STEP_UNITS)) s = b;
+  }
+  return s;
+}
+
 // Classes of batched items, (N, filters per unit): the kernel takes the items
 // class by class (stable within a class), so that each workgroup meets each
 // class in one run of tiles.

@@ -37,6 +37,8 @@ def emu() -> ctypes.CDLL:
         L.ols_emu_stencil_delay.restype = I32
         L.ols_emu_stencil_hop.argtypes = [I32, I32, I32]
         L.ols_emu_stencil_hop.restype = I32
+        L.ols_emu_forward_shape.argtypes = [I32, I32, I32, I32, I32, I64, I64, P]
+        L.ols_emu_forward_shape.restype = None
         L.ols_emu_dh_slots.argtypes = [I64, I64, I32, I32, I32, I32, I32, P]
         L.ols_emu_dh_slots.restype = I32
         L.ols_emu_split_tile.argtypes = [I64, I64, I64, I32, I64, P]
@@ -232,6 +234,26 @@ def wave_block(N: int) -> int:
     if emu().ols_emu_wave_block(N, out) != 0:
         raise ValueError(N)
     return int(out[0])
+
+
+def forward_shape(N: int, K: int, M: int, Ns: int, *, full: int = 512, nf: int = 0, real: bool = False,
+                  power: bool = False, y_addr: int = 0, delays: bool = True) -> tuple:
+    """(filters per unit, threads per workgroup) of a forward call on a device
+    that holds `full` workgroups.  nf = 0: the library's tiling; delays: the plan
+    holds its delayed spectra."""
+    L, el = emu(), 4 if real or power else 8
+    geo = (ctypes.c_int32 * 2)()
+    D = -(-(M - 1) // 16) * 16
+    H, realigned = N - D, False
+    if delays and K * Ns >= 1 << 22:
+        L.ols_emu_row_shift_geometry(ctypes.c_void_p(y_addr), Ns, N, D, H, el, geo)
+        H, realigned = geo[0], geo[1] != 0
+    nseg = -(-Ns // H)
+    on_grid = y_addr % 128 == 0 and Ns % (128 // el) == 0
+    auto_nf = 2 if N in ((2048,) if real else (2048, 4096)) and (K % 2 == 0 or K >= 9) else 1
+    flags = (nf == 0) + 2 * real + 4 * power + 8 * on_grid + 16 * realigned
+    L.ols_emu_forward_shape(N, K, H, nf or auto_nf, flags, -(-nseg // 2) if real else nseg, full, geo)
+    return geo[0], geo[1]
 
 
 def dh_slots(U: int, P: int, upt: int, fpu: int, segs: int, paired: bool, K: int) -> np.ndarray:
