@@ -1042,10 +1042,12 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
   const bool one_unit = c.units(one) > c.slots(narrow) && c.units(two) <= c.slots(narrow);
   if (c.nf_auto && c.nf == 2 && N == 2048 && !one_unit) s.nf = 1;
   if (c.nf_auto && c.nf == 2 && N == 4096) {
-    // Two filters from N4096_NF2_UNITS units per workgroup on, where the pair's
-    // shared barriers count (2^23 x 32: 446 against 457).
+    // a pair costs 1.86 single units (us, one / two filters: 1290944 x 4 x
+    // 1300, 4 and 2 units 20.9 / 18.2, x 60, 3 and 2 units 17.7 / 20.6; 1710519
+    // x 4 x 1571, 6 and 3 units 28.6 / 25.1), and from N4096_NF2_UNITS units per
+    // workgroup the pair's shared barriers count (2^23 x 32: 446 against 457)
     constexpr int N4096_NF2_UNITS = 8;
-    if (!one_unit && !c.at_least(one, N4096_NF2_UNITS)) s.nf = 1;
+    if (15 * c.longest(two) > 8 * c.longest(one) && !c.at_least(one, N4096_NF2_UNITS)) s.nf = 1;
   }
   if (c.nf_auto && N == 8192 && !c.real && one_unit) s.nf = 2;
   // base_threads, where they pay, from 8 (N <= 512) or 4 units each on (N = 512,

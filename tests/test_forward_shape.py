@@ -31,8 +31,8 @@ CASES = [
     (2048, 1024, 400, 5040, {}, (1, 128)),
     # N = 4096: pairs by what the longest workgroup gets
     (4096, 16, 512, 1 << 18, {}, (1, 256)), (4096, 32, 512, 1 << 23, {}, (2, 256)),
-    (4096, 4, 60, 1290944, {}, (1, 256)),
-    (4096, 7, 1300, 737680, {}, (1, 256)), (4096, 2, 1300, 2581888, REAL, (1, 256)),
+    (4096, 4, 1300, 1290944, {}, (2, 256)), (4096, 4, 60, 1290944, {}, (1, 256)), (4096, 4, 1571, 1710519, {}, (2, 256)),
+    (4096, 7, 1300, 737680, {}, (1, 256)), (4096, 2, 1300, 2581888, POWER, (2, 256)), (4096, 2, 1300, 2581888, REAL, (1, 256)),
     # N = 8192 (one workgroup of 512 threads per CU), N = 512 and 256
     (8192, 2, 2048, 1 << 20, dict(full=256), (2, 512)), (8192, 8, 2048, 1 << 24, dict(full=256), (1, 512)),
     (512, 8, 32, 1 << 20, {}, (1, 64)), (512, 8, 32, 1 << 22, {}, (1, 256)), (256, 8, 20, 1 << 18, {}, (1, 64)),
