@@ -1771,15 +1771,12 @@ struct Kern {
   }
   template <int NF, bool REAL>
   static ForwardFn forward_fn_nf(int wg, bool power) {
-    return wg == NARROW ? forward_fn_wg<NF, REAL, NARROW>(power) : forward_fn_wg<NF, REAL, wide(NF, REAL)>(power);
+    return wg == NARROW ? forward_fn_wg<NF, REAL, NARROW>(power) : forward_fn_wg<NF, REAL, GE::WG>(power);
   }
   static ForwardFn forward_fn(int nf, int flags, int wg) {
     const bool power = (flags & OLS_POST_POWER) != 0, real = (flags & OLS_REAL) != 0;
     if constexpr (CALL_NF2) {
       if (nf == 2 && !real) return forward_fn_nf<2, false>(wg, power);
-      if constexpr (N == 2048) {
-        if (wg == GE::WG && !real && !power) return ols_forward_kernel<N, 1, false, false, GE::WG>;
-      }
       // R2R takes two filters per unit only up to N = 2048 (choose_nf_real)
       if constexpr (N <= BATCH_NF2_MAX_N) {
         if (nf == 2) return forward_fn_nf<2, true>(wg, power);

@@ -1057,21 +1057,42 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
   // units, 36.9 against 37.5)
   const ForwardShape w{s.nf, wide_threads(N, s.nf, c.real)}, b{s.nf, base};
   if (w.wg != narrow && c.at_least(w, N <= 512 ? 8 : 4)) s = w;
+  const int64_t bank = (int64_t)c.K * N * 8;  // bytes of spectra; an XCD's L2 holds 4 MiB
   const int aliased = N - c.H;
+  if (N == 1024) {
+    // Banks that the L2 does not hold: a spectrum read by four segments at once,
+    // unless the longest workgroup gets many more units by it.  us, 64 -> 256 threads: 10080 x
+    // 512 x 200 17.2 -> 14.8, 23168 x 1024 x 200 64 -> 42, 92672 x 1024 x 19 201 ->
+    // 164, power 18240 x 1300 x 19 47 -> 33, two filters per unit 17888 x 1182 x 133
+    // 60 -> 50.  Fewer filters are level or slower (20160 x 256 x 19 14.5 against
+    // 15.1), and so are fewer units (5040 x 1024 x 19: 3 units and 4, 14.2 against
+    // 14.9).
+    const ForwardShape narrowest{s.nf, narrow};
+    const int64_t n = c.longest(narrowest);
+    if (bank >= ((int64_t)4 << 20) && n >= 2 && 4 * c.longest(b) <= 5 * n) s = b;
+  }
   if (N == 2048 && s.nf == 1) {
-    // Two segments per workgroup, their waves in step (step_forward).  us, 128 ->
-    // 256 threads:
+    // Two segments per workgroup; complex outputs with their waves in step
+    // (step_forward).  us, 128 -> 256 threads:
     //   - banks of many short filters on the grid, which write as fast as the HBM
     //     takes it: 2^22 x 32 x 64 227 -> 208, 2^23 x 32 x 32 439 -> 406, 3000000 x
     //     32 x 112 169 -> 154, 2^19 x 32 x 32 35.0 -> 32.8.  Not from 128 aliased
     //     samples on (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444),
     //     with fewer filters (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113
     //     against 120), off the grid (2^23 + 1 x 32 x 64 485 against 492) or few
-    //     units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5).
+    //     units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5);
+    //   - banks of twice the L2, one segment at a time up to 6 TB/s of spectra:
+    //     39537 x 600 x 400 67 -> 60, 72993 x 1300 x 400 (no delayed spectra) 250 ->
+    //     204, power 51616 x 1300 x 60 133 -> 96, R2R 111841 x 600 x 60 85 -> 70;
+    //     complex on the grid, of four times (23168 x 1024 x 400 70 -> 48; 158176 x
+    //     600 x 400 157 against 168).  Where neighbouring workgroups happen to work
+    //     on the same filters the L2 serves them either way, and the narrow ones
+    //     are up to 10 % faster (power 39536 x 600 x 400 38 against 42).
     constexpr int STEP_ALIASED = 128, STEP_UNITS = 6;
     const bool shorts = aliased < STEP_ALIASED, complex = !c.real && !c.power;
     const bool step = complex && c.on_grid && shorts && c.K >= 24;
-    if (step && c.at_least(b, STEP_UNITS)) s = b;
+    const bool large = bank >= ((int64_t)(complex && c.on_grid ? 16 : 8) << 20);
+    if ((step || large) && c.at_least(b, STEP_UNITS)) s = b;
   }
   return s;
 }
