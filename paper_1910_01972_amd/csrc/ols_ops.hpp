@@ -1060,16 +1060,20 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
   const int64_t bank = (int64_t)c.K * N * 8;  // bytes of spectra; an XCD's L2 holds 4 MiB
   const int aliased = N - c.H;
   if (N == 1024) {
-    // Banks that the L2 does not hold: a spectrum read by four segments at once,
-    // unless the longest workgroup gets many more units by it.  us, 64 -> 256 threads: 10080 x
+    // Banks that the L2 does not hold, and many rows off the grid (whose spectra
+    // lie delay by delay): a spectrum read by four segments at once, unless the
+    // longest workgroup gets many more units by it.  us, 64 -> 256 threads: 10080 x
     // 512 x 200 17.2 -> 14.8, 23168 x 1024 x 200 64 -> 42, 92672 x 1024 x 19 201 ->
     // 164, power 18240 x 1300 x 19 47 -> 33, two filters per unit 17888 x 1182 x 133
-    // 60 -> 50.  Fewer filters are level or slower (20160 x 256 x 19 14.5 against
-    // 15.1), and so are fewer units (5040 x 1024 x 19: 3 units and 4, 14.2 against
-    // 14.9).
+    // 60 -> 50; off the grid 40337 x 128 x 19 17.6 -> 14.7, 370721 x 64 x 19 53.3 ->
+    // 49.9.  Fewer filters are level or slower (on the grid 20160 x 256 x 19 14.5
+    // against 15.1, off it 215153 x 24 x 19 16.1 against 16.0), and so are fewer
+    // units (5040 x 1024 x 19: 3 units and 4, 14.2 against 14.9; 80673 x 64 x 19,
+    // off the grid: 3 and 3, 15.6 against 16.2).
     const ForwardShape narrowest{s.nf, narrow};
     const int64_t n = c.longest(narrowest);
-    if (bank >= ((int64_t)4 << 20) && n >= 2 && 4 * c.longest(b) <= 5 * n) s = b;
+    const bool rows = c.realigned && (c.K >= 128 || (c.K >= 64 && n >= 8));
+    if ((bank >= ((int64_t)4 << 20) || rows) && n >= 2 && 4 * c.longest(b) <= 5 * n) s = b;
   }
   if (N == 2048 && s.nf == 1) {
     // Two segments per workgroup; complex outputs with their waves in step
@@ -1079,8 +1083,11 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     //     32 x 112 169 -> 154, 2^19 x 32 x 32 35.0 -> 32.8.  Not from 128 aliased
     //     samples on (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444),
     //     with fewer filters (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113
-    //     against 120), off the grid (2^23 + 1 x 32 x 64 485 against 492) or few
-    //     units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6 units: 28.7 -> 27.5);
+    //     against 120) or few units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6
+    //     units: 28.7 -> 27.5);
+    //   - re-aligned rows the other way round: long filters, 741441 x 32 x 400 52.4
+    //     -> 48.5, 1482897 x 64 x 400 179 -> 166, not short ones (2^23 + 1 x 32 x 64
+    //     485 against 492) nor fewer rows (5931633 x 16 x 400 171 against 182);
     //   - banks of twice the L2, one segment at a time up to 6 TB/s of spectra:
     //     39537 x 600 x 400 67 -> 60, 72993 x 1300 x 400 (no delayed spectra) 250 ->
     //     204, power 51616 x 1300 x 60 133 -> 96, R2R 111841 x 600 x 60 85 -> 70;
@@ -1090,7 +1097,7 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     //     are up to 10 % faster (power 39536 x 600 x 400 38 against 42).
     constexpr int STEP_ALIASED = 128, STEP_UNITS = 6;
     const bool shorts = aliased < STEP_ALIASED, complex = !c.real && !c.power;
-    const bool step = complex && c.on_grid && shorts && c.K >= 24;
+    const bool step = complex && ((c.on_grid && shorts && c.K >= 24) || (c.realigned && !shorts && c.K >= 32));
     const bool large = bank >= ((int64_t)(complex && c.on_grid ? 16 : 8) << 20);
     if ((step || large) && c.at_least(b, STEP_UNITS)) s = b;
   }
