@@ -238,8 +238,7 @@ def sweep_measurement(launches: int = 10, rounds: int = 3) -> dict:
         y = torch.empty((K, Ns), dtype=torch.complex64, device="cuda")
         plans = {N: OLSPlan(h, N=N) for N in tuner.CANDIDATES if N >= M and 4 * (N - M + 1) >= N}
         auto = OLSPlan(h, N=0)
-        chosen, hop = auto.info()["N"], auto.info()["H"]
-        tiling, grid = auto.tiling(), auto.launch()["grid"]
+        chosen, ran = auto.info()["N"], auto.call(Ns, y)
         auto.close()
         times = {N: [] for N in plans}
         for p in plans.values():
@@ -259,12 +258,11 @@ def sweep_measurement(launches: int = 10, rounds: int = 3) -> dict:
         best = min(med, key=med.get)
         alg = 8.0 * K * Ns + 8.0 * Ns + 8.0 * K * M
         frac = lambda ms: alg / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9)
-        # the cost model's configuration: hop H, tiling, and segments per
-        # persistent workgroup S (average over the grid)
-        cells.append({"M": M, "K": K, "cost_model_N": chosen, "hop": hop,
-                      "filters_per_unit": tiling["filters_per_unit"],
-                      "workgroups_per_cu": tiling["workgroups_per_cu"],
-                      "segments_per_workgroup": round(-(-Ns // hop) / grid, 2),
+        # what the cost model's plan launches: hop H, filters per unit, threads
+        # and workgroups, and segments per workgroup S (average over the grid)
+        cells.append({"M": M, "K": K, "cost_model_N": chosen, "hop": ran["hop"],
+                      "filters_per_unit": ran["filters_per_unit"], "block": ran["block"], "grid": ran["grid"],
+                      "segments_per_workgroup": round(-(-Ns // ran["hop"]) / ran["grid"], 2),
                       "cost_model_ms": med[chosen], "cost_model_frac": frac(med[chosen]),
                       "cost_model_GBps": alg / (med[chosen] * 1e-3) / 1e9, "best_N": best, "best_ms": med[best],
                       "best_frac": frac(med[best]), "samples_per_s": K * Ns / (med[chosen] * 1e-3),
@@ -585,9 +583,9 @@ def main():
     y = torch.empty((wl.K, wl.Ns), dtype=torch.complex64, device=dev)
     plan = OLSPlan(h, N=wl.N)
     info = plan.info()
-    launch = plan.launch()
-    nf = plan.tiling()["filters_per_unit"]
-    launch_key = {"N": info["N"], "grid": launch["grid"], "block": launch["block"], "filters_per_unit": nf}
+    launch = plan.call(wl.Ns, y)  # what a step launches
+    launch_key = {"N": info["N"], "grid": launch["grid"], "block": launch["block"],
+                  "filters_per_unit": launch["filters_per_unit"]}
     stream = torch.cuda.current_stream()
 
     settle = settle_clocks(lambda: plan.forward(s, y), args.settle_ms)
@@ -633,8 +631,9 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": WORKLOAD,
-            "Ns": wl.Ns, "K": wl.K, "M": wl.M, "N": info["N"], "hop": info["H"], "delay": info["D"],
-            "grid": launch["grid"], "block": launch["block"], "cus": launch["cus"], "filters_per_unit": nf,
+            "Ns": wl.Ns, "K": wl.K, "M": wl.M, "N": info["N"], "hop": launch["hop"], "delay": info["D"],
+            "grid": launch["grid"], "block": launch["block"], "cus": plan.launch()["cus"],
+            "filters_per_unit": launch["filters_per_unit"],
         },
         "roofline": {
             # the metric is the HBM roofline; "floors" says which floor binds

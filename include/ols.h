@@ -404,7 +404,7 @@ ols_status_t ols_calibration_copy(void* dst, const void* src, size_t bytes, ols_
  * the persistent grid of ols_forward for this plan, in workgroups of `block`
  * threads (256, or 512 at N = 8192).  A call may run as smaller workgroups with
  * as many threads in all (one transform, or one wave of them, each), and
- * launches no more than it has work units. */
+ * launches no more than it has work units: ols_plan_get_call says what it does. */
 ols_status_t ols_plan_get_launch(ols_plan_t plan, int32_t* grid, int32_t* block, int32_t* cus);
 
 /*
@@ -419,6 +419,7 @@ ols_status_t ols_plan_get_launch(ols_plan_t plan, int32_t* grid, int32_t* block,
  *                      (2 only for N <= 4096, and N <= 2048 for R2R);
  *                      0 restores the library's choice: one value is
  *                      reported, each call takes what its size needs
+ *                      (ols_plan_get_call)
  *   workgroups_per_cu  1 .. the kernel's occupancy; 0 = the occupancy
  * The workgroup count leaves the output bit-identical; the filters-per-unit
  * choice selects another kernel instance, whose results may differ in the
@@ -429,6 +430,16 @@ ols_status_t ols_plan_set_tiling(ols_plan_t plan, int32_t filters_per_unit, int3
 /* Current tiling (see ols_plan_set_tiling) and the occupancy limit for it. */
 ols_status_t ols_plan_get_tiling(ols_plan_t plan, int32_t* filters_per_unit, int32_t* workgroups_per_cu,
                                  int32_t* max_workgroups_per_cu);
+
+/*
+ * ols_plan_get_call -- how ols_forward of N_s samples into y runs: filters per
+ * unit, threads per workgroup, workgroups (0 for N_s = 0) and hop.  They follow
+ * from the plan's tiling (ols_plan_set_tiling) and from the size of the call;
+ * of y only the alignment matters (NULL: as a 128-byte aligned one), nothing is
+ * read or launched.  Any output pointer may be NULL.  Errors: INVALID_VALUE.
+ */
+ols_status_t ols_plan_get_call(ols_plan_t plan, int64_t N_s, const void* y, int32_t* filters_per_unit, int32_t* block,
+                               int32_t* grid, int32_t* hop);
 
 #ifdef __cplusplus
 }

@@ -1701,6 +1701,7 @@ struct ols_plan_s {
   Stencil stencil{};
   // the stage kernel; else a stencil is folded into the segments' spectra (Response)
   bool staged() const { return stencil_on && (stencil.J > 1 || !fold_stencil(N)); }
+  bool float_out() const { return (flags & (OLS_REAL | OLS_POST_POWER)) != 0; }  // outputs of 4 bytes, else 8
   void* bwd_mem = nullptr;  // the adjoint's scratch, allocated by ols_plan_reserve_backward
   BwdWorkspace bwd{};       // carved from bwd_mem for the adjoint's full grid
   float2* spectra = nullptr;
@@ -1822,57 +1823,64 @@ struct Kern {
     }
     return stencil_fn_nf<1>(power, real);
   }
-  // How one call runs (forward_shape; the stage and the fold have one shape each).
-  static ForwardShape call_shape(const ols_plan_s* p, const ForwardCall& call) {
-    if (p->staged()) return ForwardShape{p->nf, GE::WG};
-    if (p->stencil_on) return ForwardShape{1, wide(1, call.real)};  // folded
-    return forward_shape(call);
-  }
-  static hipError_t forward(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
+  // How the forward of Ns samples into y runs (forward_shape; the stage and the
+  // fold have one shape each).
+  struct Launch {
+    RowShift rs;
+    ForwardShape c;
+    int64_t ntiles, grid;
+  };
+  static Launch forward_launch(const ols_plan_s* p, int64_t Ns, const void* y) {
+    Launch l{};
     // output rows off the 128-byte grid read the plan's spectra for each
     // row's delay (the call only reads the plan)
-    const bool float_out = (p->flags & (OLS_REAL | OLS_POST_POWER)) != 0;
+    const int el = p->float_out() ? 4 : 8;
     // (a folded stencil needs its reach ahead free of the delay too)
-    const RowShift rs = row_shift_geometry(
-        y, Ns, N - p->stencil_R, p->D, p->H, float_out ? 4 : 8,
-        p->spectra_delays && !p->staged() && (int64_t)p->K * Ns >= SHIFT_MIN_OUTPUTS);
-    const float2* F = rs.mask ? p->spectra_delays : p->spectra;
-    const int H = rs.H;
-    const int64_t nseg = (Ns + H - 1) / H;
-    const int64_t ntrans = (p->flags & OLS_REAL) ? (nseg + 1) / 2 : nseg;  // R2R: segment pairs
+    l.rs = row_shift_geometry(y, Ns, N - p->stencil_R, p->D, p->H, el,
+                              p->spectra_delays && !p->staged() && (int64_t)p->K * Ns >= SHIFT_MIN_OUTPUTS);
+    const int64_t nseg = (Ns + l.rs.H - 1) / l.rs.H;
     ForwardCall call{};
     call.N = N;
     call.K = p->K;
-    call.H = H;
+    call.H = l.rs.H;
     call.nf = p->nf;
     call.nf_auto = p->nf_auto;
     call.real = (p->flags & OLS_REAL) != 0;
     call.power = (p->flags & OLS_POST_POWER) != 0;
-    call.on_grid = (uintptr_t)y % SHIFT_LINE == 0 && Ns % (SHIFT_LINE / (float_out ? 4 : 8)) == 0;
-    call.realigned = rs.mask != 0;
-    call.ntrans = ntrans;
+    call.on_grid = (uintptr_t)y % SHIFT_LINE == 0 && Ns % (SHIFT_LINE / el) == 0;
+    call.realigned = l.rs.mask != 0;
+    call.ntrans = call.real ? (nseg + 1) / 2 : nseg;  // R2R: segment pairs
     call.full = p->full;
-    const ForwardShape c = call_shape(p, call);
-    const int segs = c.wg / GE::G;
-    const int64_t ntiles = (ntrans + segs - 1) / segs;
-    const int64_t u = call.units(c), most = (int64_t)p->grid * (GE::WG / c.wg), grid = u < most ? u : most;
+    if (p->staged()) l.c = ForwardShape{p->nf, GE::WG};
+    else if (p->stencil_on) l.c = ForwardShape{1, wide(1, call.real)};  // folded
+    else l.c = forward_shape(call);
+    const int segs = l.c.wg / GE::G;
+    l.ntiles = (call.ntrans + segs - 1) / segs;
+    const int64_t u = call.units(l.c), most = (int64_t)p->grid * (GE::WG / l.c.wg);
+    l.grid = u < most ? u : most;
+    return l;
+  }
+  static hipError_t forward(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
+    const Launch l = forward_launch(p, Ns, y);
+    const float2* F = l.rs.mask ? p->spectra_delays : p->spectra;
+    const dim3 grid((unsigned)l.grid), block(l.c.wg);
     if (p->staged()) {
       // J <= 2 phases go out as one element per sample when y is aligned to it
       Stencil sten = p->stencil;
-      const uintptr_t el = (uintptr_t)sten.J * (float_out ? 4 : 8);
+      const uintptr_t el = (uintptr_t)sten.J * (p->float_out() ? 4 : 8);
       sten.packed = sten.J <= 2 && (uintptr_t)y % el == 0;
-      hipLaunchKernelGGL(stencil_fn(c.nf, p->flags), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, p->spectra, y,
-                         p->K, p->D, p->H, ntiles, p->twiddles, sten);
+      hipLaunchKernelGGL(stencil_fn(l.c.nf, p->flags), grid, block, 0, st, s, Ns, p->spectra, y, p->K, p->D, p->H,
+                         l.ntiles, p->twiddles, sten);
     } else if (p->stencil_on) {
       Response resp{};
       resp.T = p->stencil.T;
       resp.L = p->stencil.L;
       for (int d = 0; d < resp.T; ++d) resp.w[d] = p->stencil.w[0][d];
-      hipLaunchKernelGGL(fold_fn(p->flags), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, F, y, p->K, p->D, H,
-                         ntiles, p->twiddles, rs.mask, resp, p->roots);
+      hipLaunchKernelGGL(fold_fn(p->flags), grid, block, 0, st, s, Ns, F, y, p->K, p->D, l.rs.H, l.ntiles,
+                         p->twiddles, l.rs.mask, resp, p->roots);
     } else
-      hipLaunchKernelGGL(forward_fn(c.nf, p->flags, c.wg), dim3((unsigned)grid), dim3(c.wg), 0, st, s, Ns, F, y,
-                         p->K, p->D, H, ntiles, p->twiddles, rs.mask);
+      hipLaunchKernelGGL(forward_fn(l.c.nf, p->flags, l.c.wg), grid, block, 0, st, s, Ns, F, y, p->K, p->D, l.rs.H,
+                         l.ntiles, p->twiddles, l.rs.mask);
     return hipGetLastError();
   }
   // Workgroups of GE::WG threads per CU (or as many threads in smaller ones).
@@ -1968,6 +1976,17 @@ template <int N>
 struct RunForward {
   static hipError_t run(const ols_plan_s* p, const void* s, int64_t Ns, void* y, hipStream_t st) {
     return Kern<N>::forward(p, s, Ns, y, st);
+  }
+};
+template <int N>
+struct RunForwardLaunch {
+  static int run(const ols_plan_s* p, int64_t Ns, const void* y, int32_t* out) {
+    const auto l = Kern<N>::forward_launch(p, Ns, y);
+    out[0] = l.c.nf;
+    out[1] = l.c.wg;
+    out[2] = (int32_t)l.grid;
+    out[3] = l.rs.H;
+    return 0;
   }
 };
 template <int N>
@@ -2423,6 +2442,19 @@ ols_status_t ols_plan_get_tiling(ols_plan_t p, int32_t* nf, int32_t* wpc, int32_
     if (e != hipSuccess) return hip_fail(e, "occupancy query");
     *max_wpc = per_cu < 1 ? 1 : per_cu;
   }
+  return OLS_SUCCESS;
+}
+
+ols_status_t ols_plan_get_call(ols_plan_t p, int64_t Ns, const void* y, int32_t* nf, int32_t* block, int32_t* grid,
+                               int32_t* hop) {
+  if (!p) return fail(OLS_ERROR_INVALID_VALUE, "plan is NULL");
+  if (Ns < 0) return fail(OLS_ERROR_INVALID_VALUE, "N_s must be >= 0");
+  if (Ns > ((int64_t)1 << 56) / 8 / p->K) return fail(OLS_ERROR_INVALID_VALUE, "K*N_s*8 overflows");
+  int32_t v[4];
+  (void)dispatch<RunForwardLaunch>(p->N, (const ols_plan_s*)p, Ns, y, v + 0);
+  int32_t* const out[4] = {nf, block, grid, hop};
+  for (int i = 0; i < 4; ++i)
+    if (out[i]) *out[i] = v[i];
   return OLS_SUCCESS;
 }
 

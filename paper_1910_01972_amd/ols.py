@@ -161,6 +161,14 @@ class OLSPlan:
         check(lib().ols_plan_get_tiling(self.handle, *[ctypes.byref(x) for x in v]), "ols_plan_get_tiling")
         return dict(zip(("filters_per_unit", "workgroups_per_cu", "max_workgroups_per_cu"), (x.value for x in v)))
 
+    def call(self, Ns: int, y: torch.Tensor | None = None) -> dict:
+        """How forward() of Ns samples (into y) runs: filters per unit, threads
+        per workgroup, workgroups and hop."""
+        v = [ctypes.c_int32() for _ in range(4)]
+        check(lib().ols_plan_get_call(self.handle, int(Ns), None if y is None else y.data_ptr(),
+                                      *[ctypes.byref(x) for x in v]), "ols_plan_get_call")
+        return dict(zip(("filters_per_unit", "block", "grid", "hop"), (x.value for x in v)))
+
     def set_hop(self, H: int) -> None:
         check(lib().ols_plan_set_hop(self.handle, int(H)), "ols_plan_set_hop")
 

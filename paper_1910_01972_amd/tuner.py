@@ -123,12 +123,11 @@ def tune(M: int, K: int, Ns: int = 1 << 22, reps: int = 10, candidates=CANDIDATE
     automatic = key == "auto"
     if not automatic:
         cfg = tuple(int(v) for v in key.split("x"))
-    H = plan.info()["H"]
-    cus = plan.launch()["cus"]
+    plan.set_tiling(*((0, 0) if automatic else cfg))
+    ran = plan.call(Ns, y)  # what the chosen configuration launches
     plan.close()
-    nseg = -(-Ns // H)
     return {"M": M, "K": K, "Ns": Ns, "N": best, "automatic": automatic, "filters_per_unit": cfg[0],
-            "workgroups_per_cu": cfg[1], "segments_per_workgroup": nseg / (cfg[1] * cus), "ms": times, "tiling_ms": tiling_ms}
+            "workgroups_per_cu": cfg[1], "segments_per_workgroup": -(-Ns // ran["hop"]) / ran["grid"], "ms": times, "tiling_ms": tiling_ms}
 
 
 class TuneCache:
@@ -204,13 +203,14 @@ def sweep(reps: int = 10, tune_ns: int = 1 << 22):
             if not t["automatic"]:
                 plan.set_tiling(t["filters_per_unit"], t["workgroups_per_cu"])
             ms = min(ms, _time_forward(plan, s, y, max(reps, 20), warmup=20))
+        ran = plan.call(wl.Ns, y)  # the tuned tiling's
         auto = OLSPlan(h, N=0)
         auto_n = auto.info()["N"]
         auto.close()
         alg = 8.0 * wl.K * wl.Ns + 8.0 * wl.Ns + 8.0 * wl.K * wl.M
         rec = {"cell": wl.name, "M": wl.M, "K": wl.K, "Ns": wl.Ns, "tuned_N": t["N"], "cost_model_N": auto_n,
-               "filters_per_unit": t["filters_per_unit"], "workgroups_per_cu": t["workgroups_per_cu"],
-               "segments_per_workgroup": -(-wl.Ns // plan.info()["H"]) / plan.launch()["grid"],
+               "filters_per_unit": ran["filters_per_unit"], "block": ran["block"], "grid": ran["grid"],
+               "segments_per_workgroup": -(-wl.Ns // ran["hop"]) / ran["grid"],
                "proxy_ms": t["ms"], "proxy_tiling_ms": t["tiling_ms"], "ms_default_tiling": ms_default,
                "ms": ms, "samples_per_s": wl.K * wl.Ns / (ms * 1e-3),
                "GBps": alg / (ms * 1e-3) / 1e9, "hbm_frac": alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
@@ -223,18 +223,19 @@ def sweep(reps: int = 10, tune_ns: int = 1 << 22):
 def run_config(M: int, K: int, Ns: int, N: int, nf: int, wpc: int, reps: int = 10) -> dict:
     """The forward for one (M, K) on Ns synthetic samples with a fixed FFT
     length and tiling (0: the library's choice): reps timed launches after
-    two warm-ups.  Reports the configuration that ran."""
+    two warm-ups.  Reports the plan's tiling and persistent grid, and under
+    "call" what a call of this size launches."""
     from .ols import OLSPlan
     s, h = synthetic(Ns, K, M, seed=M * 1000 + K)
     y = torch.empty((K, Ns), dtype=torch.complex64, device="cuda")
     plan = OLSPlan(h, N=N)
     plan.set_tiling(nf, wpc)
     ms = _time_forward(plan, s, y, reps)
-    launch, tiling = plan.launch(), plan.tiling()
+    launch, tiling, ran = plan.launch(), plan.tiling(), plan.call(Ns, y)
     n_used = plan.fft_length()
     plan.close()
     return {"M": M, "K": K, "Ns": Ns, "N": n_used, "filters_per_unit": tiling["filters_per_unit"],
-            "workgroups_per_cu": tiling["workgroups_per_cu"], "ms": ms, "grid": launch["grid"]}
+            "workgroups_per_cu": tiling["workgroups_per_cu"], "ms": ms, "grid": launch["grid"], "call": ran}
 
 
 def main(argv=None):

@@ -25,11 +25,8 @@ class Plan:
         nf, wpc = self.fixed or (2, 2)
         return {"filters_per_unit": nf, "workgroups_per_cu": wpc, "max_workgroups_per_cu": 2}
 
-    def info(self):
-        return {"N": self.N, "H": self.N // 2}
-
-    def launch(self):
-        return {"grid": 512, "block": 256, "cus": 256}
+    def call(self, Ns, y=None):
+        return {"filters_per_unit": 1, "block": 128, "grid": 1024, "hop": self.N // 2}
 
     def close(self):
         pass
