@@ -169,8 +169,9 @@ ols_status_t ols_plan_set_hop(ols_plan_t plan, int32_t H);
  * With y aligned to J output elements (always for J = 1), one or two phases
  * per sample are written as one element.  A stencil with one phase is a
  * convolution: up to N = 4096 it is applied to the segments' spectra instead
- * of to staged outputs (results agree to rounding), one filter per unit.  A
- * plan with a stencil has no ols_backward (UNSUPPORTED).
+ * of to staged outputs (results agree to rounding), one filter per unit
+ * whatever ols_plan_set_tiling asks for (and reported so).  A plan with a
+ * stencil has no ols_backward (UNSUPPORTED).
  * Errors: INVALID_VALUE (null plan or w, J, left, right out of range, filter
  * too long for the stencil), HIP.
  */

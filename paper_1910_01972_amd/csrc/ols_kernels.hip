@@ -2416,6 +2416,7 @@ ols_status_t ols_plan_set_tiling(ols_plan_t p, int32_t nf, int32_t wpc) {
     const bool nf_auto = nf == 0;
     if (nf_auto) nf = (p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K);
     if (!nf_allowed(p, nf)) return fail(OLS_ERROR_INVALID_VALUE, "filters_per_unit must be 1 or 2 (2 only for N <= 4096, R2R N <= 2048)");
+    if (p->stencil_on && !p->staged()) nf = 1;  // the fold has no filter pairs
     int per_cu = 0;
     hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, p->stencil_on ? p->stencil.J : 0, &per_cu);
     if (e != hipSuccess) return hip_fail(e, "occupancy query");

@@ -51,3 +51,18 @@ def test_call_is_what_the_rule_says(N, K, M, Ns, flags):
     with pytest.raises(ols.OLSError):
         plan.call(-1)
     plan.close()
+
+
+@pytest.mark.parametrize("N,weights,folds", [(1024, [[-1.0, 1.0]], True), (4096, [[0.5, 0.5]], True),
+                                             (2048, [[0.0, 1.0], [0.5, 0.5]], False)])
+def test_tiling_of_a_stencil_is_reported_as_it_runs(N, weights, folds):
+    """A folded stencil takes one filter per unit whatever tiling is asked for,
+    and says so; a staged one takes the two it is given."""
+    from paper_1910_01972_amd import ols
+    print(f"stencil tiling report N={N}", flush=True)
+    h = dev(workloads.make_signal_filters(1, 4, 30, seed=2)[1])
+    plan = ols.OLSPlan(h, N=N, stencil=(weights, 1))
+    plan.set_tiling(2, 0)  # accepted, as before
+    want = 1 if folds else 2
+    assert plan.tiling()["filters_per_unit"] == want and plan.call(100000)["filters_per_unit"] == want
+    plan.close()
