@@ -263,7 +263,7 @@ __global__ void ols_spectra_natural_kernel(const float2* __restrict__ F, int K, 
 // N = 1024 for complex outputs: that kernel now needs more than 168 VGPRs
 // anyway (two workgroups per CU either way), and prefetch measured 3-4 %
 // faster with 8 or 16 filters, level with 1 or 24, and 2 % faster on one
-// filter over 2^20 samples.  The power kernel (167 VGPRs, three workgroups
+// filter over 2^20 samples.  The power kernel (142 VGPRs, three workgroups
 // per CU without it) does not.
 template <int N, int NF>
 constexpr bool prefetch_spectra() { return NF == 1 && N != 1024; }
@@ -287,7 +287,7 @@ constexpr int forward_lds() {
 // neighbouring segments arrive at different times, and the launch falls into a
 // slower state of the write stream.  One barrier per unit keeps them together:
 // in complex forwards whose workgroups hold several transforms of more than a
-// wave (forward_shape says when), 2^22 x 32 x 64, N = 2048: 227 -> 208 us, and in
+// wave (forward_shape says when), 2^22 x 32 x 64, N = 2048: 226 -> 204 us, and in
 // the staged kernels up to N = 4096 (two phases, us, N = 2048, 2^23 x 32 x 256:
 // 817 -> 771; N = 4096, 2^23 x 32 x 500: 838 -> 807; R2R, N = 2048, 2^22 x 32 x
 // 100: 231 -> 218).  Not where the transforms and taps bind more than the stores:
@@ -505,8 +505,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ol
 // The forward kernel with a one-phase stencil folded into the segments'
 // spectra: one filter per unit.  Kernels of their own, because the transfer
 // function's 64 registers would otherwise be every forward kernel's.  The
-// backward difference on 2^23 x 32 x 256: staged like the other stencils 567
-// us, folded 437 (the plain forward 429).
+// backward difference on 2^23 x 32 x 256: staged like the other stencils 565
+// us, folded 429 (the plain forward 428).
 template <int N, bool POWER, bool REAL, int WG>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2))) void ols_forward_fold_kernel(
     const void* __restrict__ s, int64_t Ns, const float2* __restrict__ F, void* __restrict__ y, int K, int D, int H,
@@ -1027,9 +1027,10 @@ __device__ __attribute__((noinline)) BatchWalk batched_run(const BatchItem* __re
   }
 }
 
-// Two filters per unit only up to N = 2048 here (BATCH_NF2_MAX_N): the
-// N = 4096 two-filter body needs more than 256 registers as a separate
-// function, which would drop the whole kernel to one wave per SIMD.
+// Two filters per unit only up to N = 2048 here (BATCH_NF2_MAX_N): the N = 4096
+// two-filter body fits (248 VGPRs, no spills) and is no faster (us, one / two
+// filters: 16 signals of 2^21 with 16 filters of 500 taps 1074 / 1066, with 9 of
+// 900 705 / 739, 128 uneven signals 1617 / 1652).
 
 template <int N>
 __device__ __forceinline__ BatchWalk batched_class(const BatchItem* __restrict__ items, int nitems, BatchWalk w,
@@ -2359,8 +2360,10 @@ ols_status_t ols_plan_set_stencil(ols_plan_t p, int32_t J, int32_t L, int32_t R,
       for (int j = 0; j < J; ++j)
         for (int d = 0; d < st.T; ++d) st.w[j][d] = w[j * st.T + d];
     }
-    // one filter per unit with the stage: with two, the stage kernels at
-    // N = 2048 spill registers and measured 5-15 % slower
+    // one filter per unit with the stage (us at N = 2048, two -> one filter):
+    // faster on calls of few units (2^20 x 8 x 100, cubic midpoint 42.7 -> 40.6,
+    // its power 35.4 -> 31.7, R2R 32.5 -> 26.5), level on long ones (2^22 x 32 x
+    // 256 409 -> 400, three phases 1710 -> 1751)
     const int nf = J != 0 ? 1 : ((p->flags & OLS_REAL) ? choose_nf_real(p->N, p->K) : choose_nf(p->N, p->K));
     int per_cu = 0;
     hipError_t e = dispatch<RunOccupancy>(p->N, nf, p->flags, (int)J, &per_cu);

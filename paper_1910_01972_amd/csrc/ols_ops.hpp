@@ -1079,8 +1079,8 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     // Two segments per workgroup; complex outputs with their waves in step
     // (step_forward).  us, 128 -> 256 threads:
     //   - banks of many short filters on the grid, which write as fast as the HBM
-    //     takes it: 2^22 x 32 x 64 227 -> 208, 2^23 x 32 x 32 439 -> 406, 3000000 x
-    //     32 x 112 169 -> 154, 2^19 x 32 x 32 35.0 -> 32.8.  Not from 128 aliased
+    //     takes it: 2^22 x 32 x 64 226 -> 204, 2^23 x 32 x 32 438 -> 416, 3000000 x
+    //     32 x 112 170 -> 168, 2^19 x 32 x 32 36.6 -> 35.5.  Not from 128 aliased
     //     samples on (2^23 x 32: M = 128 415 against 423, M = 256 427 against 444),
     //     with fewer filters (2^22 x 16 x 64 109.7 against 111.6, 2^23 x 8 x 64 113
     //     against 120) or few units (2^18 x 32 x 64, 4 units: 21.4 against 22.1; 6
@@ -1132,8 +1132,9 @@ OLS_HD int64_t next_batch_tile(int64_t t, int64_t P) { return t + P; }
 constexpr int BATCH_SHARE_WEIGHT = 88;
 OLS_HD int64_t batch_item_weight(int64_t ntiles, int K) { return ntiles * (1 + (int64_t)K); }
 OLS_HD bool batch_shares(int64_t total_weight, int64_t P) { return total_weight < BATCH_SHARE_WEIGHT * P; }
-// First unit of an item at or past weight off (0 <= off <= the item's weight;
-// within the shared batches' bounds the product stays small).
+// Unit of an item that weight off falls in (0 <= off <= the item's weight, which
+// gives the item's units; within the shared batches' bounds the product stays
+// small).
 OLS_HD int64_t batch_unit_at(int64_t off, int64_t units, int64_t weight) {
   return weight > 0 ? off * units / weight : 0;
 }
