@@ -1513,8 +1513,10 @@ __global__ __launch_bounds__(BwdGeo<N>::WG) __attribute__((amdgpu_waves_per_eu(2
 
 // The windows of one split tile (split_tile), summed in workgroup order; part
 // `part` of `split` workgroups.  SEGS transforms per tile, upt units per tile
-// (the filters, or the filter pairs of the paired adjoint).
-template <int N, int SEGS>
+// (the filters, or the filter pairs of the paired adjoint).  W windows are loaded
+// at a time, so that they overlap: four for the usual two, eight for tiles of many
+// workgroups (4356 x 59 x 1, N = 4096, ds: 16.7 us by fours, 15.0 by eights).
+template <int N, int SEGS, int W>
 __device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns,
                                          int64_t upt, int H, int64_t U, int64_t P, const SplitTile st, int part,
                                          int split) {
@@ -1527,24 +1529,19 @@ __device__ __forceinline__ void ds_fixup(const float2* __restrict__ ws_ds, float
   for (int e = threadIdx.x + part * TAIL_THREADS; e < SEGS * H; e += split * TAIL_THREADS) {
     if (o0 + e >= Ns) break;
     const int sg = SEGS == 1 ? 0 : e / H, p = e - sg * H;
-    // several windows at a time, so that their loads overlap
-    auto sum = [&](auto width) {
-      constexpr int W = decltype(width)::value;
-      float2 a = make_float2(0.f, 0.f);
-      for (int64_t bb = st.blo; bb <= st.bhi; bb += W) {
-        float2 v[W];
+    float2 a = make_float2(0.f, 0.f);
+    for (int64_t bb = st.blo; bb <= st.bhi; bb += W) {
+      float2 v[W];
 #pragma unroll
-        for (int k = 0; k < W; ++k) {
-          const int64_t slot = bb + k == st.blo ? slot_lo : 0;
-          if (bb + k <= st.bhi) v[k] = ws_ds[(((bb + k) * 2 + slot) * SEGS + sg) * (int64_t)N + p];
-        }
-#pragma unroll
-        for (int k = 0; k < W; ++k)
-          if (bb + k <= st.bhi) a = cadd(a, v[k]);
+      for (int k = 0; k < W; ++k) {
+        const int64_t slot = bb + k == st.blo ? slot_lo : 0;
+        if (bb + k <= st.bhi) v[k] = ws_ds[(((bb + k) * 2 + slot) * SEGS + sg) * (int64_t)N + p];
       }
-      return a;
-    };
-    ds[o0 + e] = st.bhi - st.blo < 4 ? sum(std::integral_constant<int, 4>()) : sum(std::integral_constant<int, 8>());
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+        if (bb + k <= st.bhi) a = cadd(a, v[k]);
+    }
+    ds[o0 + e] = a;
   }
 }
 
@@ -1587,9 +1584,12 @@ __device__ __forceinline__ void dh_sums(const float2* __restrict__ part, const D
 }
 
 // Workgroups [0, ndh) sum dh, which takes longer where there are many slots, the
-// others fix ds (either may be absent).
+// others fix ds (either may be absent).  Eight waves per SIMD are asked for, or
+// the compiler takes 106 scalar registers, which leave seven, and a choice of W
+// inside ds_fixup's loop costs as much: 17.7 us on the 2^22 x 16 x 512 adjoint with
+// both, 16.5 with eight waves, 15.6 so.
 template <int N, int SEGS, bool PAIRED>
-__global__ __launch_bounds__(TAIL_THREADS) void ols_backward_tail_kernel(
+__global__ __launch_bounds__(TAIL_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void ols_backward_tail_kernel(
     const float2* __restrict__ ws_ds, float2* __restrict__ ds, int64_t Ns, int H, const float2* __restrict__ part,
     const DhSlots sl, int64_t KM, float2* __restrict__ dh, const TailShape ts) {
   const int64_t blk = blockIdx.x;
@@ -1607,8 +1607,10 @@ __global__ __launch_bounds__(TAIL_THREADS) void ols_backward_tail_kernel(
     return;
   }
   const SplitTile st = split_tile(sl.U, sl.P, sl.upt, ts.by_tile != 0, (blk - ts.ndh) / ts.split);
-  if (st.t >= 0)
-    ds_fixup<N, SEGS>(ws_ds, ds, Ns, sl.upt, H, sl.U, sl.P, st, (int)((blk - ts.ndh) % ts.split), ts.split);
+  if (st.t < 0) return;
+  const int at = (int)((blk - ts.ndh) % ts.split);
+  if (st.bhi - st.blo < 4) ds_fixup<N, SEGS, 4>(ws_ds, ds, Ns, sl.upt, H, sl.U, sl.P, st, at, ts.split);
+  else ds_fixup<N, SEGS, 8>(ws_ds, ds, Ns, sl.upt, H, sl.U, sl.P, st, at, ts.split);
 }
 
 // Plain fill with zero (used instead of a memset so callers may capture it).
