@@ -1026,6 +1026,21 @@ struct ForwardCall {
   // Units of the longest workgroup.
   OLS_HD int64_t longest(ForwardShape s) const { return (units(s) + slots(s.wg) - 1) / slots(s.wg); }
   OLS_HD bool at_least(ForwardShape s, int per_workgroup) const { return units(s) >= per_workgroup * slots(s.wg); }
+  // Times that the device reads the bank's spectra, in a call of few units per
+  // workgroup: a tile starts slots / tiles workgroups after the one before, and
+  // where that is a multiple of the 8 XCDs, which take the workgroups in turn,
+  // both tiles read the same spectra through the same L2.
+  OLS_HD int64_t bank_reads(ForwardShape s) const {
+    const int segs = s.wg / (N / 16);
+    const int64_t tiles = (ntrans + segs - 1) / segs;
+    int64_t a = tiles, b = slots(s.wg) / 8;
+    while (b != 0) {
+      const int64_t r = a % b;
+      a = b;
+      b = r;
+    }
+    return a > 0 ? tiles / a : 0;
+  }
 };
 OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
   const int N = c.N, narrow = narrow_threads(N), base = base_threads(N);
@@ -1069,11 +1084,16 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     // 49.9.  Fewer filters are level or slower (on the grid 20160 x 256 x 19 14.5
     // against 15.1, off it 215153 x 24 x 19 16.1 against 16.0), and so are fewer
     // units (5040 x 1024 x 19: 3 units and 4, 14.2 against 14.9; 80673 x 64 x 19,
-    // off the grid: 3 and 3, 15.6 against 16.2).
+    // off the grid: 3 and 3, 15.6 against 16.2).  Banks of more than twice the L2
+    // are worth a third more units (8000 x 1300 x 60, 6 and 8: 32.3 -> 26.3, x 2000, 9
+    // and 12: 46.7 -> 34.7, R2R 5040 x 2000 19.6 -> 16.1; 5040 x 1300, 4 and 6: 18.4
+    // against 20.1), not with the power, whose narrow workgroups are three waves
+    // per SIMD (8000 x 2000 30.0 against 33.1).
     const ForwardShape narrowest{s.nf, narrow};
-    const int64_t n = c.longest(narrowest);
+    const int64_t n = c.longest(narrowest), m = c.longest(b);
     const bool rows = c.realigned && (c.K >= 128 || (c.K >= 64 && n >= 8));
-    if ((bank >= ((int64_t)4 << 20) || rows) && n >= 2 && 4 * c.longest(b) <= 5 * n) s = b;
+    const bool twice = bank >= ((int64_t)10 << 20) && !c.power;
+    if ((bank >= ((int64_t)4 << 20) || rows) && n >= 2 && (twice ? 3 * m <= 4 * n : 4 * m <= 5 * n)) s = b;
   }
   if (N == 2048 && s.nf == 1) {
     // Two segments per workgroup; complex outputs with their waves in step
@@ -1100,6 +1120,24 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     const bool step = complex && ((c.on_grid && shorts && c.K >= 24) || (c.realigned && !shorts && c.K >= 32));
     const bool large = bank >= ((int64_t)(complex && c.on_grid ? 16 : 8) << 20);
     if ((step || large) && c.at_least(b, STEP_UNITS)) s = b;
+    // Banks over the L2 in calls of few segments: pairs of filters and of segments,
+    // where the spectra read less often outweigh what pairs add to the longest
+    // workgroup (a unit is worth 32 MiB of spectra), and for re-aligned rows in
+    // place of two segments, where they add nothing (us, one filter -> two: 10001 x
+    // 512 x 400, 7 reads to 1, 22.9 -> 16.7, power 20.3 -> 15.7; 5040 x 1024 x 60 20.2
+    // -> 17.8, 5040 x 1500 27.4 -> 22.4; 20000 x 700 x 400 44.7 -> 38.8, R2R 20000 x
+    // 512 x 400 22.6 -> 17.6; re-aligned 10001 x 2000 x 400 59.8 -> 50.9, 14001 x 1500 x
+    // 60 49.7 -> 43.3.  Against: 8000 x 512 x 60 18.2 and 19.5, 10001 x 512 x 60, 3
+    // reads and 3, 16.3 and 19.9; longer calls are level, 39033 x 562 x 400 46.7 and
+    // 47.4).
+    constexpr int PAIR_UNITS = 16;
+    const ForwardShape pair{2, base};
+    if (c.nf_auto && c.nf == 2 && bank >= ((int64_t)4 << 20) && c.longest(s) < PAIR_UNITS) {
+      const int64_t more = 15 * c.longest(pair) - 8 * c.longest(s);
+      const int64_t less = c.bank_reads(s) - c.bank_reads(pair);
+      const bool rows = c.realigned && s.wg == base && 2 * c.longest(pair) <= c.longest(s);
+      if (rows || (less > 0 && 8 * less * bank > ((int64_t)32 << 20) * more)) s = pair;
+    }
   }
   return s;
 }
