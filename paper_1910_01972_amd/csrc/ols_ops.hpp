@@ -1026,8 +1026,8 @@ struct ForwardCall {
   // Units of the longest workgroup.
   OLS_HD int64_t longest(ForwardShape s) const { return (units(s) + slots(s.wg) - 1) / slots(s.wg); }
   OLS_HD bool at_least(ForwardShape s, int per_workgroup) const { return units(s) >= per_workgroup * slots(s.wg); }
-  // Times that the device reads the bank's spectra, in a call of few units per
-  // workgroup: a tile starts slots / tiles workgroups after the one before, and
+  // Times that the device reads the bank's spectra, as long as its workgroups keep
+  // step: a tile starts slots / tiles workgroups after the one before, and
   // where that is a multiple of the 8 XCDs, which take the workgroups in turn,
   // both tiles read the same spectra through the same L2.
   OLS_HD int64_t bank_reads(ForwardShape s) const {
@@ -1120,23 +1120,25 @@ OLS_HD ForwardShape forward_shape(const ForwardCall& c) {
     const bool step = complex && ((c.on_grid && shorts && c.K >= 24) || (c.realigned && !shorts && c.K >= 32));
     const bool large = bank >= ((int64_t)(complex && c.on_grid ? 16 : 8) << 20);
     if ((step || large) && c.at_least(b, STEP_UNITS)) s = b;
-    // Banks over the L2 in calls of few segments: pairs of filters and of segments,
-    // where the spectra read less often outweigh what pairs add to the longest
-    // workgroup (a unit is worth 32 MiB of spectra), and for re-aligned rows in
-    // place of two segments, where they add nothing (us, one filter -> two: 10001 x
-    // 512 x 400, 7 reads to 1, 22.9 -> 16.7, power 20.3 -> 15.7; 5040 x 1024 x 60 20.2
-    // -> 17.8, 5040 x 1500 27.4 -> 22.4; 20000 x 700 x 400 44.7 -> 38.8, R2R 20000 x
-    // 512 x 400 22.6 -> 17.6; re-aligned 10001 x 2000 x 400 59.8 -> 50.9, 14001 x 1500 x
-    // 60 49.7 -> 43.3.  Against: 8000 x 512 x 60 18.2 and 19.5, 10001 x 512 x 60, 3
-    // reads and 3, 16.3 and 19.9; longer calls are level, 39033 x 562 x 400 46.7 and
-    // 47.4).
-    constexpr int PAIR_UNITS = 16;
+    // Banks over the L2: pairs of filters and of segments where the spectra read
+    // less often outweigh what pairs add to the longest workgroup (a unit is worth
+    // 32 MiB of spectra), up to READS_UNITS units per workgroup, beyond which the
+    // workgroups no longer keep step; and for re-aligned rows of few units in place
+    // of two segments, where pairs add nothing (us, one filter -> two: 10001 x 512 x
+    // 400, 7 reads to 1, 22.9 -> 16.7, power 20.3 -> 15.7; 5040 x 1500 x 60 27.4 -> 22.4;
+    // 130000 x 511 x 461, 83 reads to 21, 168 -> 128, R2R 101 -> 73; 264947 x 473 x 60 263
+    // -> 242; re-aligned 10001 x 2000 x 400 59.8 -> 50.9, 14001 x 1500 x 60 49.7 -> 43.3.
+    // Against: 8000 x 512 x 60 18.2 and 19.5, 10001 x 512 x 60, 3 reads and 3, 16.3 and
+    // 19.9, 264960 x 473 x 461, 21 and 21, 220 and 231; re-aligned 39033 x 562 x 400 46.7
+    // and 47.4).
+    constexpr int READS_UNITS = 96, ROWS_UNITS = 16;
     const ForwardShape pair{2, base};
-    if (c.nf_auto && c.nf == 2 && bank >= ((int64_t)4 << 20) && c.longest(s) < PAIR_UNITS) {
-      const int64_t more = 15 * c.longest(pair) - 8 * c.longest(s);
+    if (c.nf_auto && c.nf == 2 && bank >= ((int64_t)4 << 20)) {
+      const int64_t n = c.longest(s), p = c.longest(pair);
       const int64_t less = c.bank_reads(s) - c.bank_reads(pair);
-      const bool rows = c.realigned && s.wg == base && 2 * c.longest(pair) <= c.longest(s);
-      if (rows || (less > 0 && 8 * less * bank > ((int64_t)32 << 20) * more)) s = pair;
+      const bool rows = c.realigned && s.wg == base && n < ROWS_UNITS && 2 * p <= n;
+      const bool reads = less > 0 && n <= READS_UNITS && 8 * less * bank > ((int64_t)32 << 20) * (15 * p - 8 * n);
+      if (rows || reads) s = pair;
     }
   }
   return s;
